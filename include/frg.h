@@ -145,8 +145,11 @@ int frg_integrate(frg_ctx *ctx, const frg_set *sets, int32_t n_sets, int32_t mem
 /* Tensor grid of external points sharing one quadrature:
  *   out[a * n_m + b] = I(p[a], m2[b])   (same formula as frg_set).
  * The regulator part of G(|q+p|) depends on p only, so it is evaluated once
- * per (p, node) and reused for every mass.  err_est / used_fp64 as in
- * frg_set (n_p * n_m entries, optional). */
+ * per (p, node) and reused for every mass.  Large calls with many masses form
+ * the sum at 32 masses per factor of 16 in m^2 + k^2 and interpolate the others
+ * (the interpolant differs from the sum by less than 1e-17 relative, far below
+ * rounding; masses in no such range are summed themselves).  err_est /
+ * used_fp64 as in frg_set (n_p * n_m entries, optional). */
 int frg_integrate_grid(frg_ctx *ctx, const frg_quad *quad, int64_t n_p, const double *p,
                        int64_t n_m, const double *m2, double *out, double *err_est,
                        uint8_t *used_fp64, int32_t mem, void *hip_stream);
@@ -206,8 +209,8 @@ int frg_integrate_tab(frg_ctx *ctx, const frg_quad *quad, const frg_gtab *tab, i
  * Tensor grid of configurations and masses:
  *   out[c * n_m + b] = V(p1[c], p2[c], acos(cos12[c]), m2[b]).
  * p1, p2 >= 0, -1 <= cos12 <= 1 and m2 + k^2 > 0, else NaN and FRG_E_DOMAIN
- * (host memory; device calls are asynchronous and return FRG_OK).  mem says
- * where p1, p2, cos12, m2 and out live. */
+ * (host memory; device calls are asynchronous and return FRG_OK).  Many masses
+ * as for frg_integrate_grid.  mem says where p1, p2, cos12, m2 and out live. */
 int frg_integrate_vertex(frg_ctx *ctx, const frg_quad *quad, int32_t n_azimuth, int64_t n_c,
                          const double *p1, const double *p2, const double *cos12, int64_t n_m,
                          const double *m2, double *out, int32_t mem, void *hip_stream);
@@ -441,7 +444,8 @@ int frg_autotune(frg_ctx *ctx, int32_t mode, const char *cache_path);
  * per lane, radial node and group of up to 32 angular terms, radial factor
  * included, when the table fits in LDS, the default; 1: eight-term running
  * fractions as in frg_integrate; 2 / 3: coefficients in groups of 8 / 16;
- * the forms agree to a few ulp), "grid_mfma" (coefficient form, 1: power
+ * the forms agree to a few ulp; large calls with at least 128 masses are
+ * interpolated in the mass only under form 0 with "grid_mfma" 1), "grid_mfma" (coefficient form, 1: power
  * sums over tiles of 16 masses on the FP64 matrix cores, the default; 0:
  * nested evaluation on the vector units, at most 8 masses per wave; the two
  * agree to a few ulp), "fv_persistent" (finite-volume solves, 1: one

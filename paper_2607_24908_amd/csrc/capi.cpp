@@ -561,7 +561,9 @@ int Ctx::grid_device(const frg_quad &q_in, int64_t n_p, const double *p, int64_t
   g.form = tune.grid_form;
   if (grid_lds_bytes(g) > 64 * 1024) return fail(FRG_E_INVAL, "grid tables exceed 64 KiB of LDS");
   const GridCfg cfg = grid_cfg(q, g, st);
-  rc = grid_launch(g, q.reg, cfg, st);
+  rc = mass_nodes_launch(g, q.reg, false, false, st);
+  if (rc < 0) return rc;
+  rc = rc ? FRG_OK : grid_launch(g, q.reg, cfg, st);
   if (rc || q_in.prec != FRG_PREC_FP32C) return rc;
   const int e = launch_fp64_marks(err, used, n_p * n_m, st);
   if (e) return hip_fail((hipError_t)e, "fp64_marks_kernel launch");
@@ -587,6 +589,105 @@ int Ctx::grid_launch(GridArgs g, int reg, const GridCfg &cfg_in, hipStream_t st)
   const int e = launch_grid(g, reg, cfg.M, cfg.W, st);
   if (e) return hip_fail((hipError_t)e, "grid_kernel launch");
   return FRG_OK;
+}
+
+// ---------------------------------------------------------- mass nodes --
+// Grid and vertex calls with many masses: values at the nodes of the mass
+// panels, interpolated (mass_nodes.hip), in batches of momenta whose values
+// stay within kMassValBytes.  Taken with the default form knobs when
+//   - there are at least kMassMin masses (two panels of 32 nodes are then at
+//     most half of them; masses spread over one factor of 16 to 256 in delta,
+//     the common range, fill two panels) and at most kMassMax (every workgroup
+//     looks through them);
+//   - the direct form would spend kMassWork lane slots (momenta x masses x
+//     padded nodes).  The two launches cost about 20 us before they scale:
+//     measured against the direct form, 64 x 16 nodes, 1024 momenta x 128
+//     masses (1.3e8) 24.0 against 24.9 us, 256 x 512 (1.3e8) 27.0 against
+//     25.3 us; 128 x 32 nodes, 256 x 256 (2.7e8) 31.9 against 52.2 us, 1024 x
+//     512 (2.1e9) 47 against 176 us; vertex 48 x 8 x 16, 256 x 128 (2.0e8) 36.1
+//     against 29.7 us, 256 x 512 (8.1e8) 36 against 73 us;
+//   - or a vertex table takes over half the LDS (one workgroup per CU in the
+//     direct form, whose build nothing overlaps) and there are at most a
+//     quarter as many configurations as CUs: 64 x 128 masses 24.3 against
+//     28.8 us, 16 x 512 21.5 against 36.0 us;
+//   - the buffers fit the HBM budget, and the stream is not being captured
+//     (the buffers are the context's, ordered between streams by an event
+//     that a capture cannot wait for).
+constexpr int64_t kMassMin = 128, kMassMax = 8192;
+constexpr double kMassWork = 2.5e8;
+constexpr size_t kMassValBytes = (size_t)64 << 20;
+
+int Ctx::mass_nodes_launch(const GridArgs &g_in, int reg, bool vertex, bool big_table,
+                           hipStream_t st) {
+  GridArgs g = g_in;
+  const int G = vertex ? vertex_group(g.n_phi) : grid_coef_group(g);
+  const double slots = (double)g.n_p * g.n_m * kWave * g.T * ((g.U + G - 1) / G * G);
+  const bool worth = slots >= kMassWork || (vertex && big_table && 4 * g.n_p <= n_cu);
+  if (tune.grid_form != 0 || !tune.grid_mfma || g.n_m < kMassMin || g.n_m > kMassMax || !worth ||
+      !std::isnormal(g.pref_c) || !std::isnormal(g.sig))
+    return 0;
+  if (st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return 0;
+  }
+  MassPlan m{};
+  // at most half as many nodes as masses, then one place per mass
+  m.ld = kMassNodes * std::min<int64_t>(kMassPanels, g.n_m / (2 * kMassNodes)) +
+         ((g.n_m + 31) & ~(int64_t)31);
+  m.parts = mass_nodes_parts(g.n_p, n_cu);
+  const int64_t batch = std::min<int64_t>(
+      g.n_p, std::max<int64_t>(64, (int64_t)(kMassValBytes / (sizeof(double) * m.ld))));
+  m.plane = batch * m.ld;
+  const size_t o_lag = 256;
+  const size_t o_val = o_lag + sizeof(double) * kMassNodes * g.n_m;
+  const size_t bytes = o_val + sizeof(double) * (size_t)m.plane * (m.parts > 1 ? 4 : 1);
+  const size_t node_doubles = 5 * kMassNodes, reg_doubles = (size_t)kRegPanels * kRegCoef;
+  const size_t node_bytes = sizeof(double) * (node_doubles + reg_doubles);
+  size_t more = mass_nodes.bytes ? 0 : node_bytes;
+  if (mass_scr.bytes < bytes) more += bytes - mass_scr.bytes;
+  if (hbm.used.load() + more > hbm.budget) return 0;
+  if (!mass_done && hipEventCreateWithFlags(&mass_done, hipEventDisableTiming) != hipSuccess) {
+    mass_done = nullptr;
+    return fail(FRG_E_DEVICE, "hipEventCreate");
+  }
+  if (!mass_nodes.bytes) {
+    std::vector<double> t = build_mass_nodes();
+    const std::vector<double> r = build_regulator_table();
+    t.insert(t.end(), r.begin(), r.end());
+    int rc = mass_nodes.reserve(node_bytes);
+    if (rc) return rc;
+    hipError_t e = hipMemcpy(mass_nodes.ptr, t.data(), node_bytes, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      mass_nodes.release();
+      return hip_fail(e, "upload mass nodes");
+    }
+  }
+  if (mass_scr.bytes < bytes) hipEventSynchronize(mass_done);
+  int rc = mass_scr.reserve(bytes);
+  if (rc) return rc;
+  hipError_t he = hipStreamWaitEvent(st, mass_done, 0);
+  if (he != hipSuccess) return hip_fail(he, "hipStreamWaitEvent");
+  char *base = (char *)mass_scr.ptr;
+  m.nodes = (const double *)mass_nodes.ptr;
+  m.reg = m.nodes + node_doubles;
+  m.panels = (unsigned *)base;
+  m.lag = (double *)(base + o_lag);
+  m.val = (double *)(base + o_val);
+  int e = 0;
+  for (int64_t a = 0; a < g_in.n_p && !e; a += batch) {
+    g.n_p = std::min(batch, g_in.n_p - a);
+    g.p = g_in.p + a;
+    if (vertex) {
+      g.p2 = g_in.p2 + a;
+      g.c12 = g_in.c12 + a;
+    }
+    g.out = g_in.out + a * g_in.n_m;
+    e = launch_mass_nodes(g, m, reg, vertex, a == 0, n_cu, st);
+  }
+  he = hipEventRecord(mass_done, st);
+  if (e) return hip_fail((hipError_t)e, "mass_nodes launch");
+  if (he != hipSuccess) return hip_fail(he, "hipEventRecord");
+  return 1;
 }
 
 // ------------------------------------------------------ tabulated G --
@@ -813,6 +914,10 @@ Context::~Context() {
   if (tab_done) {
     hipEventSynchronize(tab_done);
     hipEventDestroy(tab_done);
+  }
+  if (mass_done) {
+    hipEventSynchronize(mass_done);
+    hipEventDestroy(mass_done);
   }
   if (na_done) {
     hipEventSynchronize(na_done);

@@ -57,6 +57,14 @@ __device__ __forceinline__ double rcp64(double x) {
   return __builtin_fma(r, e, r);
 }
 
+// 1/x to rounding: the estimate's error e is taken to third order (one FMA more
+// than rcp64, whose e^2 <= 2.3e-15 is of one sign and so adds up in a sum).
+__device__ __forceinline__ double rcp64_full(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = __builtin_fma(-x, r, 1.0);
+  return __builtin_fma(r, __builtin_fma(e, e, e), r);
+}
+
 constexpr int kGroup = 8;
 constexpr int kHalf = 4;  // terms computed together in the exponential groups
 

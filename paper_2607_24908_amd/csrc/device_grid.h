@@ -532,9 +532,9 @@ __device__ __forceinline__ void mfma_slice_pair(const double *grp, int lane, con
   P0 = __builtin_amdgcn_mfma_f64_16x16x4f64(l0, v[kP - 1], P0, 0, 0, 0);
   P1 = __builtin_amdgcn_mfma_f64_16x16x4f64(l1, v[kP - 1], P1, 0, 0, 0);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) tot = __builtin_fma(N0[r], rcp64(P0[r]), tot);
+  for (int r = 0; r < 4; ++r) tot = __builtin_fma(N0[r], rcp64_full(P0[r]), tot);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) tot = __builtin_fma(N1[r], rcp64(P1[r]), tot);
+  for (int r = 0; r < 4; ++r) tot = __builtin_fma(N1[r], rcp64_full(P1[r]), tot);
 }
 
 // Lane partial (four rows per 16-row slice, every slice of the table) of

@@ -171,6 +171,10 @@ struct Context {
   // segmented tabulated form: partial sums, sorted term lists, their segment
   // offsets, counts + work counter
   frg::DevBuf tab_part{&hbm}, tab_terms{&hbm}, tab_offs{&hbm}, tab_scr{&hbm};
+  // mass nodes (mass_nodes.hip): constants; Lagrange rows and values of the
+  // last call, ordered between streams by mass_done
+  frg::DevBuf mass_nodes{&hbm}, mass_scr{&hbm};
+  hipEvent_t mass_done = nullptr;
   hipEvent_t tab_done = nullptr;   // after the last segmented launch (which used them)
   frg::Tune tune;
   uint64_t tune_gen = 1;  // advanced whenever a knob or a tuned choice changes
@@ -246,6 +250,9 @@ struct Context {
                     double *out, hipStream_t st);
   // autotune.cpp
   int grid_launch(GridArgs g, int reg, const GridCfg &cfg, hipStream_t st);
+  // mass_nodes.hip: 1 if the grid or vertex call in g was launched in that
+  // form, 0 if it is for the direct form, < 0 on error
+  int mass_nodes_launch(const GridArgs &g, int reg, bool vertex, bool big_table, hipStream_t st);
   GridCfg grid_cfg(const frg_quad &q, const GridArgs &g, hipStream_t st);
   int plain_tile_for(const SetDev &s, hipStream_t st);
   PersistCfg persist_cfg(const std::vector<SetDev> &sd, int prec, hipStream_t st);

@@ -307,6 +307,38 @@ constexpr int vertex_max_waves(int M, int G) { return M == 16 && G <= 16 ? 12 : 
 int vertex_lds_bytes(const GridArgs &g, int M, int W, bool table);
 int launch_vertex(const GridArgs &g, int reg, int M, int W, void *stream);
 std::vector<double> build_vertex_table(int d, int n_a, int n_phi);
+
+// Mass nodes (mass_nodes.hip): panels [16^j, 16^(j+1)) of x = sig delta, the
+// exponents kMassPanelLo .. kMassPanelHi, kMassNodes Chebyshev nodes in ln x
+// each.
+constexpr int kMassNodes = 32;
+constexpr int kMassPanelLo = -24, kMassPanelHi = 24;
+constexpr int kMassPanels = (kMassPanelHi - kMassPanelLo) / 4;
+// [x_n in [1, 16] | u_n = ln(x_n/4) as hi | lo | barycentric weights w_n as hi | lo]
+std::vector<double> build_mass_nodes();
+// h(y) = y/(1 - e^-y) - 1 in panels: [0, 5/16), eight per octave up to 40, and
+// y >= 40 (h = y - 1); kRegCoef coefficients each, ascending powers of y minus
+// the panel's middle (of y itself in the first and last).  kRegBits: exponent
+// and three mantissa bits of 5/16, less one.
+constexpr int kRegCoef = 10;
+constexpr int kRegPanels = 58;
+constexpr int kRegBits = ((1023 - 2) << 3) + 2 - 1;
+std::vector<double> build_regulator_table();
+// Device arrays of one call: panels, which of them are interpolated; lag[32 b +
+// n] the Lagrange rows; val[a ld + e] the values (32 nodes per interpolated
+// panel, then the masses; parts > 1: four planes to be added, plane doubles
+// apart).  n_lag: set by the launch.
+struct MassPlan {
+  const double *nodes, *reg;
+  unsigned *panels;
+  double *val, *lag;
+  int64_t ld, plane;
+  int parts, n_lag;
+};
+int mass_nodes_parts(int64_t n_p, int n_cu);
+// first: the first batch of momenta of the call (also forms the Lagrange rows)
+int launch_mass_nodes(const GridArgs &g, MassPlan m, int reg, bool vertex, bool first, int n_cu,
+                      void *stream);
 // Whether the FP64 grid kernel keeps its table resident, and in which form.
 bool grid_uses_coef(const GridArgs &g);
 bool grid_resident(const GridArgs &g);

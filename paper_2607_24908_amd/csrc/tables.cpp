@@ -224,6 +224,107 @@ std::vector<double> build_vertex_table(int d, int n_a, int n_phi) {
   return t;
 }
 
+// Chebyshev nodes of a mass panel in u = ln(x/4), |u| <= ln 4: x_n rounded to
+// double, u_n = ln(x_n/4) of the rounded node in two doubles, and the
+// barycentric weights of exactly these u_n (up to a common factor), in two
+// doubles.
+std::vector<double> build_mass_nodes() {
+  const int n = kMassNodes;
+  std::vector<double> t(5 * n);
+  std::vector<long double> u(n);
+  const long double pi = 3.14159265358979323846264338327950288L, half = logl(4.0L);
+  for (int i = 0; i < n; ++i) {
+    const double x = (double)(4.0L * expl(half * cosl(pi * (2 * i + 1) / (2.0L * n))));
+    u[i] = logl((long double)x / 4.0L);
+    t[i] = x;
+    t[n + i] = (double)u[i];
+    t[2 * n + i] = (double)(u[i] - (long double)t[n + i]);
+  }
+  for (int i = 0; i < n; ++i) {
+    long double w = 1.0L;
+    for (int m = 0; m < n; ++m)
+      if (m != i) w *= 0.5L * half / (u[i] - u[m]);  // capacity of the interval: w stays O(1)
+    t[3 * n + i] = (double)w;
+    t[4 * n + i] = (double)(w - (long double)t[3 * n + i]);
+  }
+  return t;
+}
+
+// Coefficients of h(y) per panel: Chebyshev interpolation in long double
+// (degree 9; 8 for h/y in the first panel, so that h keeps its relative
+// accuracy there), converted to powers of y - c.  The nearest poles of h lie
+// at +-2 pi i, so the truncation is below 2e-18 of h in every panel.
+std::vector<double> build_regulator_table() {
+  const long double pi = 3.14159265358979323846264338327950288L;
+  auto h_of = [](long double y) -> long double {
+    if (y < 0.5L) {  // Bernoulli series, |term ratio| < 0.0064
+      static const long double b[8] = {1.0L / 12, -1.0L / 720, 1.0L / 30240, -1.0L / 1209600,
+                                       1.0L / 47900160, -691.0L / 1307674368000.0L,
+                                       1.0L / 74724249600.0L, -3617.0L / 10670622842880000.0L};
+      const long double z = y * y;
+      long double t = 0.0L;
+      for (int n = 7; n >= 0; --n) t = t * z + b[n];
+      return 0.5L * y + z * t;
+    }
+    const long double w = -expm1l(-y);
+    return (y - w) / w;
+  };
+  std::vector<double> t((size_t)kRegPanels * kRegCoef, 0.0);
+  for (int k = 0; k < kRegPanels - 1; ++k) {
+    long double lo = 0.0L, hi = 0.3125L;
+    if (k > 0) {
+      const int e = (k + 1) / 8, s = (k + 1) % 8;
+      lo = ldexpl(8.0L + s, e - 5);
+      hi = ldexpl(9.0L + s, e - 5);
+    }
+    const int n = k ? kRegCoef : kRegCoef - 1;  // coefficients of h, or of h/y
+    const long double c = 0.5L * (lo + hi), w = 0.5L * (hi - lo);
+    // Chebyshev coefficients, then powers of v = (y - c)/w
+    std::vector<long double> a(n, 0.0L), f(n);
+    for (int i = 0; i < n; ++i) {
+      const long double y = c + w * cosl(pi * (2 * i + 1) / (2.0L * n));
+      f[i] = k ? h_of(y) : h_of(y) / y;
+    }
+    for (int j = 0; j < n; ++j) {
+      for (int i = 0; i < n; ++i) a[j] += f[i] * cosl(pi * j * (2 * i + 1) / (2.0L * n));
+      a[j] *= (j ? 2.0L : 1.0L) / n;
+    }
+    std::vector<long double> p(n, 0.0L), t0(n, 0.0L), t1(n, 0.0L);
+    t0[0] = 1.0L;
+    if (n > 1) t1[1] = 1.0L;
+    for (int j = 0; j < n; ++j) {
+      const std::vector<long double> &tj = j == 0 ? t0 : t1;
+      for (int i = 0; i < n; ++i) p[i] += a[j] * tj[i];
+      if (j >= 1) {  // T_{j+1} = 2 v T_j - T_{j-1}
+        std::vector<long double> t2(n, 0.0L);
+        for (int i = 0; i < n; ++i) t2[i] = (i ? 2.0L * t1[i - 1] : 0.0L) - t0[i];
+        t0 = t1;
+        t1 = t2;
+      }
+    }
+    double *dst = t.data() + (size_t)k * kRegCoef;
+    if (k) {
+      long double s = 1.0L;
+      for (int i = 0; i < n; ++i, s /= w) dst[i] = (double)(p[i] * s);
+    } else {
+      // r(v) = h/y with v = (y - c)/w, in powers of y; h = y r
+      std::vector<long double> q(n, 0.0L);
+      for (int i = n - 1; i >= 0; --i) {  // q <- q (y - c)/w + p_i
+        std::vector<long double> z(n, 0.0L);
+        for (int l = 0; l < n; ++l) z[l] = ((l ? q[l - 1] : 0.0L) - c * q[l]) / w;
+        z[0] += p[i];
+        q = z;
+      }
+      dst[0] = 0.0;
+      for (int i = 0; i < n; ++i) dst[i + 1] = (double)q[i];
+    }
+  }
+  double *last = t.data() + (size_t)(kRegPanels - 1) * kRegCoef;
+  last[0] = -1.0;
+  last[1] = 1.0;
+  return t;
+}
+
 void lane_split(int n_r, int n_a, int *R, int *J, int *T, int *U) {
   int r = 1;
   while (r * 2 <= n_r && r * 2 <= kWave) r *= 2;

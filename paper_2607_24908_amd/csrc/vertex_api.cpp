@@ -60,6 +60,8 @@ int Ctx::vertex_device(const frg_quad &q, int n_phi, int64_t n_c, const double *
   cfg.M = tune.grid_mfma ? 16 : std::min(cfg.M, 8);
   g.mblocks = 1;
   const bool big = vertex_lds_bytes(g, cfg.M, cfg.W, true) > 80 * 1024;
+  rc = mass_nodes_launch(g, q.reg, true, big, st);
+  if (rc) return rc < 0 ? rc : FRG_OK;
   if (big) cfg.W = std::min(tune.vertex_W, vertex_max_waves(cfg.M, vertex_group(n_phi)));
   const int64_t per_wg = (int64_t)cfg.M * cfg.W;
   const int64_t want_wgs = (big ? 1LL : 4LL) * n_cu;
