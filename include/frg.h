@@ -449,8 +449,8 @@ int frg_autotune(frg_ctx *ctx, int32_t mode, const char *cache_path);
  * sums over tiles of 16 masses on the FP64 matrix cores, the default; 0:
  * nested evaluation on the vector units, at most 8 masses per wave; the two
  * agree to a few ulp), "fv_persistent" (finite-volume solves, 1: one
- * workgroup per flow runs the steps with its cells in LDS, the default where
- * 3 n_cells + 2 n_radial doubles fit in 64 KiB; 0: two launches per stage;
+ * workgroup per flow runs the steps with its cells in LDS, the default up to
+ * 3339 cells, more take two launches per stage; 0: two launches per stage;
  * the same bits), "pflow_fused" (momentum-dependent flows with rows in LDS,
  * 1: one launch per RK4 stage, each workgroup redoing the previous stage's
  * update for its row, the default; 0: a diagram launch and a stage launch

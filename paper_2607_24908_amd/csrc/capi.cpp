@@ -186,10 +186,26 @@ int Ctx::lpa_table(int d, int reg, int n_r, double qmk, const double **dev, doub
     LEntry ent;
     ent.buf = std::move(buf);
     ent.Cd = t.Cd;
+    ent.host = std::move(t);
     it = ltabs.emplace(key, std::move(ent)).first;
   }
   *dev = (const double *)it->second.buf->ptr;
   *Cd = it->second.Cd;
+  return FRG_OK;
+}
+
+int Ctx::fv_panels(int d, int reg, int n_r, double qmk, const double **dev) {
+  LEntry &ent = ltabs.at(std::make_tuple(d, reg, n_r, dbits(qmk)));
+  if (!ent.panels) {
+    const std::vector<double> t = build_fv_panels(ent.host);
+    auto buf = std::make_unique<DevBuf>(&hbm);
+    int rc = buf->reserve(t.size() * sizeof(double));
+    if (rc) return rc;
+    hipError_t e = hipMemcpy(buf->ptr, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "upload finite-volume panels");
+    ent.panels = std::move(buf);
+  }
+  *dev = (const double *)ent.panels->ptr;
   return FRG_OK;
 }
 

@@ -187,6 +187,8 @@ struct Context {
   struct LEntry {
     std::unique_ptr<frg::DevBuf> buf;
     double Cd = 0.0;
+    frg::LpaTable host;
+    std::unique_ptr<frg::DevBuf> panels;  // build_fv_panels, when a finite-volume call asked
   };
   std::map<std::tuple<int, int, uint64_t, uint64_t, int, int>, QEntry> qtabs;
   std::map<std::tuple<int, int, int, uint64_t>, LEntry> ltabs;
@@ -199,6 +201,8 @@ struct Context {
   int quad_table(const frg_quad &q, const double **dev, frg::QuadTable *host_copy,
                  frg::QuadTable **host_ref = nullptr);
   int lpa_table(int d, int reg, int n_r, double qmk, const double **dev, double *Cd);
+  // polynomial panels of the finite-volume flux for a table lpa_table has made
+  int fv_panels(int d, int reg, int n_r, double qmk, const double **dev);
   int make_setdev(const frg_set &s, frg::SetDev *out);
   void fill_setdev(const frg_set &s, const frg::QuadTable &h, const double *tab, frg::SetDev *out);
   // noalloc.hip: pinned staging of the allocation-free call (filled and

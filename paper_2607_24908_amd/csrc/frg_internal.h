@@ -56,6 +56,16 @@ constexpr int kFvGroup = 8;
 constexpr int kFvCoef = 31;
 inline int fv_groups(int n_r) { return (n_r + kFvGroup - 1) / kFvGroup; }
 LpaTable build_lpa_table(int d, int reg, int n_r, double q_max_over_k);
+// Polynomial panels of the two radial sums of the finite-volume flux,
+//   s1(x) = sum_i c_i/(h_i + x),  s2(x) = sum_i c_i/(h_i + x)^2 = -s1'(x):
+// kFvPerOctave panels per octave of x from 2^kFvLo to 2^kFvHi, s1 as
+// kFvPoly coefficients of ascending powers of x - (middle of the panel), and
+// s2 as minus their derivative.
+constexpr int kFvLo = -14, kFvHi = 22;
+constexpr int kFvPerOctave = 16;
+constexpr int kFvPanels = (kFvHi - kFvLo) * kFvPerOctave;
+constexpr int kFvPoly = 11;
+std::vector<double> build_fv_panels(const LpaTable &t);
 
 double omega_sphere(int n);  // area of S^{n-1}
 double h_exp_host(double y);
@@ -186,6 +196,7 @@ struct PflowArgs {
 // bounds lam (same layout); F_n from the scale-free LPA table [chat | hhat].
 struct FvArgs {
   const double *tab;   // LpaTable::data on the device
+  const double *poly;  // build_fv_panels on the device
   double *y0;          // state at the start of the step
   double *ys;          // stage state
   double *Q, *lam;
@@ -206,12 +217,12 @@ int launch_fv_init(const FvArgs &a, double t_end, void *stream);
 int launch_fv_flux(const FvArgs &a, void *stream);
 int launch_fv_stage(const FvArgs &a, void *stream);
 int launch_fv_dt(const FvArgs &a, void *stream);
-// Steps [s0, s0 + n_st) of a solve, one workgroup of `threads` per flow with
-// its state in LDS (fv_solve_lds_bytes); alive, t_reached and flag set up by
+// Steps [s0, s0 + n_st) of a solve, one workgroup per flow with its state in
+// LDS (fv_solve_lds_bytes); alive, t_reached and flag set up by
 // launch_fv_init.
 int64_t fv_solve_lds_bytes(const FvArgs &a);
 constexpr int kFvSolveLdsMax = 160 * 1024;
-int launch_fv_solve(const FvArgs &a, int64_t s0, int64_t n_st, int threads, void *stream);
+int launch_fv_solve(const FvArgs &a, int64_t s0, int64_t n_st, void *stream);
 int launch_pflow_init(const PflowArgs &a, double t_end, void *stream);
 int launch_pflow_prep(const PflowArgs &a, int reg, void *stream);
 int launch_pflow_stage(const PflowArgs &a, int reg, void *stream);

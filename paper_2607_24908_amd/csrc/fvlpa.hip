@@ -46,10 +46,14 @@ __global__ __launch_bounds__(256) void fv_init_kernel(FvArgs a, double t_end) {
   }
 }
 
-// Scales of the stage at RG time t: k = lambda e^t, k^2, 1/k^2, k^d, k^(d-2)
-// (integer powers by products).  Every kernel forms them the same way.
+// Scales of the stage at RG time t with k = lambda e^t: k^2, 1/k^2 and the
+// factors of the radial sums in the flux (integer powers by products).  Every
+// kernel forms them the same way.
 struct FvScale {
-  double k2, inv_k2, kd, kdm2;
+  double k2, inv_k2;
+  double c1, c2;  // C_d k^d / 2, C_d k^(d-2) / 2
+  double g1, g2;  // (N - 1)/2 times them
+  double n1, n2;  // N times them
 };
 __device__ __forceinline__ FvScale fv_scale(const FvArgs &a, double t) {
   const double k = a.lambda * exp(t);
@@ -58,233 +62,263 @@ __device__ __forceinline__ FvScale fv_scale(const FvArgs &a, double t) {
   sc.inv_k2 = 1.0 / sc.k2;
   double p = 1.0;
   for (int i = 0; i < a.d - 2; ++i) p *= k;
-  sc.kdm2 = p;
-  sc.kd = p * sc.k2;
+  sc.c2 = 0.5 * a.Cd * p;
+  sc.c1 = 0.5 * a.Cd * (p * sc.k2);
+  const double g = 0.5 * (double)(a.N - 1);
+  sc.g1 = g * sc.c1;
+  sc.g2 = g * sc.c2;
+  sc.n1 = (double)a.N * sc.c1;
+  sc.n2 = (double)a.N * sc.c2;
   return sc;
 }
 
-// The masses of interface j of one flow with cell values u[0..n) (global
-// memory or LDS): d_sigma u and, on the Goldstone part (j > 0, N > 1), the
-// limited states u-/sigma_j and u+/sigma_j (nm masses).  dh[m] =
-// (m^2 + k^2)/k^2 for the masses in the domain (1 elsewhere); bad: one of them
-// has left it.  The four neighbouring cells are loaded at clamped indices
-// (issued together) and the ghost rules applied afterwards.
-struct FvIface {
-  double dh[3];
-  double um, up, isj;
-  int nm;
-  bool bad;
+// Ghost cells of one flow behind its last two cells f2, f1.
+__device__ __forceinline__ double fv_ghost(double f2, double f1) { return 2.0 * f1 - f2; }
+
+// Cells of the stencil of interface j: u_{j-2}, u_{j-1}, u_j, u_{j+1}.
+struct FvCells {
+  double LL, L, R, RR;
 };
-__device__ __forceinline__ FvIface fv_prep(const FvArgs &a, const FvScale &sc, const double *u,
-                                           int j) {
-  const int n = (int)a.n;  // at most 2^24 cells
-  const double ids = a.inv_ds;
+// ... from the cells u[0..n), n >= 2, without ghosts: loaded at clamped indices
+// (issued together), the ghost rules applied afterwards by selects.
+__device__ __forceinline__ FvCells fv_cells(const double *u, int n, int j) {
   const int nm1 = n - 1;
   auto cl = [&](int i) { return i < 0 ? 0 : (i > nm1 ? nm1 : i); };
-  const double v0 = u[cl(j - 2)], v1 = u[cl(j - 1)], v2 = u[cl(j)], v3 = u[cl(j + 1)];
-  const double e0 = u[0], e1 = u[1], f1 = u[nm1], f2 = u[n - 2];
-  const double gn = 2.0 * f1 - f2, gn1 = 2.0 * gn - f1;
-  auto cell = [&](int i, double v) {
-    return i == -1 ? -e0 : i == -2 ? -e1 : i == n ? gn : i == n + 1 ? gn1 : v;
-  };
-  FvIface f;
-  f.nm = (j > 0 && a.N > 1) ? 3 : 1;
-  f.um = 0.0;
-  f.up = 0.0;
-  f.isj = 0.0;
-  double ms;
-  if (j == 0) {
-    ms = 2.0 * e0 * ids;
-  } else {
-    const double uLL = cell(j - 2, v0), uL = cell(j - 1, v1), uR = cell(j, v2),
-                 uRR = cell(j + 1, v3);
-    ms = (uR - uL) * ids;
-    const double sL = minmod(uL - uLL, uR - uL);
-    const double sR = minmod(uR - uL, uRR - uR);
-    f.um = uL + 0.5 * sL;
-    f.up = uR - 0.5 * sR;
-    f.isj = ids / (double)j;  // 1/sigma_j
+  FvCells c{u[cl(j - 2)], u[cl(j - 1)], u[cl(j)], u[cl(j + 1)]};
+  const double f1 = j == n ? c.L : c.R, f2 = j == n ? c.LL : c.L;  // u_{n-1}, u_{n-2}
+  const double gn = fv_ghost(f2, f1);
+  const double gn1 = fv_ghost(f1, gn);
+  if (j < 2) c.LL = j == 1 ? -c.L : -c.RR;
+  if (j < 1) c.L = -c.R;
+  if (j == nm1) c.RR = gn;
+  if (j == n) {
+    c.R = gn;
+    c.RR = gn1;
   }
-  const double m2[3] = {ms, f.um * f.isj, f.up * f.isj};
-  f.bad = false;
-#pragma unroll
-  for (int m = 0; m < 3; ++m) {
-    const double delta = m2[m] + sc.k2;
-    f.bad |= m < f.nm && !(delta > 0.0);
-    f.dh[m] = (m < f.nm && delta > 0.0) ? delta * sc.inv_k2 : 1.0;
-  }
-  return f;
+  return c;
 }
 
-// s1 = sum_i chat_i/(hhat_i + x) and s2 = sum_i chat_i/(hhat_i + x)^2 over
-// all radial nodes, in one lane.  For x in [kFvXMin, kFvXMax] the table's
-// coefficient groups in order: N/P and M/P^2 by Horner with one reciprocal per
-// group of eight nodes (the powers of x and the products stay inside the
-// FP64 range there); term by term outside it.  Every term and coefficient is
-// positive and x > 0, so neither form cancels.
+// The radial sums s1 = sum_i chat_i/(hhat_i + x) and s2 = sum_i chat_i/(hhat_i +
+// x)^2.  For 2^kFvLo <= x < 2^kFvHi from the table's polynomial panels
+// (build_fv_panels; poly in LDS or global memory): s1 and its derivative by one
+// Horner pass over 11 coefficients, within 2.2e-16 and 3.3e-16 (20 FMAs; the 64
+// nodes of the usual table took 232 FMAs and 8 reciprocals as rational groups).
+// Outside the panels the coefficient groups (x in [kFvXMin, kFvXMax]): N/P and
+// M/P^2 by Horner with one reciprocal per group of eight nodes (the powers of x
+// and the products stay inside the FP64 range there); beyond those term by
+// term.  Every term and coefficient of these two is positive and x > 0, so
+// neither form cancels.
 constexpr double kFvXMin = 1e-20, kFvXMax = 1e20;
 
-// fma(a, b, c) with c wave-uniform, taken from a scalar register: written out
-// so that the compiler does not copy c into a vector register first (its
-// two-address form wants the addend there), which cost two moves per
-// coefficient.
-__device__ __forceinline__ double fma_su(double a, double b, double c) {
-  double r;
-  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
-  return r;
+// Panel of x; as an unsigned number below kFvPanels exactly for x in their range
+// (not for x <= 0, infinities and NaN).
+__device__ __forceinline__ int fv_panel(double x) {
+  static_assert(kFvPerOctave == 16, "four mantissa bits select the panel");
+  const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32);
+  int p = (int)(hi >> 16) - ((1023 + kFvLo) << 4);
+  asm("" : "+v"(p));  // the address is p times the panel's size, not a folded base below zero
+  return p;
 }
-__device__ __forceinline__ double fma_vu(double a, double b, double c) {
-  return __builtin_fma(a, b, c);
-}
-
-// One coefficient group c at x: N, r = 1/P and M r, whose terms enter the
-// sums as s1 = fma(N, r, s1), s2 = fma(M r, r, s2).  UNIFORM: c is the same
-// in every lane (scalar operands); else per lane (the same operations).
-template <bool UNIFORM>
-__device__ __forceinline__ void fv_group(double x, const double *c, double &N, double &r,
-                                         double &Mr) {
-  auto fm = [](double u, double v, double w) {
-    if constexpr (UNIFORM)
-      return fma_su(u, v, w);
-    else
-      return fma_vu(u, v, w);
-  };
-  double P = x + c[7];
+// s1[m], s2[m] at x[m] in panel p[m]; s2[0] only for FIRST.  The loads of all
+// masses first (those of the last kFvLate coefficients after the first steps, in
+// the registers these free), then their Horner chains in step (the compiler's own
+// order runs the masses one after the other, each waiting for its loads and for
+// itself).
+constexpr int kFvLate = 3;
+template <int M, bool FIRST>
+__device__ __forceinline__ void fv_poly(const double *poly, const double *x, const int *p,
+                                        double *s1, double *s2) {
+  double q[M][kFvPoly], z[M], P[M], D[M];
+  const double *qp[M];
 #pragma unroll
-  for (int k = 6; k >= 0; --k) P = fm(P, x, c[k]);
-  N = c[15];
+  for (int m = 0; m < M; ++m) {
+    const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, x[m]) >> 32);
+    const double c = __builtin_bit_cast(
+        double, (unsigned long long)((hi & 0xffff0000u) | 0x8000u) << 32);  // its middle
+    z[m] = x[m] - c;
+    qp[m] = poly + p[m] * kFvPoly;
+  }
 #pragma unroll
-  for (int k = 14; k >= 8; --k) N = fm(N, x, c[k]);
-  double M = c[30];
+  for (int k = kFvPoly - 1; k >= kFvLate; --k)
 #pragma unroll
-  for (int k = 29; k >= 16; --k) M = fm(M, x, c[k]);
-  r = rcp64(P);
-  Mr = M * r;
-}
-
-__device__ __forceinline__ bool fv_coef_range(double x) { return x >= kFvXMin && x <= kFvXMax; }
-
-__device__ __forceinline__ void fv_radial(const FvArgs &a, const double *tab,
-                                          const double *__restrict__ cf, double x, double &s1,
-                                          double &s2) {
-  s1 = 0.0;
-  s2 = 0.0;
-  if (fv_coef_range(x)) {
-    const int ng = (a.n_r + kFvGroup - 1) / kFvGroup;
-    for (int g = 0; g < ng; ++g) {
-      double N, r, Mr;
-      fv_group<true>(x, cf + kFvCoef * g, N, r, Mr);
-      s1 = __builtin_fma(N, r, s1);
-      s2 = __builtin_fma(Mr, r, s2);
+    for (int m = 0; m < M; ++m) q[m][k] = qp[m][k];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    P[m] = q[m][kFvPoly - 1];
+    D[m] = P[m];
+    P[m] = __builtin_fma(P[m], z[m], q[m][kFvPoly - 2]);
+  }
+#pragma unroll
+  for (int k = kFvPoly - 3; k >= 0; --k) {
+    if (k == kFvPoly - 5) {
+#pragma unroll
+      for (int l = kFvLate - 1; l >= 0; --l)
+#pragma unroll
+        for (int m = 0; m < M; ++m) q[m][l] = qp[m][l];
+      __builtin_amdgcn_sched_barrier(0);
     }
-  } else {
-    for (int i = 0; i < a.n_r; ++i) {
-      const double G = rcp64(tab[a.n_r + i] + x);
-      const double cg = tab[i] * G;
-      s1 += cg;
-      s2 = __builtin_fma(cg, G, s2);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      if (FIRST || m > 0) D[m] = __builtin_fma(D[m], z[m], P[m]);
+      P[m] = __builtin_fma(P[m], z[m], q[m][k]);
     }
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      asm volatile("" : "+v"(P[m]));
+      if (FIRST || m > 0) asm volatile("" : "+v"(D[m]));
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    s1[m] = P[m];
+    s2[m] = FIRST || m > 0 ? -D[m] : 0.0;
   }
 }
 
-// F_1 = C_d k^d s1 and F_2 = C_d k^(d-2) s2 from the radial sums.
-__device__ __forceinline__ void fv_scale_sums(const FvArgs &a, const FvScale &sc, double s1,
-                                              double s2, double &F1, double &F2) {
-  F1 = a.Cd * sc.kd * s1;
-  F2 = a.Cd * sc.kdm2 * s2;
-}
-
-// F_1 and F_2 at dh = x.
-__device__ __forceinline__ void fv_mass(const FvArgs &a, const FvScale &sc, const double *tab,
-                                        const double *__restrict__ cf, double x, double &F1,
-                                        double &F2) {
+struct FvSums {
   double s1, s2;
-  fv_radial(a, tab, cf, x, s1, s2);
-  fv_scale_sums(a, sc, s1, s2, F1, F2);
-}
-
-// Flux Q and the local bound lam of the step estimate at interface j from
-// its masses and F1[m], F2[m] at them.
-__device__ __forceinline__ void fv_flux(const FvArgs &a, const FvIface &f, int j,
-                                        const double *F1, const double *F2, double &Q,
-                                        double &lam) {
-  const double ids = a.inv_ds;
-  if (j == 0) {
-    Q = 0.5 * (double)a.N * F1[0];
-    lam = 2.0 * (0.5 * (double)a.N * F2[0]) * (ids * ids);
+};
+__device__ __forceinline__ FvSums fv_radial_far(const double *tab, int n_r, double x) {
+  const double *cf = tab + 2 * n_r;
+  FvSums s{0.0, 0.0};
+  if (x >= kFvXMin && x <= kFvXMax) {
+    const int ng = (n_r + kFvGroup - 1) / kFvGroup;
+#pragma unroll 1
+    for (int g = 0; g < ng; ++g) {
+      const double *c = cf + kFvCoef * g;
+      double P = x + c[7];
+      for (int k = 6; k >= 0; --k) P = __builtin_fma(P, x, c[k]);
+      double N = c[15];
+      for (int k = 14; k >= 8; --k) N = __builtin_fma(N, x, c[k]);
+      double M = c[30];
+      for (int k = 29; k >= 16; --k) M = __builtin_fma(M, x, c[k]);
+      const double r = rcp64(P);
+      s.s1 = __builtin_fma(N, r, s.s1);
+      s.s2 = __builtin_fma(M * r, r, s.s2);
+    }
   } else {
-    Q = 0.5 * F1[0];
-    lam = 2.0 * (0.5 * F2[0]) * (ids * ids);
-    if (f.nm == 3) {
-      const double c = 0.5 * (double)(a.N - 1);
-      const double am = fmax(c * F2[1] * f.isj, c * F2[2] * f.isj);
-      Q += 0.5 * (c * F1[1] + c * F1[2]) - 0.5 * am * (f.up - f.um);
-      lam += am * ids;
+#pragma unroll 1
+    for (int i = 0; i < n_r; ++i) {
+      const double G = rcp64(tab[n_r + i] + x);
+      const double cg = tab[i] * G;
+      s.s1 += cg;
+      s.s2 = __builtin_fma(cg, G, s.s2);
     }
   }
+  return s;
 }
 
-// SSP-RK3 stage `stage` (0..2) of one cell with right-hand side L.
-__device__ __forceinline__ void fv_update(int stage, double L, double h, double &y0, double &ys) {
-  switch (stage) {
-    case 0:
-      ys = y0 + h * L;
-      break;
-    case 1:
-      ys = 0.75 * y0 + 0.25 * (ys + h * L);
-      break;
-    default:
-      y0 = y0 / 3.0 + (2.0 / 3.0) * (ys + h * L);
-      break;
+// Flux Q and (LAM) the local bound lam of the step estimate at interface j from
+// the cells c of its stencil; isj = 1/sigma_j, 0 for j = 0 (zero), where d_sigma u
+// = (u_0 - u_{-1})/ds = 2 u_0/ds is the only mass that enters.  The masses are
+// d_sigma u and, for N > 1 (GOLD), the limited states u-/sigma_j and u+/sigma_j;
+// bad: one of them has left the domain.  All masses of the interface in one lane,
+// so that their panel loads and Horner chains fill each other's latency; a mass
+// outside the domain is outside the panels too, so only the other branch looks.
+struct FvOut {
+  double Q, lam;
+  bool bad;
+};
+template <bool GOLD, bool LAM>
+__device__ __forceinline__ FvOut fv_iface(const FvArgs &a, const FvScale &sc, const double *poly,
+                                          const FvCells &c, double isj, bool zero) {
+  constexpr int M = GOLD ? 3 : 1;
+  const double ids = a.inv_ds;
+  double jump = 0.0, delta[M], x[M], s1[M], s2[M];
+  int p[M];
+  const double b = c.R - c.L;
+  delta[0] = __builtin_fma(b, ids, sc.k2);
+  if constexpr (GOLD) {
+    const double um = __builtin_fma(0.5, minmod(c.L - c.LL, b), c.L);
+    const double up = __builtin_fma(-0.5, minmod(b, c.RR - c.R), c.R);
+    jump = up - um;
+    delta[1] = __builtin_fma(um, isj, sc.k2);
+    delta[2] = __builtin_fma(up, isj, sc.k2);
   }
+  bool near = true;
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    x[m] = delta[m] * sc.inv_k2;
+    p[m] = fv_panel(x[m]);
+    near &= (unsigned)p[m] < (unsigned)kFvPanels;
+  }
+  FvOut o;
+  o.bad = false;
+  if (near) {
+    fv_poly<M, LAM>(poly, x, p, s1, s2);
+  } else {
+#pragma unroll 1
+    for (int m = 0; m < M; ++m) {
+      const bool bad = !((m == 0 ? delta[0] : (m == 1 ? delta[M / 2] : delta[M - 1])) > 0.0);
+      const double xm = bad ? 1.0 : (m == 0 ? x[0] : (m == 1 ? x[M / 2] : x[M - 1]));
+      const int pm = fv_panel(xm);
+      o.bad |= bad;
+      FvSums s;
+      if ((unsigned)pm < (unsigned)kFvPanels)
+        fv_poly<1, true>(poly, &xm, &pm, &s.s1, &s.s2);
+      else
+        s = fv_radial_far(a.tab, a.n_r, xm);
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        s1[i] = i == m ? s.s1 : s1[i];
+        s2[i] = i == m ? s.s2 : s2[i];
+      }
+    }
+  }
+  const double q0 = (zero ? sc.n1 : sc.c1) * s1[0];
+  o.Q = q0;
+  o.lam = LAM ? 2.0 * ((zero ? sc.n2 : sc.c2) * s2[0]) * (ids * ids) : 0.0;
+  if constexpr (GOLD) {
+    const double ah = sc.g2 * fmax(s2[1], s2[2]) * isj;  // half the larger |f'|; 0 at j = 0
+    const double Q = __builtin_fma(-ah, jump, __builtin_fma(sc.g1, s1[1] + s1[2], q0));
+    o.Q = zero ? q0 : Q;
+    if (LAM) o.lam += 2.0 * ah * ids;
+  }
+  return o;
 }
 
-// Grid (blocks of 4 kFvPerWave interfaces, flows) at the stage time a.t:
-// lane 3 i + m of a wave computes mass m of the wave's interface i
-// (fv_mass), lane 3 i gathers the three and stores Q, lam (lane 63 idles).
-constexpr int kFvPerWave = kWave / 3;
-__global__ __launch_bounds__(256) void fv_flux_kernel(FvArgs a, const double *__restrict__ cf) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
+// 1/sigma_j; 0 for j = 0.
+__device__ __forceinline__ double fv_isj(const FvArgs &a, int j) {
+  return j > 0 ? a.inv_ds / (double)j : 0.0;
+}
+
+// SSP-RK3 stage s (0..2) of one cell: y0 at the start of the step, y the state
+// this stage starts from (y0 itself in stage 0), e = y + h L with dq = L ds and
+// hids = h/ds; y0 + w (e - y0), w = 1, 1/4, 2/3.  In this form a rounded weight
+// scales a small change only: y0/3 + (2/3) e multiplies the state by 1 - 3.7e-17 in
+// every step, which over 2000 steps of a flow of 256 cells made 7.1e-14 of the
+// solution (2.7e-15 in this form, both against 80-bit arithmetic).
+__device__ __forceinline__ double fv_update(int s, double dq, double hids, double y0, double y) {
+  const double e = __builtin_fma(hids, dq, y);
+  return s == 0 ? e : __builtin_fma(s == 1 ? 0.25 : 2.0 / 3.0, e - y0, y0);
+}
+
+// Grid (interface blocks, flows) at the stage time a.t.
+__global__ __launch_bounds__(256) void fv_flux_kernel(FvArgs a) {
   const int64_t r = blockIdx.y;
-  const int64_t n = a.n, nq = n + 1;
-  const int il = lane / 3, m = lane - 3 * il;
-  const int64_t j = ((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) * kFvPerWave + il;
-  const bool live = il < kFvPerWave && j < nq;
-  const int64_t o = r * nq + j;
+  const int64_t nq = a.n + 1;
+  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= nq) return;
+  double *Q = a.Q + r * nq, *lam = a.lam + r * nq;
   if (!a.alive[r]) {  // workgroup-uniform
-    if (live && m == 0) {
-      a.Q[o] = 0.0;
-      a.lam[o] = 0.0;
-    }
+    Q[j] = lam[j] = 0.0;
     return;
   }
-  const double *u = (a.first ? a.y0 : a.ys) + r * n;
+  const double *u = (a.first ? a.y0 : a.ys) + r * a.n;
   const FvScale sc = fv_scale(a, a.t);
-  const FvIface f = fv_prep(a, sc, u, (int)(live ? j : n));
-  double F1 = 0.0, F2 = 0.0;
-  const double x = m == 0 ? f.dh[0] : (m == 1 ? f.dh[1] : f.dh[2]);
-  if (live && m < f.nm) fv_mass(a, sc, a.tab, cf, x, F1, F2);
-  double G1[3], G2[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {  // every lane takes part
-    G1[k] = __shfl(F1, lane - m + k, kWave);
-    G2[k] = __shfl(F2, lane - m + k, kWave);
-  }
-  if (!live || m != 0) return;
-  if (f.bad) {
+  const FvCells c = fv_cells(u, (int)a.n, (int)j);
+  const double isj = fv_isj(a, (int)j);
+  const FvOut o = a.N > 1 ? fv_iface<true, true>(a, sc, a.poly, c, isj, j == 0)
+                          : fv_iface<false, true>(a, sc, a.poly, c, isj, j == 0);
+  if (o.bad) {
     // the flow ends at the start of this step with its state kept
     a.alive[r] = 0;
     a.t_reached[r] = a.t_n;
     *a.flag = 1;
-    a.Q[o] = 0.0;
-    a.lam[o] = 0.0;
-    return;
   }
-  double Q, lam;
-  fv_flux(a, f, (int)j, G1, G2, Q, lam);
-  a.Q[o] = Q;
-  a.lam[o] = lam;
+  Q[j] = o.bad ? 0.0 : o.Q;
+  lam[j] = o.bad ? 0.0 : o.lam;
 }
 
 // Grid (cell blocks, flows): d_t u_i = (Q_{i+1} - Q_i)/ds and the stage.
@@ -298,143 +332,123 @@ __global__ __launch_bounds__(256) void fv_stage_kernel(FvArgs a) {
     return;
   }
   const double *Q = a.Q + r * (a.n + 1);
-  const double L = (Q[i + 1] - Q[i]) * a.inv_ds;
+  const double dq = Q[i + 1] - Q[i];
   if (a.stage == 3) {
-    a.dudt[e] = L;
+    a.dudt[e] = dq * a.inv_ds;
   } else {
-    double y0 = a.y0[e], ys = a.stage == 0 ? 0.0 : a.ys[e];
-    fv_update(a.stage, L, a.h, y0, ys);
-    if (a.stage == 2)
-      a.y0[e] = y0;
-    else
-      a.ys[e] = ys;
+    const double y0 = a.y0[e], y = a.stage == 0 ? y0 : a.ys[e];
+    (a.stage == 2 ? a.y0 : a.ys)[e] = fv_update(a.stage, dq, a.h * a.inv_ds, y0, y);
   }
 }
 
-// Steps [s0, s0 + n_st) of one flow per workgroup: state, stage state,
-// fluxes, the radial table and per interface its masses, F_1 and F_2 in LDS
-// (the coefficient groups, the same for every lane, through the scalar
-// cache).  Per stage: one thread per interface forms its masses (fv_prep), a
-// barrier; thread t takes mass t % 3 of interface t / 3 (fv_mass), a barrier;
-// one thread per interface forms the flux (fv_flux), a barrier; the cell
-// updates, a barrier.  The per-mass, per-interface and per-cell arithmetic is
-// that of the flux and stage kernels (same bits); no launch per stage.  A
-// flow whose masses leave the domain in a stage ends with the state of the
-// start of that step.
-__global__ __launch_bounds__(1024) void fv_solve_kernel(FvArgs a, const double *__restrict__ cf,
-                                                       int64_t s0, int64_t n_st) {
+// Steps [s0, s0 + n_st) of one flow per workgroup, everything in LDS: three
+// state buffers with their ghost cells, 1/sigma_j, the polynomial panels and the
+// scales of the next kFvScaleSteps steps (formed by all threads at once).  A
+// wave takes 64 consecutive interfaces and with them the 63 cells between: each
+// lane forms its interface's flux (fv_iface), takes its left neighbour's by a
+// lane permutation and updates the cell between the two; the next wave starts
+// at this one's last interface, and the last wave ends with interface n, so that
+// one wave holds the cells of the ghosts.  One barrier per stage.  The
+// per-interface and per-cell arithmetic is that of the flux and stage kernels
+// (same bits); no launch per stage.  A step goes from buffer Y over A and B to A,
+// so a flow whose masses leave the domain in it ends with Y, the state of its
+// start.
+//
+// Bound by the latency of this chain (cells, states, panels, Horner, flux) on
+// the one CU of a flow, one wave on most SIMDs: 0.60 us per stage for one wave
+// (63 cells), 0.76 for four and 0.92 for the five of 256 cells, whose panel
+// coefficients (84 KB per stage) also share the CU's LDS port.  128 flows of 256
+// cells, 64 nodes, N = 4, 2000 steps: 5.5 ms.  With the radial sums as rational
+// groups, one lane per mass, four barriers per stage and the scales formed by
+// every thread it took 25.9 ms; this kernel's sums with a quad of lanes per
+// interface (each lane one mass, two barriers) 8.6 ms, bound by instruction
+// issue.  At most 128 VGPRs, so that two workgroups of five waves fit a CU
+// (512 flows: 1.31 us per stage, 1.83 at 151 VGPRs).
+constexpr int kFvScaleSteps = 32;
+constexpr int kFvWaveCells = kWave - 1;
+constexpr int kFvMaxWaves = 8;
+
+template <bool GOLD>
+__global__ __launch_bounds__(kFvMaxWaves * kWave, 4) void fv_solve_kernel(FvArgs a, int64_t s0,
+                                                                         int64_t n_st) {
   extern __shared__ double lds[];
   const int64_t r = blockIdx.x;
   if (!a.alive[r]) return;  // workgroup-uniform
-  const int n = (int)a.n, nq = n + 1;
+  const int n = (int)a.n;
   const int tid = threadIdx.x, bs = blockDim.x;
-  double *y0 = lds;
-  double *ys = y0 + n;
-  double *Q = ys + n;
-  double *tab = Q + nq;            // chat | hhat
-  double *lP = tab + 2 * a.n_r;    // [n + 1][6]: dh (then F_1) of the masses, um, up, 1/sigma_j
-  double *lF2 = lP + 6 * nq;       // [n + 1][3]: F_2 of the masses
-  int *lN = reinterpret_cast<int *>(lF2 + 3 * nq);  // [n + 1]: number of masses
-  int *bad_flag = lN + nq;
-  for (int i = tid; i < n; i += bs) y0[i] = a.y0[r * n + i];
-  for (int i = tid; i < 2 * a.n_r; i += bs) tab[i] = a.tab[i];
-  if (tid == 0) *bad_flag = 0;
-  __syncthreads();
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  double *poly = lds;
+  double *Y = poly + kFvPanels * kFvPoly + 2;  // cells -2 .. n + 1 each
+  double *A = Y + n + 4;
+  double *B = A + n + 4;
+  double *isj = B + n + 2;  // [n + 1]
+  FvScale *scales = reinterpret_cast<FvScale *>(isj + n + 1);  // [kFvScaleSteps][3]
+  int *bad_flag = reinterpret_cast<int *>(scales + 3 * kFvScaleSteps);
+  const double *y = a.y0 + r * n;
+  for (int i = tid; i < kFvPanels * kFvPoly; i += bs) poly[i] = a.poly[i];
+  for (int i = tid; i < n; i += bs) Y[i] = y[i];
+  for (int j = tid; j <= n; j += bs) isj[j] = fv_isj(a, j);
+  if (tid == 0) {
+    *bad_flag = 0;
+    Y[-2] = A[-2] = B[-2] = 0.0;  // read by interface 0, in which it does not enter
+    Y[-1] = -y[0];
+    Y[n] = fv_ghost(y[n - 2], y[n - 1]);
+    Y[n + 1] = fv_ghost(y[n - 1], Y[n]);
+  }
   const double cs[3] = {0.0, 1.0, 0.5};
-  const int ng = (a.n_r + kFvGroup - 1) / kFvGroup;  // coefficient groups
+  const double hids = a.h * a.inv_ds;
   for (int64_t st = 0; st < n_st; ++st) {
-    const double tn = (double)(s0 + st) * a.h;
-    for (int s = 0; s < 3; ++s) {
-      const FvScale sc = fv_scale(a, tn + cs[s] * a.h);
-      const double *u = s == 0 ? y0 : ys;
-      bool bad = false;
-      for (int j = tid; j < nq; j += bs) {
-        const FvIface f = fv_prep(a, sc, u, j);
-        double *P = lP + 6 * j;
-        P[0] = f.dh[0];
-        P[1] = f.dh[1];
-        P[2] = f.dh[2];
-        P[3] = f.um;
-        P[4] = f.up;
-        P[5] = f.isj;
-        lN[j] = f.nm;
-        bad |= f.bad;
-      }
-      if (bad) *bad_flag = 1;
-      __syncthreads();
-      if (*bad_flag) {  // workgroup-uniform
-        if (tid == 0) {
-          a.alive[r] = 0;
-          a.t_reached[r] = tn;
-          *a.flag = 1;
-        }
-        for (int i = tid; i < n; i += bs) a.y0[r * n + i] = y0[i];
-        return;
-      }
-      // radial sums, one lane per (interface, mass) task.  When the tasks
-      // leave a few in a last wave (3 (n + 1) = 64 w + tail), that wave
-      // splits each of its tail tasks over the coefficient groups, one lane
-      // per group, and the task's first lane folds the groups' terms in
-      // order: the operations of one lane alone (the same bits), in the time
-      // of one group instead of all of them, so the SIMD that holds that wave
-      // is not left with one more whole radial sum than the others.
-      const int T = 3 * nq, tail = T % kWave, t_full = T - tail;
-      const bool split = tail > 0 && T <= bs && tail * ng <= kWave;  // workgroup-uniform
-      for (int t = tid; t < (split ? t_full : T); t += bs) {
-        const int j = t / 3, m = t - 3 * j;
-        if (m < lN[j]) {
-          double F1, F2;
-          fv_mass(a, sc, tab, cf, lP[6 * j + m], F1, F2);
-          lP[6 * j + m] = F1;
-          lF2[3 * j + m] = F2;
-        }
-      }
-      if (split && tid >= t_full && tid < t_full + kWave) {  // wave-uniform: the last wave
-        const int l = tid - t_full;
-        const int k = l / ng, g = l - k * ng;  // tail task k, group g
-        const int tk = t_full + (k < tail ? k : 0);
-        const int j = tk / 3, m = tk - 3 * j;
-        const bool real = k < tail && m < lN[j];
-        const double x = real ? lP[6 * j + m] : 1.0;
-        double Nv = 0.0, rv = 0.0, Mr = 0.0;
-        if (real && fv_coef_range(x)) fv_group<false>(x, cf + kFvCoef * g, Nv, rv, Mr);
-        double s1 = 0.0, s2 = 0.0;
-        for (int gg = 0; gg < ng; ++gg) {  // every lane of the wave takes part
-          const int src = min(k * ng + gg, kWave - 1);
-          const double n_ = __shfl(Nv, src, kWave), r_ = __shfl(rv, src, kWave);
-          const double m_ = __shfl(Mr, src, kWave);
-          s1 = __builtin_fma(n_, r_, s1);
-          s2 = __builtin_fma(m_, r_, s2);
-        }
-        if (real && g == 0) {
-          if (!fv_coef_range(x)) fv_radial(a, tab, cf, x, s1, s2);  // term by term
-          double F1, F2;
-          fv_scale_sums(a, sc, s1, s2, F1, F2);
-          lP[6 * j + m] = F1;
-          lF2[3 * j + m] = F2;
-        }
-      }
-      __syncthreads();
-      for (int j = tid; j < nq; j += bs) {
-        const double *P = lP + 6 * j;
-        FvIface f;
-        f.nm = lN[j];
-        f.um = P[3];
-        f.up = P[4];
-        f.isj = P[5];
-        double q, lam;
-        fv_flux(a, f, j, P, lF2 + 3 * j, q, lam);
-        Q[j] = q;
-      }
-      __syncthreads();
-      for (int i = tid; i < n; i += bs) {
-        const double L = (Q[i + 1] - Q[i]) * a.inv_ds;
-        fv_update(s, L, a.h, y0[i], ys[i]);
+    const int sl = (int)(st % kFvScaleSteps);
+    if (sl == 0) {
+      for (int k = tid; k < 3 * kFvScaleSteps; k += bs) {
+        const double t = (double)(s0 + st + k / 3) * a.h;
+        scales[k] = fv_scale(a, t + cs[k % 3] * a.h);
       }
       __syncthreads();
     }
+    bool bad = false;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const FvScale sc = scales[3 * sl + s];
+      const double *u = s == 0 ? Y : (s == 1 ? A : B);
+      double *dst = s == 1 ? B : A;
+      for (int je = n - wave * kFvWaveCells; je > 0; je -= bs / kWave * kFvWaveCells) {
+        const int jl = je - kFvWaveCells + lane;  // je is the wave's last interface
+        const int j = max(jl, 0);
+        const FvCells c{u[j - 2], u[j - 1], u[j], u[j + 1]};
+        const double y0 = s == 0 ? c.L : Y[j - 1];
+        const FvOut o = fv_iface<GOLD, false>(a, sc, poly, c, isj[j], j == 0);
+        bad |= o.bad;
+        const double left = dpp_f64<0x138>(o.Q);  // wave_shr 1: the flux of interface j - 1
+        const double v = fv_update(s, o.Q - left, hids, y0, c.L);
+        const double vl = dpp_f64<0x138>(v);
+        if (lane > 0 && jl > 0) {
+          dst[j - 1] = v;
+          if (j == 1) dst[-1] = -v;
+          if (j == n) {
+            const double gn = fv_ghost(vl, v);
+            dst[n] = gn;
+            dst[n + 1] = fv_ghost(v, gn);
+          }
+        }
+      }
+      if (s == 2 && bad) *bad_flag = 1;
+      __syncthreads();
+    }
+    if (*bad_flag) {  // workgroup-uniform
+      if (tid == 0) {
+        a.alive[r] = 0;
+        a.t_reached[r] = (double)(s0 + st) * a.h;
+        *a.flag = 1;
+      }
+      break;
+    }
+    double *t = Y;
+    Y = A;
+    A = t;
   }
-  for (int i = tid; i < n; i += bs) a.y0[r * n + i] = y0[i];
+  for (int i = tid; i < n; i += bs) a.y0[r * n + i] = Y[i];
 }
 
 // One workgroup per flow: step estimate 1 / max_j lam_j.
@@ -463,10 +477,8 @@ int launch_fv_init(const FvArgs &a, double t_end, void *stream) {
 
 int launch_fv_flux(const FvArgs &a, void *stream) {
   if (a.n_rows <= 0) return 0;
-  const int64_t per_block = 4 * kFvPerWave;
-  hipLaunchKernelGGL(fv_flux_kernel,
-                     dim3((unsigned)((a.n + 1 + per_block - 1) / per_block), (unsigned)a.n_rows),
-                     dim3(256), 0, (hipStream_t)stream, a, a.tab + 2 * a.n_r);
+  hipLaunchKernelGGL(fv_flux_kernel, dim3((unsigned)(a.n / 256 + 1), (unsigned)a.n_rows),
+                     dim3(256), 0, (hipStream_t)stream, a);
   return (int)hipGetLastError();
 }
 
@@ -478,22 +490,24 @@ int launch_fv_stage(const FvArgs &a, void *stream) {
 }
 
 int64_t fv_solve_lds_bytes(const FvArgs &a) {
-  return (int64_t)sizeof(double) * (3 * a.n + 1 + 2 * (int64_t)a.n_r + 9 * (a.n + 1)) +
-         (int64_t)sizeof(int) * (a.n + 1) + 16;
+  return (int64_t)sizeof(double) * (kFvPanels * kFvPoly + 3 * (a.n + 4) + a.n + 1) +
+         (int64_t)sizeof(FvScale) * 3 * kFvScaleSteps + 16;
 }
 
-int launch_fv_solve(const FvArgs &a, int64_t s0, int64_t n_st, int threads, void *stream) {
+int launch_fv_solve(const FvArgs &a, int64_t s0, int64_t n_st, void *stream) {
   if (a.n_rows <= 0 || n_st <= 0) return 0;
-  if (threads < 64 || threads > 1024 || threads % 64) return (int)hipErrorInvalidValue;
   if (fv_solve_lds_bytes(a) > kFvSolveLdsMax) return (int)hipErrorInvalidValue;
   static const bool once =
-      ((void)hipFuncSetAttribute((const void *)&fv_solve_kernel,
+      ((void)hipFuncSetAttribute((const void *)&fv_solve_kernel<true>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, kFvSolveLdsMax),
+       (void)hipFuncSetAttribute((const void *)&fv_solve_kernel<false>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, kFvSolveLdsMax),
        (void)hipGetLastError(), true);
   (void)once;
-  hipLaunchKernelGGL(fv_solve_kernel, dim3((unsigned)a.n_rows), dim3(threads),
-                     (size_t)fv_solve_lds_bytes(a), (hipStream_t)stream, a, a.tab + 2 * a.n_r,
-                     s0, n_st);
+  const int waves = (int)((a.n + kFvWaveCells - 1) / kFvWaveCells);
+  hipLaunchKernelGGL(a.N > 1 ? fv_solve_kernel<true> : fv_solve_kernel<false>,
+                     dim3((unsigned)a.n_rows), dim3(kWave * (waves < kFvMaxWaves ? waves : kFvMaxWaves)),
+                     (size_t)fv_solve_lds_bytes(a), (hipStream_t)stream, a, s0, n_st);
   return (int)hipGetLastError();
 }
 

@@ -36,6 +36,9 @@ int Ctx::fvlpa_device(const frg_fvlpa &f, int64_t n, double t_end, int64_t n_ste
   double Cd;
   int rc = lpa_table(f.d, f.reg, f.n_radial, f.q_max_over_k, &tab, &Cd);
   if (rc) return rc;
+  const double *poly;
+  rc = fv_panels(f.d, f.reg, f.n_radial, f.q_max_over_k, &poly);
+  if (rc) return rc;
   const bool solve = dudt == nullptr;
   const int64_t m = n * f.n_cells, nq = n * (f.n_cells + 1);
   // scratch: Q | lam | [ys] | [t_reached] | alive
@@ -46,6 +49,7 @@ int Ctx::fvlpa_device(const frg_fvlpa &f, int64_t n, double t_end, int64_t n_ste
   double *d = (double *)buf;
   FvArgs a{};
   a.tab = tab;
+  a.poly = poly;
   a.Q = d;
   d += nq;
   a.lam = d;
@@ -99,11 +103,9 @@ int Ctx::fvlpa_device(const frg_fvlpa &f, int64_t n, double t_end, int64_t n_ste
     a.h = hh;
     if (tune.fv_persistent && fv_solve_lds_bytes(a) <= kFvSolveLdsMax) {
       // one workgroup per flow runs the steps with its state in LDS, in
-      // launches of at most kFvStepsPerLaunch steps; the whole chip's
-      // threads per flow while there are at most as many flows as CUs
-      const int threads = n <= n_cu ? 1024 : n <= 2 * n_cu ? 512 : 256;
+      // launches of at most kFvStepsPerLaunch steps
       for (int64_t s0 = 0; s0 < n_steps && !rc; s0 += kFvStepsPerLaunch) {
-        const int r = launch_fv_solve(a, s0, std::min(kFvStepsPerLaunch, n_steps - s0), threads, st);
+        const int r = launch_fv_solve(a, s0, std::min(kFvStepsPerLaunch, n_steps - s0), st);
         if (r) rc = hip_fail((hipError_t)r, "fv_solve_kernel launch");
       }
     } else {

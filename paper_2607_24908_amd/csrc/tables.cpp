@@ -204,6 +204,53 @@ LpaTable build_lpa_table(int d, int reg, int n_r, double q_max_over_k) {
   return t;
 }
 
+// Per panel the Taylor series of s1 about the middle c, terms t_k = (-1)^k sum_i
+// c_i w^k/(h_i + c)^(k+1) (w the half-width; w/c = 1/33 at most, so t_k/t_0 <=
+// 33^-k), economised: the Chebyshev terms above degree kFvPoly - 1 = 10 are
+// dropped (below 66^-11 = 1e-20 of s1; their derivative below 1e-16 of s2 / 2).
+std::vector<double> build_fv_panels(const LpaTable &t) {
+  constexpr int K = 16, n = kFvPoly;  // Taylor terms, coefficients kept
+  // z^k = sum_j b[k][j] T_j(z); T_j = sum_i a[j][i] z^i
+  static const auto econ = [] {
+    std::vector<std::vector<long double>> a(K, std::vector<long double>(K, 0.0L)), b = a;
+    a[0][0] = 1.0L;
+    a[1][1] = 1.0L;
+    for (int j = 2; j < K; ++j)
+      for (int i = 0; i < K; ++i) a[j][i] = (i ? 2.0L * a[j - 1][i - 1] : 0.0L) - a[j - 2][i];
+    b[0][0] = 1.0L;
+    for (int k = 1; k < K; ++k)  // z T_j = (T_{j+1} + T_{|j-1|})/2
+      for (int j = 0; j < k; ++j) {
+        b[k][j + 1] += (j ? 0.5L : 1.0L) * b[k - 1][j];
+        if (j) b[k][j - 1] += 0.5L * b[k - 1][j];
+      }
+    std::vector<long double> m(n * K, 0.0L);  // kept coefficient i of z^k
+    for (int k = 0; k < K; ++k)
+      for (int j = 0; j < n; ++j)
+        for (int i = 0; i <= j; ++i) m[i * K + k] += b[k][j] * a[j][i];
+    return m;
+  }();
+  const int n_r = t.n_r;
+  std::vector<double> out((size_t)kFvPanels * n);
+  for (int p = 0; p < kFvPanels; ++p) {
+    const int e = kFvLo + p / kFvPerOctave, s = p % kFvPerOctave;
+    const long double lo = ldexpl((long double)(kFvPerOctave + s) / kFvPerOctave, e);
+    const long double w = ldexpl(0.5L / kFvPerOctave, e), c = lo + w;
+    long double tk[K] = {};
+    for (int i = 0; i < n_r; ++i) {
+      const long double g = 1.0L / ((long double)t.data[n_r + i] + c), f = -w * g;
+      long double v = (long double)t.data[i] * g;
+      for (int k = 0; k < K; ++k, v *= f) tk[k] += v;
+    }
+    long double wi = 1.0L;
+    for (int i = 0; i < n; ++i, wi /= w) {
+      long double v = 0.0L;
+      for (int k = 0; k < K; ++k) v += econ[i * K + k] * tk[k];
+      out[(size_t)p * n + i] = (double)(v * wi);
+    }
+  }
+  return out;
+}
+
 // Angular data of the vertex diagram: [x_j | sqrt(1 - x_j^2) | cos phi_l |
 // nu_l], x_j the polar Gauss-Legendre nodes (as in build_quad_table),
 // phi_l the Gauss-Legendre nodes on [0, pi] and nu_l = (pi/2) w_l sin^{d-3}(phi_l).
