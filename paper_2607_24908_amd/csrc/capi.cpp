@@ -197,12 +197,15 @@ int Ctx::lpa_table(int d, int reg, int n_r, double qmk, const double **dev, doub
 int Ctx::fv_panels(int d, int reg, int n_r, double qmk, const double **dev) {
   LEntry &ent = ltabs.at(std::make_tuple(d, reg, n_r, dbits(qmk)));
   if (!ent.panels) {
-    const std::vector<double> t = build_fv_panels(ent.host);
     auto buf = std::make_unique<DevBuf>(&hbm);
-    int rc = buf->reserve(t.size() * sizeof(double));
-    if (rc) return rc;
+    if (buf->reserve(sizeof(double) * kFvPanels * kFvPoly) != FRG_OK) {  // no room in the budget
+      clear_error();
+      *dev = nullptr;
+      return FRG_OK;
+    }
+    const std::vector<double> t = build_fv_panels(ent.host);
     hipError_t e = hipMemcpy(buf->ptr, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "upload finite-volume panels");
+    if (e != hipSuccess) return hip_fail(e, "upload radial-sum panels");
     ent.panels = std::move(buf);
   }
   *dev = (const double *)ent.panels->ptr;
@@ -855,20 +858,19 @@ int Ctx::tab_launch(TabArgs a, int reg, hipStream_t st) {
 // ----------------------------------------------------------------- LPA --
 int Ctx::lpa_job_table(int n, const frg_lpa *lpa, const double *t, const double *const *U,
                        double *const *dUdt, double *const *jac, int *flags_dev, LpaJob *jobs,
-                       int64_t *start) {
-  int64_t total = 0;
+                       int64_t *blocks) {
+  *blocks = 0;
   for (int f = 0; f < n; ++f) {
     const frg_lpa &l = lpa[f];
-    const double *tab;
+    LpaJob &j = jobs[f];
     double Cd;
-    int rc = lpa_table(l.d, l.reg, l.n_radial, l.q_max_over_k, &tab, &Cd);
+    int rc = lpa_table(l.d, l.reg, l.n_radial, l.q_max_over_k, &j.tab, &Cd);
+    if (!rc) rc = fv_panels(l.d, l.reg, l.n_radial, l.q_max_over_k, &j.poly);
     if (rc) return rc;
     const double k = l.Lambda * std::exp(t[f]);
-    LpaJob &j = jobs[f];
     j.U = U[f];
     j.dUdt = dUdt[f];
     j.jac = jac ? jac[f] : nullptr;
-    j.tab = tab;
     j.flag = flags_dev ? flags_dev + f : d_flag;
     j.k2 = k * k;
     j.inv_k2 = 1.0 / j.k2;
@@ -876,34 +878,35 @@ int Ctx::lpa_job_table(int n, const frg_lpa *lpa, const double *t, const double 
     j.pre2 = Cd * std::pow(k, l.d - 2);
     j.dr = l.rho_max / (double)(l.n_grid - 1);
     j.Nm1 = (double)(l.N - 1);
-    j.n = l.n_grid;
+    j.i2 = 1.0 / (2.0 * j.dr);
+    j.i1 = 1.0 / (j.dr * j.dr);
+    j.n = (int32_t)l.n_grid;
     j.n_r = l.n_radial;
     j.N = l.N;
-    start[f] = total;
-    total += l.n_grid;
+    j.block = (int32_t)*blocks;
+    *blocks += (l.n_grid + kLpaBlock - 1) / kLpaBlock;
   }
-  start[n] = total;
   return FRG_OK;
 }
 
 int Ctx::lpa_jobs(int n, const frg_lpa *lpa, const double *t, const double *const *U,
                   double *const *dUdt, double *const *jac, int *flags_dev, hipStream_t st) {
   std::vector<LpaJob> jobs(n);
-  std::vector<int64_t> start(n + 1);
-  int rc = lpa_job_table(n, lpa, t, U, dUdt, jac, flags_dev, jobs.data(), start.data());
+  int64_t blocks;
+  int rc = lpa_job_table(n, lpa, t, U, dUdt, jac, flags_dev, jobs.data(), &blocks);
   if (rc) return rc;
-  const int64_t total = start[n];
-  const size_t jb = n * sizeof(LpaJob);
-  std::vector<char> blob(jb + (n + 1) * sizeof(int64_t));
-  std::memcpy(blob.data(), jobs.data(), jb);
-  std::memcpy(blob.data() + jb, start.data(), (n + 1) * sizeof(int64_t));
-  void *dev;
-  int slot;
-  rc = ring.upload(blob.data(), blob.size(), st, &dev, &slot);
-  if (rc) return rc;
-  int e = launch_lpa((const LpaJob *)dev, (const int64_t *)((char *)dev + jb), n, total, st);
-  rc = ring.release(slot, st);
-  if (e) return hip_fail((hipError_t)e, "lpa_kernel launch");
+  int e;
+  if (n <= kLpaArgs) {
+    e = launch_lpa_args(jobs.data(), n, blocks, st);
+  } else {
+    void *dev;
+    int slot;
+    rc = ring.upload(jobs.data(), n * sizeof(LpaJob), st, &dev, &slot);
+    if (rc) return rc;
+    e = launch_lpa_table((const LpaJob *)dev, n, blocks, st);
+    rc = ring.release(slot, st);
+  }
+  if (e) return hip_fail((hipError_t)e, "lpa kernel launch");
   return rc;
 }
 

@@ -188,7 +188,7 @@ struct Context {
     std::unique_ptr<frg::DevBuf> buf;
     double Cd = 0.0;
     frg::LpaTable host;
-    std::unique_ptr<frg::DevBuf> panels;  // build_fv_panels, when a finite-volume call asked
+    std::unique_ptr<frg::DevBuf> panels;  // build_fv_panels, from the first call that asks
   };
   std::map<std::tuple<int, int, uint64_t, uint64_t, int, int>, QEntry> qtabs;
   std::map<std::tuple<int, int, int, uint64_t>, LEntry> ltabs;
@@ -201,7 +201,8 @@ struct Context {
   int quad_table(const frg_quad &q, const double **dev, frg::QuadTable *host_copy,
                  frg::QuadTable **host_ref = nullptr);
   int lpa_table(int d, int reg, int n_r, double qmk, const double **dev, double *Cd);
-  // polynomial panels of the finite-volume flux for a table lpa_table has made
+  // polynomial panels of the radial sums for a table lpa_table has made; null where
+  // the memory budget has no room for them
   int fv_panels(int d, int reg, int n_r, double qmk, const double **dev);
   int make_setdev(const frg_set &s, frg::SetDev *out);
   void fill_setdev(const frg_set &s, const frg::QuadTable &h, const double *tab, frg::SetDev *out);
@@ -237,11 +238,11 @@ struct Context {
                   double *out, double *err, uint8_t *used, hipStream_t st);
   int lpa_jobs(int n, const frg_lpa *lpa, const double *t, const double *const *U,
                double *const *dUdt, double *const *jac, int *flags_dev, hipStream_t st);
-  // Descriptors of n LPA jobs (device pointers given) and their grid offsets
-  // start[0..n]; no GPU work except building missing LPA tables.
+  // Descriptors of n LPA jobs (device pointers given) and the workgroups they
+  // take; no GPU work except building missing LPA tables.
   int lpa_job_table(int n, const frg_lpa *lpa, const double *t, const double *const *U,
                     double *const *dUdt, double *const *jac, int *flags_dev, LpaJob *jobs,
-                    int64_t *start);
+                    int64_t *blocks);
   void stop_server();
   // fvlpa_api.cpp: finite-volume LPA; dudt != nullptr: one right-hand side
   // at t_rhs (and dt_est if not null), else SSP-RK3 from 0 to t_end

@@ -131,13 +131,18 @@ struct LpaJob {
   double *dUdt;
   double *jac;      // may be null
   const double *tab;  // LpaTable::data on the device
+  const double *poly; // build_fv_panels on the device, null: none
   int *flag;        // set to 1 on a domain violation (may be null)
   double k2, inv_k2;
   double pre1, pre2;  // C_d k^d, C_d k^{d-2}
   double dr, Nm1;
-  int64_t n;
-  int32_t n_r, N;
+  double i2, i1;      // 1/(2 dr), 1/dr^2
+  int32_t n, n_r, N;
+  int32_t block;      // first workgroup of the flow in its launch
 };
+// Workgroups of kLpaBlock grid points; jobs a launch carries in its arguments.
+constexpr int kLpaBlock = 64;
+constexpr int kLpaArgs = 24;
 
 void lane_split(int n_r, int n_a, int *R, int *J, int *T, int *U);
 
@@ -210,6 +215,7 @@ struct FvArgs {
   double ds, inv_ds, h, t_n;
   int64_t n_rows, n;
   int32_t n_r, N, d;
+  int32_t n_panels;    // kFvPanels; 0: no panels, every sum takes the other branch
   int32_t stage;       // 0..2 SSP-RK3 stages, 3: right-hand side only
   int32_t first;       // flux kernel: read y0 (first stage / rhs) instead of ys
 };
@@ -357,7 +363,9 @@ bool grid_resident(const GridArgs &g);
 int launch_tab(const TabArgs &t, int reg, int W, bool lds_rows, int64_t stream_blocks,
                void *stream);
 int tab_lds_bytes(const TabArgs &t, bool lds_rows);
-int launch_lpa(const LpaJob *d_jobs, const int64_t *d_start, int n_jobs, int64_t total_points,
-               void *stream);
+// jobs on the host, at most kLpaArgs, passed as kernel arguments; or any number
+// in memory the kernel can read.
+int launch_lpa_args(const LpaJob *jobs, int n_jobs, int64_t blocks, void *stream);
+int launch_lpa_table(const LpaJob *d_jobs, int n_jobs, int64_t blocks, void *stream);
 
 }  // namespace frg

@@ -24,6 +24,7 @@
 #pragma clang fp contract(off)
 
 #include "device_fp64.h"
+#include "device_panels.h"
 
 namespace frg {
 
@@ -98,83 +99,12 @@ __device__ __forceinline__ FvCells fv_cells(const double *u, int n, int j) {
   return c;
 }
 
-// The radial sums s1 = sum_i chat_i/(hhat_i + x) and s2 = sum_i chat_i/(hhat_i +
-// x)^2.  For 2^kFvLo <= x < 2^kFvHi from the table's polynomial panels
-// (build_fv_panels; poly in LDS or global memory): s1 and its derivative by one
-// Horner pass over 11 coefficients, within 2.2e-16 and 3.3e-16 (20 FMAs; the 64
-// nodes of the usual table took 232 FMAs and 8 reciprocals as rational groups).
-// Outside the panels the coefficient groups (x in [kFvXMin, kFvXMax]): N/P and
-// M/P^2 by Horner with one reciprocal per group of eight nodes (the powers of x
-// and the products stay inside the FP64 range there); beyond those term by
-// term.  Every term and coefficient of these two is positive and x > 0, so
-// neither form cancels.
+// s1 and s2 outside the panels (device_panels.h): for x in [kFvXMin, kFvXMax] the
+// coefficient groups, N/P and M/P^2 by Horner with one reciprocal per group of
+// eight nodes (the powers of x and the products stay inside the FP64 range
+// there); beyond those term by term.  Every term and coefficient is positive
+// and x > 0, so neither form cancels.
 constexpr double kFvXMin = 1e-20, kFvXMax = 1e20;
-
-// Panel of x; as an unsigned number below kFvPanels exactly for x in their range
-// (not for x <= 0, infinities and NaN).
-__device__ __forceinline__ int fv_panel(double x) {
-  static_assert(kFvPerOctave == 16, "four mantissa bits select the panel");
-  const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32);
-  int p = (int)(hi >> 16) - ((1023 + kFvLo) << 4);
-  asm("" : "+v"(p));  // the address is p times the panel's size, not a folded base below zero
-  return p;
-}
-// s1[m], s2[m] at x[m] in panel p[m]; s2[0] only for FIRST.  The loads of all
-// masses first (those of the last kFvLate coefficients after the first steps, in
-// the registers these free), then their Horner chains in step (the compiler's own
-// order runs the masses one after the other, each waiting for its loads and for
-// itself).
-constexpr int kFvLate = 3;
-template <int M, bool FIRST>
-__device__ __forceinline__ void fv_poly(const double *poly, const double *x, const int *p,
-                                        double *s1, double *s2) {
-  double q[M][kFvPoly], z[M], P[M], D[M];
-  const double *qp[M];
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, x[m]) >> 32);
-    const double c = __builtin_bit_cast(
-        double, (unsigned long long)((hi & 0xffff0000u) | 0x8000u) << 32);  // its middle
-    z[m] = x[m] - c;
-    qp[m] = poly + p[m] * kFvPoly;
-  }
-#pragma unroll
-  for (int k = kFvPoly - 1; k >= kFvLate; --k)
-#pragma unroll
-    for (int m = 0; m < M; ++m) q[m][k] = qp[m][k];
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    P[m] = q[m][kFvPoly - 1];
-    D[m] = P[m];
-    P[m] = __builtin_fma(P[m], z[m], q[m][kFvPoly - 2]);
-  }
-#pragma unroll
-  for (int k = kFvPoly - 3; k >= 0; --k) {
-    if (k == kFvPoly - 5) {
-#pragma unroll
-      for (int l = kFvLate - 1; l >= 0; --l)
-#pragma unroll
-        for (int m = 0; m < M; ++m) q[m][l] = qp[m][l];
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      if (FIRST || m > 0) D[m] = __builtin_fma(D[m], z[m], P[m]);
-      P[m] = __builtin_fma(P[m], z[m], q[m][k]);
-    }
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      asm volatile("" : "+v"(P[m]));
-      if (FIRST || m > 0) asm volatile("" : "+v"(D[m]));
-    }
-  }
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    s1[m] = P[m];
-    s2[m] = FIRST || m > 0 ? -D[m] : 0.0;
-  }
-}
 
 struct FvSums {
   double s1, s2;
@@ -241,7 +171,7 @@ __device__ __forceinline__ FvOut fv_iface(const FvArgs &a, const FvScale &sc, co
   for (int m = 0; m < M; ++m) {
     x[m] = delta[m] * sc.inv_k2;
     p[m] = fv_panel(x[m]);
-    near &= (unsigned)p[m] < (unsigned)kFvPanels;
+    near &= (unsigned)p[m] < (unsigned)a.n_panels;
   }
   FvOut o;
   o.bad = false;
@@ -255,7 +185,7 @@ __device__ __forceinline__ FvOut fv_iface(const FvArgs &a, const FvScale &sc, co
       const int pm = fv_panel(xm);
       o.bad |= bad;
       FvSums s;
-      if ((unsigned)pm < (unsigned)kFvPanels)
+      if ((unsigned)pm < (unsigned)a.n_panels)
         fv_poly<1, true>(poly, &xm, &pm, &s.s1, &s.s2);
       else
         s = fv_radial_far(a.tab, a.n_r, xm);
@@ -386,7 +316,7 @@ __global__ __launch_bounds__(kFvMaxWaves * kWave, 4) void fv_solve_kernel(FvArgs
   FvScale *scales = reinterpret_cast<FvScale *>(isj + n + 1);  // [kFvScaleSteps][3]
   int *bad_flag = reinterpret_cast<int *>(scales + 3 * kFvScaleSteps);
   const double *y = a.y0 + r * n;
-  for (int i = tid; i < kFvPanels * kFvPoly; i += bs) poly[i] = a.poly[i];
+  for (int i = tid; i < a.n_panels * kFvPoly; i += bs) poly[i] = a.poly[i];
   for (int i = tid; i < n; i += bs) Y[i] = y[i];
   for (int j = tid; j <= n; j += bs) isj[j] = fv_isj(a, j);
   if (tid == 0) {

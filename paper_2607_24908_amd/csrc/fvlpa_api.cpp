@@ -50,6 +50,7 @@ int Ctx::fvlpa_device(const frg_fvlpa &f, int64_t n, double t_end, int64_t n_ste
   FvArgs a{};
   a.tab = tab;
   a.poly = poly;
+  a.n_panels = poly ? kFvPanels : 0;
   a.Q = d;
   d += nq;
   a.lam = d;

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 
 #include "frg_internal.h"
@@ -13,6 +14,7 @@
 
 #include "device_fp32c.h"
 #include "device_fp64.h"
+#include "device_panels.h"
 #include "device_grid.h"
 
 namespace frg {
@@ -555,35 +557,47 @@ __device__ __forceinline__ void fd_coef(int64_t j, int64_t n, int o, double i2, 
   *c2 = b;
 }
 
-// LPA right-hand side for a batch of flows: one wave per grid point, lanes
-// over radial nodes; F_1 and F_2 at the sigma and pion masses.
-__global__ __launch_bounds__(256) void lpa_kernel(const LpaJob *__restrict__ jobs,
-                                                  const int64_t *__restrict__ start, int n_jobs,
-                                                  int64_t total) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t gid = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-  if (gid >= total) return;
-  int lo = 0, hi = n_jobs - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (start[mid] <= gid) lo = mid; else hi = mid - 1;
+// s1 and s2 outside the panels, term by term.
+__device__ __forceinline__ void lpa_sums(const LpaJob &jb, double x, double &s1, double &s2) {
+  s1 = 0.0;
+  s2 = 0.0;
+#pragma unroll 1
+  for (int i = 0; i < jb.n_r; ++i) {
+    const double g = rcp64(jb.tab[jb.n_r + i] + x);
+    const double c = jb.tab[i] * g;
+    s1 += c;
+    s2 = __builtin_fma(c, g, s2);
   }
-  const LpaJob jb = jobs[lo];
-  const int64_t j = gid - start[lo];
-  const int64_t n = jb.n;
-  const double *U = jb.U;
+}
+
+// LPA right-hand side and Jacobian bands for a batch of flows: one lane per grid
+// point, F_1 and F_2 at its sigma and pion mass from the panels (outside them
+// term by term).  Workgroups of one wave, so that a flow of 1024 points uses 16
+// CUs; the job of a workgroup is found by scalar loads.
+//
+// Bound by launch and memory latency: arguments, U, panels, stores, one after
+// the other.  13 flows of 128 to 1024 points, with Jacobian bands: 4.4 us (one
+// wave per grid point with its lanes over the 64 radial nodes took 10.2 us,
+// and the upload of the job table before it 3.1 us); in the server's pinned
+// buffers 5.6 us per batch (8.6 us).
+__device__ __forceinline__ void lpa_point(const LpaJob &jb, int j) {
+  const int n = jb.n;
   const double dr = jb.dr;
-  double d1, d2;
+  // four values of U from c, the points of j's formulas among them (n >= 4)
+  const int c = min(max(j - 1, 0), n - 4);
+  const double u0 = jb.U[c], u1 = jb.U[c + 1], u2 = jb.U[c + 2], u3 = jb.U[c + 3];
+  const bool last2 = j == n - 2;  // c = j - 2 there, else j - 1
+  const double ul = last2 ? u1 : u0, um = last2 ? u2 : u1, ur = last2 ? u3 : u2;
+  double d1 = ur - ul, d2 = (ur - 2.0 * um) + ul;
   if (j == 0) {
-    d1 = ((-3.0 * U[0] + 4.0 * U[1]) - U[2]) / (2.0 * dr);
-    d2 = (((2.0 * U[0] - 5.0 * U[1]) + 4.0 * U[2]) - U[3]) / (dr * dr);
+    d1 = (-3.0 * u0 + 4.0 * u1) - u2;
+    d2 = ((2.0 * u0 - 5.0 * u1) + 4.0 * u2) - u3;
   } else if (j == n - 1) {
-    d1 = ((3.0 * U[n - 1] - 4.0 * U[n - 2]) + U[n - 3]) / (2.0 * dr);
-    d2 = (((2.0 * U[n - 1] - 5.0 * U[n - 2]) + 4.0 * U[n - 3]) - U[n - 4]) / (dr * dr);
-  } else {
-    d1 = (U[j + 1] - U[j - 1]) / (2.0 * dr);
-    d2 = ((U[j + 1] - 2.0 * U[j]) + U[j - 1]) / (dr * dr);
+    d1 = (3.0 * u3 - 4.0 * u2) + u1;
+    d2 = ((2.0 * u3 - 5.0 * u2) + 4.0 * u1) - u0;
   }
+  d1 = d1 / (2.0 * dr);
+  d2 = d2 / (dr * dr);
   const double rho = (double)j * dr;
   const double ms = d1 + (2.0 * rho) * d2;
   const double mp = d1;
@@ -591,39 +605,59 @@ __global__ __launch_bounds__(256) void lpa_kernel(const LpaJob *__restrict__ job
   const double dp = mp + jb.k2;
   const bool pion = jb.N > 1;
   const bool ok = ds > 0.0 && (!pion || dp > 0.0);
-  const double dsh = (ok ? ds : jb.k2) * jb.inv_k2;
-  const double dph = ((ok && pion) ? dp : jb.k2) * jb.inv_k2;
-  const double *chat = jb.tab;
-  const double *hhat = jb.tab + jb.n_r;
-  double f1s = 0.0, f2s = 0.0, f1p = 0.0, f2p = 0.0;
-  for (int i = lane; i < jb.n_r; i += kWave) {
-    const double c = chat[i], h = hhat[i];
-    const double gs = rcp64(h + dsh);
-    const double gp = rcp64(h + dph);
-    const double cs = c * gs, cp = c * gp;
-    f1s += cs;
-    f2s = __builtin_fma(cs, gs, f2s);
-    f1p += cp;
-    f2p = __builtin_fma(cp, gp, f2p);
+  const double x[2] = {(ok ? ds : jb.k2) * jb.inv_k2, ((ok && pion) ? dp : jb.k2) * jb.inv_k2};
+  const int p[2] = {fv_panel(x[0]), fv_panel(x[1])};
+  double s1[2], s2[2];
+  if (jb.poly && (unsigned)p[0] < (unsigned)kFvPanels && (unsigned)p[1] < (unsigned)kFvPanels) {
+    fv_poly<2, true>(jb.poly, x, p, s1, s2);
+  } else {
+    lpa_sums(jb, x[0], s1[0], s2[0]);
+    lpa_sums(jb, x[1], s1[1], s2[1]);
   }
-  const double F1s = jb.pre1 * wave_sum(f1s);
-  const double F2s = jb.pre2 * wave_sum(f2s);
-  const double F1p = pion ? jb.pre1 * wave_sum(f1p) : 0.0;
-  const double F2p = pion ? jb.pre2 * wave_sum(f2p) : 0.0;
+  const double F1s = jb.pre1 * s1[0];
+  const double F2s = jb.pre2 * s2[0];
+  const double F1p = pion ? jb.pre1 * s1[1] : 0.0;
+  const double F2p = pion ? jb.pre2 * s2[1] : 0.0;
   const double nan = __builtin_nan("");
-  if (lane == 0) {
-    jb.dUdt[j] = ok ? 0.5 * (F1s + jb.Nm1 * F1p) : nan;
-    if (!ok && jb.flag) *jb.flag = 1;
-  }
-  if (jb.jac && lane < 7) {
-    const int o = lane - 3;
+  jb.dUdt[j] = ok ? 0.5 * (F1s + jb.Nm1 * F1p) : nan;
+  if (!ok && jb.flag) *jb.flag = 1;
+  if (!jb.jac) return;
+#pragma unroll
+  for (int o = -3; o <= 3; ++o) {
     double c1, c2;
-    fd_coef(j, n, o, 1.0 / (2.0 * dr), 1.0 / (dr * dr), &c1, &c2);
+    fd_coef(j, n, o, jb.i2, jb.i1, &c1, &c2);
     const double dms = c1 + (2.0 * rho) * c2;
     const double v = -0.5 * (F2s * dms + (jb.Nm1 * F2p) * c1);
-    const int64_t col = j + o;
-    jb.jac[(int64_t)lane * n + j] = ok ? ((col >= 0 && col < n) ? v : 0.0) : nan;
+    const int col = j + o;
+    jb.jac[(int64_t)(o + 3) * n + j] = ok ? ((col >= 0 && col < n) ? v : 0.0) : nan;
   }
+}
+
+__device__ __forceinline__ void lpa_block(const LpaJob &jb) {
+  const int j = ((int)blockIdx.x - jb.block) * kLpaBlock + (int)threadIdx.x;
+  if (j < jb.n) lpa_point(jb, j);
+}
+// Jobs in the kernel's arguments (which hold 4 KB, so at most kLpaArgs): no upload
+// before the launch and no look-up through memory.  first[f]: first workgroup of job f (INT_MAX
+// past the last), side by side so that two scalar loads find the job.
+struct LpaArgs {
+  int first[kLpaArgs];
+  LpaJob job[kLpaArgs];
+};
+__global__ __launch_bounds__(kLpaBlock) void lpa_args_kernel(LpaArgs a) {
+  int f = 0;
+#pragma unroll
+  for (int i = 1; i < kLpaArgs; ++i) f += a.first[i] <= (int)blockIdx.x;
+  lpa_block(a.job[f]);
+}
+__global__ __launch_bounds__(kLpaBlock) void lpa_table_kernel(const LpaJob *__restrict__ jobs,
+                                                              int n_jobs) {
+  int f = 0, end = n_jobs;  // the last job with block <= blockIdx.x
+  while (end - f > 1) {
+    const int mid = (f + end) >> 1;
+    if (jobs[mid].block <= (int)blockIdx.x) f = mid; else end = mid;
+  }
+  lpa_block(jobs[f]);
 }
 
 }  // namespace
@@ -862,13 +896,23 @@ int launch_grid(const GridArgs &g, int reg, int M, int W, void *stream) {
   return (int)hipGetLastError();
 }
 
-int launch_lpa(const LpaJob *d_jobs, const int64_t *d_start, int n_jobs, int64_t total_points,
-               void *stream) {
-  if (total_points <= 0) return 0;
-  const int waves = 4;
-  const int64_t blocks = (total_points + waves - 1) / waves;
-  hipLaunchKernelGGL(lpa_kernel, dim3((unsigned)blocks), dim3(64 * waves), 0, (hipStream_t)stream,
-                     d_jobs, d_start, n_jobs, total_points);
+int launch_lpa_args(const LpaJob *jobs, int n_jobs, int64_t blocks, void *stream) {
+  if (blocks <= 0) return 0;
+  if (n_jobs > kLpaArgs) return (int)hipErrorInvalidValue;
+  LpaArgs a;
+  for (int i = 0; i < kLpaArgs; ++i) {
+    a.first[i] = i < n_jobs ? jobs[i].block : INT_MAX;
+    a.job[i] = i < n_jobs ? jobs[i] : LpaJob{};
+  }
+  hipLaunchKernelGGL(lpa_args_kernel, dim3((unsigned)blocks), dim3(kLpaBlock), 0,
+                     (hipStream_t)stream, a);
+  return (int)hipGetLastError();
+}
+
+int launch_lpa_table(const LpaJob *d_jobs, int n_jobs, int64_t blocks, void *stream) {
+  if (blocks <= 0) return 0;
+  hipLaunchKernelGGL(lpa_table_kernel, dim3((unsigned)blocks), dim3(kLpaBlock), 0,
+                     (hipStream_t)stream, d_jobs, n_jobs);
   return (int)hipGetLastError();
 }
 

@@ -266,8 +266,8 @@ void Server::run_flow(Flow *f) {
 }
 
 // Stage the batch's right-hand sides into its buffer and enqueue it on the
-// server stream: the buffer's layout is jobs | start | U of each flow | flags
-// | outputs of each flow (dU/dt, then the 7 bands when asked); [0, o_out)
+// server stream: the buffer's layout is jobs (of more flows than a launch takes
+// as arguments) | U of each flow | flags | outputs of each flow (dU/dt, then the 7 bands when asked); [0, o_out)
 // goes up and [o_flags, end) comes back (copy mode), or the kernel reads and
 // writes the pinned buffer in place (zero copy).  Records the buffer's event.
 void Server::launch_batch(Batch &b) {
@@ -279,12 +279,10 @@ void Server::launch_batch(Batch &b) {
   std::vector<const double *> Us(nb);
   std::vector<double *> Ds(nb), Js(nb);
   std::vector<LpaJob> jobs(nb);
-  std::vector<int64_t> start(nb + 1);
   std::vector<size_t> o_u(nb);
   b.o_o.resize(nb);
-  const size_t o_start = up8(nb * sizeof(LpaJob));
-  const size_t o_U = up8(o_start + (nb + 1) * sizeof(int64_t));
-  size_t cu = o_U;
+  const bool by_args = nb <= kLpaArgs;
+  size_t cu = by_args ? 0 : up8(nb * sizeof(LpaJob));
   for (int i = 0; i < nb; ++i) {
     o_u[i] = cu;
     cu += b.flows[i]->n * sizeof(double);
@@ -318,22 +316,24 @@ void Server::launch_batch(Batch &b) {
     Js[i] = f->want_jac ? Ds[i] + f->n : nullptr;
   }
   std::memset(g.h + b.o_flags, 0, o_out - b.o_flags);
+  int64_t blocks;
   {
     std::lock_guard<std::mutex> lk(ctx->mu);
     b.rc = ctx->lpa_job_table(nb, lpas.data(), ts.data(), Us.data(), Ds.data(), Js.data(),
-                              (int *)(dev + b.o_flags), jobs.data(), start.data());
+                              (int *)(dev + b.o_flags), jobs.data(), &blocks);
   }
   if (b.rc != FRG_OK) return;
-  std::memcpy(g.h, jobs.data(), nb * sizeof(LpaJob));
-  std::memcpy(g.h + o_start, start.data(), (nb + 1) * sizeof(int64_t));
+  if (!by_args) std::memcpy(g.h, jobs.data(), nb * sizeof(LpaJob));
+  auto launch = [&] {
+    return (by_args ? launch_lpa_args(jobs.data(), nb, blocks, stream)
+                    : launch_lpa_table((const LpaJob *)dev, nb, blocks, stream)) == 0;
+  };
   bool ok;
   if (zero_copy) {
-    ok = launch_lpa((const LpaJob *)dev, (const int64_t *)(dev + o_start), nb, start[nb],
-                    stream) == 0;
+    ok = launch();
   } else {
     ok = hipMemcpyAsync(g.d, g.h, o_out, hipMemcpyHostToDevice, stream) == hipSuccess &&
-         launch_lpa((const LpaJob *)dev, (const int64_t *)(dev + o_start), nb, start[nb],
-                    stream) == 0 &&
+         launch() &&
          hipMemcpyAsync(g.h + b.o_flags, g.d + b.o_flags, end - b.o_flags,
                         hipMemcpyDeviceToHost, stream) == hipSuccess;
   }
