@@ -241,9 +241,16 @@ int Server::rhs_cb(void *user, double t, const double *U, int64_t n, double *dUd
   }
   s->cv_disp.notify_one();
   if (!spin || !spin_until([&] { return f->ready_a.load(std::memory_order_acquire); })) {
+    // a stop ends the wait of a call that still queues; one that a batch has
+    // taken is waited for, since the dispatcher reads and writes its vectors
     std::unique_lock<std::mutex> lk(s->m);
-    f->cv.wait(lk, [&] { return f->ready || s->stop; });
-    if (!f->ready) return FRG_E_DEVICE;
+    auto queued = [&] { return std::find(s->pending.begin(), s->pending.end(), f); };
+    f->cv.wait(lk, [&] { return f->ready || (s->stop && queued() != s->pending.end()); });
+    if (!f->ready) {
+      s->pending.erase(queued());
+      s->n_pending.fetch_sub(1, std::memory_order_relaxed);
+      return FRG_E_DEVICE;
+    }
   }
   return f->rc;
 }

@@ -61,3 +61,27 @@ def test_batches_and_panel_edges(n_flows):
     finally:
         torch.cuda.synchronize()
         frg.frg_destroy(ctx)
+
+
+def test_destroy_while_the_first_batch_is_prepared():
+    """Flows whose calls a batch has taken when the context goes (the first batch
+    builds the tables of 1024 radial nodes, longer than a call polls) outlive that
+    batch; a later context works."""
+    print("[case] destroy during the first batch", flush=True)
+    for i in range(3):
+        c = frg.frg_create(0)
+        outs = [np.zeros(256) for _ in range(8)]
+        lpa = frg.make_lpa(d=3, N=2, n_radial=1024, q_max_over_k=6.0 + 0.1 * i, n_grid=256)
+        for o in outs:
+            frg.frg_submit(c, frg.make_request(lpa, 6.0, 0.05, -9.0, 1e-8, 1e-10, o))
+        frg.frg_destroy(c)
+        assert all(np.all(np.isfinite(o)) for o in outs)
+    c = frg.frg_create(0)
+    try:
+        U = torch.zeros(64, dtype=torch.float64, device="cuda")
+        D = torch.full_like(U, float("nan"))
+        frg.frg_flow_rhs(c, frg.make_lpa(d=3, N=1, n_grid=64), 0.0, U, D)
+        torch.cuda.synchronize()
+        assert torch.isfinite(D).all()
+    finally:
+        frg.frg_destroy(c)
