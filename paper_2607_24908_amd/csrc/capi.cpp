@@ -884,6 +884,7 @@ int Ctx::lpa_job_table(int n, const frg_lpa *lpa, const double *t, const double 
     j.n_r = l.n_radial;
     j.N = l.N;
     j.block = (int32_t)*blocks;
+    j.far_bands = 1;
     *blocks += (l.n_grid + kLpaBlock - 1) / kLpaBlock;
   }
   return FRG_OK;
@@ -897,13 +898,13 @@ int Ctx::lpa_jobs(int n, const frg_lpa *lpa, const double *t, const double *cons
   if (rc) return rc;
   int e;
   if (n <= kLpaArgs) {
-    e = launch_lpa_args(jobs.data(), n, blocks, st);
+    e = launch_lpa_args(jobs.data(), n, blocks, LpaDone{}, st);
   } else {
     void *dev;
     int slot;
     rc = ring.upload(jobs.data(), n * sizeof(LpaJob), st, &dev, &slot);
     if (rc) return rc;
-    e = launch_lpa_table((const LpaJob *)dev, n, blocks, st);
+    e = launch_lpa_table((const LpaJob *)dev, n, blocks, LpaDone{}, st);
     rc = ring.release(slot, st);
   }
   if (e) return hip_fail((hipError_t)e, "lpa kernel launch");

@@ -139,6 +139,16 @@ struct LpaJob {
   double i2, i1;      // 1/(2 dr), 1/dr^2
   int32_t n, n_r, N;
   int32_t block;      // first workgroup of the flow in its launch
+  int32_t far_bands;  // bands -3, -2, 2, 3: 1 all rows, 0 only the first and last row
+                      // (the others are zero)
+};
+// Completion of an LPA launch for a host that polls: the last of its workgroups
+// sets *word (host memory) to value after all stores of the launch; *count
+// (device memory) is 0 before and after. word null: none.
+struct LpaDone {
+  unsigned *count;
+  unsigned *word;
+  unsigned value;
 };
 // Workgroups of kLpaBlock grid points; jobs a launch carries in its arguments.
 constexpr int kLpaBlock = 64;
@@ -365,7 +375,9 @@ int launch_tab(const TabArgs &t, int reg, int W, bool lds_rows, int64_t stream_b
 int tab_lds_bytes(const TabArgs &t, bool lds_rows);
 // jobs on the host, at most kLpaArgs, passed as kernel arguments; or any number
 // in memory the kernel can read.
-int launch_lpa_args(const LpaJob *jobs, int n_jobs, int64_t blocks, void *stream);
-int launch_lpa_table(const LpaJob *d_jobs, int n_jobs, int64_t blocks, void *stream);
+int launch_lpa_args(const LpaJob *jobs, int n_jobs, int64_t blocks, const LpaDone &done,
+                    void *stream);
+int launch_lpa_table(const LpaJob *d_jobs, int n_jobs, int64_t blocks, const LpaDone &done,
+                     void *stream);
 
 }  // namespace frg

@@ -580,7 +580,14 @@ __device__ __forceinline__ void lpa_sums(const LpaJob &jb, double x, double &s1,
 // wave per grid point with its lanes over the 64 radial nodes took 10.2 us,
 // and the upload of the job table before it 3.1 us); in the server's pinned
 // buffers 5.6 us per batch (8.6 us).
+template <bool HOST>
 __device__ __forceinline__ void lpa_point(const LpaJob &jb, int j) {
+  auto put = [](double *at, double v) {
+    if constexpr (HOST)
+      __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    else
+      *at = v;
+  };
   const int n = jb.n;
   const double dr = jb.dr;
   // four values of U from c, the points of j's formulas among them (n >= 4)
@@ -619,23 +626,39 @@ __device__ __forceinline__ void lpa_point(const LpaJob &jb, int j) {
   const double F1p = pion ? jb.pre1 * s1[1] : 0.0;
   const double F2p = pion ? jb.pre2 * s2[1] : 0.0;
   const double nan = __builtin_nan("");
-  jb.dUdt[j] = ok ? 0.5 * (F1s + jb.Nm1 * F1p) : nan;
-  if (!ok && jb.flag) *jb.flag = 1;
+  put(jb.dUdt + j, ok ? 0.5 * (F1s + jb.Nm1 * F1p) : nan);
+  if (!ok && jb.flag) __hip_atomic_store(jb.flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (!jb.jac) return;
 #pragma unroll
   for (int o = -3; o <= 3; ++o) {
+    if ((o < -1 || o > 1) && !jb.far_bands && j != 0 && j != n - 1) continue;
     double c1, c2;
     fd_coef(j, n, o, jb.i2, jb.i1, &c1, &c2);
     const double dms = c1 + (2.0 * rho) * c2;
     const double v = -0.5 * (F2s * dms + (jb.Nm1 * F2p) * c1);
     const int col = j + o;
-    jb.jac[(int64_t)(o + 3) * n + j] = ok ? ((col >= 0 && col < n) ? v : 0.0) : nan;
+    put(jb.jac + (int64_t)(o + 3) * n + j, ok ? ((col >= 0 && col < n) ? v : 0.0) : nan);
   }
 }
 
-__device__ __forceinline__ void lpa_block(const LpaJob &jb) {
+// HOST: outputs in host memory and a word for a host that polls.  They are
+// written with system-scope stores, which reach the host's memory by themselves,
+// so a workgroup (one wave) only waits for its own before it counts itself done
+// (a release at system scope would write back the L2 in every workgroup).
+template <bool HOST>
+__device__ __forceinline__ void lpa_block(const LpaJob &jb, const LpaDone &done) {
   const int j = ((int)blockIdx.x - jb.block) * kLpaBlock + (int)threadIdx.x;
-  if (j < jb.n) lpa_point(jb, j);
+  if (j < jb.n) lpa_point<HOST>(jb, j);
+  if constexpr (HOST) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    if (threadIdx.x == 0 &&
+        __hip_atomic_fetch_add(done.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+            gridDim.x - 1) {
+      __hip_atomic_store(done.count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(done.word, done.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
 }
 // Jobs in the kernel's arguments (which hold 4 KB, so at most kLpaArgs): no upload
 // before the launch and no look-up through memory.  first[f]: first workgroup of job f (INT_MAX
@@ -644,20 +667,22 @@ struct LpaArgs {
   int first[kLpaArgs];
   LpaJob job[kLpaArgs];
 };
-__global__ __launch_bounds__(kLpaBlock) void lpa_args_kernel(LpaArgs a) {
+template <bool HOST>
+__global__ __launch_bounds__(kLpaBlock) void lpa_args_kernel(LpaArgs a, LpaDone done) {
   int f = 0;
 #pragma unroll
   for (int i = 1; i < kLpaArgs; ++i) f += a.first[i] <= (int)blockIdx.x;
-  lpa_block(a.job[f]);
+  lpa_block<HOST>(a.job[f], done);
 }
+template <bool HOST>
 __global__ __launch_bounds__(kLpaBlock) void lpa_table_kernel(const LpaJob *__restrict__ jobs,
-                                                              int n_jobs) {
+                                                              int n_jobs, LpaDone done) {
   int f = 0, end = n_jobs;  // the last job with block <= blockIdx.x
   while (end - f > 1) {
     const int mid = (f + end) >> 1;
     if (jobs[mid].block <= (int)blockIdx.x) f = mid; else end = mid;
   }
-  lpa_block(jobs[f]);
+  lpa_block<HOST>(jobs[f], done);
 }
 
 }  // namespace
@@ -896,7 +921,8 @@ int launch_grid(const GridArgs &g, int reg, int M, int W, void *stream) {
   return (int)hipGetLastError();
 }
 
-int launch_lpa_args(const LpaJob *jobs, int n_jobs, int64_t blocks, void *stream) {
+int launch_lpa_args(const LpaJob *jobs, int n_jobs, int64_t blocks, const LpaDone &done,
+                    void *stream) {
   if (blocks <= 0) return 0;
   if (n_jobs > kLpaArgs) return (int)hipErrorInvalidValue;
   LpaArgs a;
@@ -904,15 +930,16 @@ int launch_lpa_args(const LpaJob *jobs, int n_jobs, int64_t blocks, void *stream
     a.first[i] = i < n_jobs ? jobs[i].block : INT_MAX;
     a.job[i] = i < n_jobs ? jobs[i] : LpaJob{};
   }
-  hipLaunchKernelGGL(lpa_args_kernel, dim3((unsigned)blocks), dim3(kLpaBlock), 0,
-                     (hipStream_t)stream, a);
+  hipLaunchKernelGGL(done.word ? lpa_args_kernel<true> : lpa_args_kernel<false>, dim3((unsigned)blocks), dim3(kLpaBlock), 0,
+                     (hipStream_t)stream, a, done);
   return (int)hipGetLastError();
 }
 
-int launch_lpa_table(const LpaJob *d_jobs, int n_jobs, int64_t blocks, void *stream) {
+int launch_lpa_table(const LpaJob *d_jobs, int n_jobs, int64_t blocks, const LpaDone &done,
+                     void *stream) {
   if (blocks <= 0) return 0;
-  hipLaunchKernelGGL(lpa_table_kernel, dim3((unsigned)blocks), dim3(kLpaBlock), 0,
-                     (hipStream_t)stream, d_jobs, n_jobs);
+  hipLaunchKernelGGL(done.word ? lpa_table_kernel<true> : lpa_table_kernel<false>, dim3((unsigned)blocks), dim3(kLpaBlock), 0,
+                     (hipStream_t)stream, d_jobs, n_jobs, done);
   return (int)hipGetLastError();
 }
 

@@ -10,21 +10,25 @@
 // thread.  Its right-hand-side calls are handed to one dispatcher thread,
 // which takes ALL calls pending at that moment -- from any mix of flows,
 // grid sizes and N -- and serves them with one batched LPA launch on the
-// server's stream (continuous batching: flows join and leave at the
+// a stream of the server's (continuous batching: flows join and leave at the
 // granularity of a right-hand-side call, and calls that arrive while a batch
 // is on the GPU form the next batch).  A flow's result does not depend on
 // which flows shared its launches: the kernel evaluates each grid point of
 // each flow independently, in a fixed order.
 //
-// Round trip of a batch: descriptors, the U of every flow and zeroed domain
-// flags are packed into one pinned host buffer; the kernel reads them there
-// and writes the flags and every flow's outputs back into it (zero copy, one
-// launch and one event per batch; knob server_zero_copy), or the packed head
-// goes up in one copy and the flags and outputs come back in one (a device
-// mirror of the buffer).  The outputs are then written into the waiting
-// flows' own buffers.  There are two such buffers: while one batch runs, the
-// dispatcher stages and enqueues the next into the other, then waits for the
-// running one and hands it back.
+// Round trip of a batch: the U of every flow and zeroed domain flags are packed
+// into one pinned host buffer; the kernel reads them there and writes the
+// flags and every flow's outputs back into it (zero copy; knob
+// server_zero_copy), or the packed head goes up in one copy and the flags and
+// outputs come back in one (a device mirror of the buffer).  In zero copy the
+// kernel's last workgroup sets a word in host memory that the dispatcher polls.  A
+// flow that polls for its answer copies its outputs from the buffer itself,
+// beside the other flows and the dispatcher; for a sleeping one the dispatcher
+// copies.  There are two such buffers, each with its stream, so that two batches
+// run side by side; a buffer is staged again when its batch is back and its last
+// reader is done.  Six flows of up to 1024 points submitted at once: 26 ms; with
+// an event recorded and waited for per batch, one stream and every copy made by
+// the dispatcher 42 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -61,6 +65,9 @@ struct Flow {
   double *dUdt_dst = nullptr;
   double *jac_dst = nullptr;
   bool want_jac = false;
+  bool spin = false;                    // polls for its answer, and copies it
+  const double *out = nullptr;          // its outputs in the staging buffer
+  std::atomic<int> *readers = nullptr;  // of that buffer, to count down
   bool ready = false;
   std::atomic<bool> ready_a{false};  // mirror of ready for waiting without the lock
   int rc = FRG_OK;
@@ -75,7 +82,11 @@ struct Stage {
   char *hd = nullptr;  // its device address
   char *d = nullptr;   // device mirror (copy mode)
   size_t cap = 0;
-  hipEvent_t done = nullptr;  // recorded after the batch's last operation
+  hipStream_t stream = nullptr;
+  hipEvent_t done = nullptr;     // copy mode: recorded after the batch's last operation
+  volatile unsigned *word = nullptr;  // zero copy: pinned, set by the batch's last workgroup
+  LpaDone signal{};              // its device address, the workgroup counter
+  std::atomic<int> readers{0};   // flows that still copy their outputs
 };
 
 // A launched batch, until its outputs are handed back.
@@ -83,7 +94,8 @@ struct Batch {
   std::vector<Flow *> flows;
   std::vector<size_t> o_o;  // each flow's outputs in the staging buffer
   size_t o_flags = 0;
-  int slot = 0;
+  bool zero_copy = false;
+  unsigned polls = 0;
   int rc = FRG_OK;
 };
 
@@ -93,12 +105,14 @@ struct Batch {
 // steppers need.
 constexpr int kSpinFlows = 12;
 
+constexpr int kStages = 2;
+constexpr int kWordStride = 32;  // unsigneds: words and counters on lines of their own
+
 struct Server {
   Context *ctx = nullptr;
-  hipStream_t stream = nullptr;
-  // two staging buffers: the next batch is staged and enqueued while the
-  // previous one runs (at most two batches in flight, handed back in order)
-  Stage stg[2];
+  Stage stg[kStages];
+  unsigned *words = nullptr;   // pinned, kWordStride apart
+  unsigned *counts = nullptr;  // device
   std::mutex m;
   std::condition_variable cv_disp;
   std::deque<Flow *> queue;
@@ -118,13 +132,16 @@ struct Server {
 
   int start();
   void shutdown();
+  void release();
   void dispatch_loop();
   void admit_locked();
   static int rhs_cb(void *user, double t, const double *U, int64_t n, double *dUdt, double *jac);
   void run_flow(Flow *f);
   bool grow_stage(Stage &g, size_t bytes);
-  void launch_batch(Batch &b);
-  void finish_batch(Batch &b);
+  void launch_batch(Batch &b, Stage &g);
+  bool batch_done(Batch &b, Stage &g, bool block);
+  void finish_batch(Batch &b, Stage &g);
+  static void take_outputs(Flow *f, const double *o);
 };
 
 // A right-hand side comes back, and the next call arrives, within tens of
@@ -145,11 +162,27 @@ static bool spin_until(Cond cond) {
 }
 
 int Server::start() {
-  if (hipStreamCreateWithFlags(&stream, hipStreamNonBlocking) != hipSuccess)
-    return fail(FRG_E_DEVICE, "server stream");
-  for (Stage &g : stg)
-    if (hipEventCreateWithFlags(&g.done, hipEventDisableTiming) != hipSuccess)
-      return fail(FRG_E_DEVICE, "server event");
+  const size_t bytes = sizeof(unsigned) * kStages * kWordStride;
+  void *dev_words = nullptr;
+  if (hipHostMalloc((void **)&words, bytes, hipHostMallocMapped | hipHostMallocCoherent) !=
+          hipSuccess ||
+      hipHostGetDevicePointer(&dev_words, words, 0) != hipSuccess ||
+      hipMalloc((void **)&counts, bytes) != hipSuccess ||
+      hipMemset(counts, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    release();
+    return fail(FRG_E_DEVICE, "server completion words");
+  }
+  std::memset(words, 0, bytes);
+  for (int i = 0; i < kStages; ++i) {
+    Stage &g = stg[i];
+    g.word = words + i * kWordStride;
+    g.signal = LpaDone{counts + i * kWordStride, (unsigned *)dev_words + i * kWordStride, 0};
+    if (hipStreamCreateWithFlags(&g.stream, hipStreamNonBlocking) != hipSuccess ||
+        hipEventCreateWithFlags(&g.done, hipEventDisableTiming) != hipSuccess) {
+      release();
+      return fail(FRG_E_DEVICE, "server stream");
+    }
+  }
   if (const char *e = std::getenv("FRG_SERVER_SLOTS")) max_active = std::max(1, std::atoi(e));
   if (const char *e = std::getenv("FRG_SERVER_SPIN_FLOWS")) spin_flows = std::max(0, std::atoi(e));
   disp = std::thread([this] { dispatch_loop(); });
@@ -173,13 +206,20 @@ void Server::shutdown() {
   }
   flows.clear();
   queue.clear();
-  if (stream) (void)hipStreamSynchronize(stream);
+  release();
+}
+
+// The buffers, streams and words (no batch in flight, no dispatcher).
+void Server::release() {
   for (Stage &g : stg) {
+    if (g.stream) (void)hipStreamSynchronize(g.stream);
     if (g.d) (void)hipFree(g.d);
     if (g.h) (void)hipHostFree(g.h);
     if (g.done) (void)hipEventDestroy(g.done);
+    if (g.stream) (void)hipStreamDestroy(g.stream);
   }
-  if (stream) (void)hipStreamDestroy(stream);
+  if (words) (void)hipHostFree(words);
+  if (counts) (void)hipFree(counts);
 }
 
 // Dispatcher thread only (no batch of this buffer in flight): make the
@@ -229,6 +269,7 @@ int Server::rhs_cb(void *user, double t, const double *U, int64_t n, double *dUd
     std::lock_guard<std::mutex> lk(s->m);
     if (s->stop) return FRG_E_DEVICE;
     spin = s->active <= s->spin_flows;
+    f->spin = spin;
     f->t = t;
     f->U_src = U;
     f->dUdt_dst = dUdt;
@@ -252,7 +293,24 @@ int Server::rhs_cb(void *user, double t, const double *U, int64_t n, double *dUd
       return FRG_E_DEVICE;
     }
   }
+  if (f->readers) {
+    take_outputs(f, f->out);
+    f->readers->fetch_sub(1, std::memory_order_release);
+  }
   return f->rc;
+}
+
+// Copy a flow's outputs into its stepper's vectors.  Of the bands -3, -2, 2, 3
+// only the first and last row's entries are written (LpaJob::far_bands); the
+// stepper's vector holds zeros in the others from the start.
+void Server::take_outputs(Flow *f, const double *o) {
+  const int64_t n = f->n;
+  std::memcpy(f->dUdt_dst, o, n * sizeof(double));
+  if (!f->want_jac) return;
+  const double *src = o + n;
+  std::memcpy(f->jac_dst + 2 * n, src + 2 * n, 3 * n * sizeof(double));
+  for (int b : {0, 1, 5, 6})
+    for (int64_t i : {(int64_t)0, n - 1}) f->jac_dst[b * n + i] = src[b * n + i];
 }
 
 void Server::run_flow(Flow *f) {
@@ -273,11 +331,11 @@ void Server::run_flow(Flow *f) {
 }
 
 // Stage the batch's right-hand sides into its buffer and enqueue it on the
-// server stream: the buffer's layout is jobs (of more flows than a launch takes
+// buffer's stream: the layout is jobs (of more flows than a launch takes
 // as arguments) | U of each flow | flags | outputs of each flow (dU/dt, then the 7 bands when asked); [0, o_out)
 // goes up and [o_flags, end) comes back (copy mode), or the kernel reads and
 // writes the pinned buffer in place (zero copy).  Records the buffer's event.
-void Server::launch_batch(Batch &b) {
+void Server::launch_batch(Batch &b, Stage &g) {
   TraceRange trace_("frg_server_batch");  // staging and enqueueing one launch
   auto up8 = [](size_t x) { return (x + 7) & ~(size_t)7; };
   const int nb = (int)b.flows.size();
@@ -302,17 +360,15 @@ void Server::launch_batch(Batch &b) {
     co += (b.flows[i]->want_jac ? 8 : 1) * b.flows[i]->n * sizeof(double);
   }
   const size_t end = co;
-  Stage &g = stg[b.slot];
   if (!grow_stage(g, end)) {
     b.rc = FRG_E_NOMEM;
     return;
   }
-  bool zero_copy;
   {
     std::lock_guard<std::mutex> lk(ctx->mu);
-    zero_copy = ctx->tune.server_zero_copy != 0;
+    b.zero_copy = ctx->tune.server_zero_copy != 0;
   }
-  char *dev = zero_copy ? g.hd : g.d;  // where the kernel finds the buffer
+  char *dev = b.zero_copy ? g.hd : g.d;  // where the kernel finds the buffer
   for (int i = 0; i < nb; ++i) {
     Flow *f = b.flows[i];
     lpas[i] = f->req.lpa;
@@ -330,37 +386,60 @@ void Server::launch_batch(Batch &b) {
                               (int *)(dev + b.o_flags), jobs.data(), &blocks);
   }
   if (b.rc != FRG_OK) return;
+  for (LpaJob &j : jobs) j.far_bands = 0;
   if (!by_args) std::memcpy(g.h, jobs.data(), nb * sizeof(LpaJob));
-  auto launch = [&] {
-    return (by_args ? launch_lpa_args(jobs.data(), nb, blocks, stream)
-                    : launch_lpa_table((const LpaJob *)dev, nb, blocks, stream)) == 0;
+  auto launch = [&](const LpaDone &done) {
+    return (by_args ? launch_lpa_args(jobs.data(), nb, blocks, done, g.stream)
+                    : launch_lpa_table((const LpaJob *)dev, nb, blocks, done, g.stream)) == 0;
   };
   bool ok;
-  if (zero_copy) {
-    ok = launch();
+  if (b.zero_copy) {
+    ++g.signal.value;
+    ok = launch(g.signal);
   } else {
-    ok = hipMemcpyAsync(g.d, g.h, o_out, hipMemcpyHostToDevice, stream) == hipSuccess &&
-         launch() &&
+    ok = hipMemcpyAsync(g.d, g.h, o_out, hipMemcpyHostToDevice, g.stream) == hipSuccess &&
+         launch(LpaDone{}) &&
          hipMemcpyAsync(g.h + b.o_flags, g.d + b.o_flags, end - b.o_flags,
-                        hipMemcpyDeviceToHost, stream) == hipSuccess;
+                        hipMemcpyDeviceToHost, g.stream) == hipSuccess &&
+         hipEventRecord(g.done, g.stream) == hipSuccess;
   }
-  ok = ok && hipEventRecord(g.done, stream) == hipSuccess;
   if (!ok) b.rc = FRG_E_DEVICE;
 }
 
-// Wait for a launched batch and hand its outputs back to its flows.
-void Server::finish_batch(Batch &b) {
-  Stage &g = stg[b.slot];
-  if (b.rc == FRG_OK && hipEventSynchronize(g.done) != hipSuccess) b.rc = FRG_E_DEVICE;
-  const int nb = (int)b.flows.size();
-  if (b.rc == FRG_OK) {
-    for (int i = 0; i < nb; ++i) {
-      Flow *f = b.flows[i];
-      const double *o = (const double *)(g.h + b.o_o[i]);
-      std::memcpy(f->dUdt_dst, o, f->n * sizeof(double));
-      if (f->want_jac) std::memcpy(f->jac_dst, o + f->n, 7 * f->n * sizeof(double));
+// Whether a launched batch has come back (block: wait until it has).  A kernel
+// that ended without setting its word, or an error of the stream, makes it one
+// that failed.
+bool Server::batch_done(Batch &b, Stage &g, bool block) {
+  if (b.rc != FRG_OK) return true;
+  for (int i = 1;; ++i, ++b.polls) {
+    if (b.zero_copy && *g.word == g.signal.value) {
+      std::atomic_thread_fence(std::memory_order_acquire);
+      return true;
     }
+    if (!b.zero_copy || b.polls % (1u << 20) == (1u << 20) - 1) {
+      const hipError_t e = b.zero_copy ? hipStreamQuery(g.stream) : hipEventQuery(g.done);
+      if (e == hipSuccess && b.zero_copy && *g.word != g.signal.value) b.rc = FRG_E_DEVICE;
+      if (e != hipSuccess && e != hipErrorNotReady) b.rc = FRG_E_DEVICE;
+      if (e != hipErrorNotReady) return true;
+      (void)hipGetLastError();
+    }
+    if (!block && i % 64 == 0) return false;
   }
+}
+
+// Hand the outputs of a batch that has come back to its flows.
+void Server::finish_batch(Batch &b, Stage &g) {
+  const int nb = (int)b.flows.size();
+  int readers = 0;
+  for (int i = 0; i < nb; ++i) {
+    Flow *f = b.flows[i];
+    f->out = (const double *)(g.h + b.o_o[i]);
+    const bool reads = b.rc == FRG_OK && f->spin;
+    f->readers = reads ? &g.readers : nullptr;
+    readers += reads;
+    if (b.rc == FRG_OK && !reads) take_outputs(f, f->out);
+  }
+  g.readers.store(readers, std::memory_order_relaxed);
   const int *flags = b.rc == FRG_OK ? (const int *)(g.h + b.o_flags) : nullptr;
   std::lock_guard<std::mutex> lk(m);
   ++launches;
@@ -374,49 +453,50 @@ void Server::finish_batch(Batch &b) {
   }
 }
 
-// Batches of the pending right-hand sides.  With no batch in flight the
-// dispatcher waits for work; with one in flight it takes whatever is pending
-// right away, stages and enqueues it (behind the running one, into the other
-// buffer), and only then waits for the running one and hands it back.
+// Batches of the pending right-hand sides: with no batch in flight the
+// dispatcher waits for work; otherwise it hands back batches as they come back
+// and takes whatever is pending as soon as a buffer is free.
 void Server::dispatch_loop() {
   (void)hipSetDevice(ctx->device);
-  Batch inflight;
-  bool busy = false;
+  Batch fly[kStages];
+  bool busy[kStages] = {};
   for (;;) {
-    Batch next;
-    bool stopping = false;
-    if (!busy) {
-      spin_until([&] { return n_pending.load(std::memory_order_acquire) > 0; });
-      std::unique_lock<std::mutex> lk(m);
-      cv_disp.wait(lk, [&] { return !pending.empty() || stop; });
-      stopping = stop;
-      if (!stopping) {
-        next.flows.swap(pending);
-        n_pending.store(0, std::memory_order_relaxed);
+    bool any = false;
+    for (int s = 0; s < kStages; ++s) {
+      if (busy[s] && batch_done(fly[s], stg[s], false)) {
+        finish_batch(fly[s], stg[s]);
+        busy[s] = false;
       }
-    } else if (n_pending.load(std::memory_order_acquire) > 0) {  // a stop is seen once idle
-      std::lock_guard<std::mutex> lk(m);
+      any |= busy[s];
+    }
+    if (!any) spin_until([&] { return n_pending.load(std::memory_order_acquire) > 0; });
+    int free_slot = -1;
+    for (int s = kStages - 1; s >= 0; --s)
+      if (!busy[s] && stg[s].readers.load(std::memory_order_acquire) == 0) free_slot = s;
+    if (any && (free_slot < 0 || n_pending.load(std::memory_order_acquire) == 0)) continue;
+    Batch next;
+    bool stopping;
+    {
+      std::unique_lock<std::mutex> lk(m);
+      if (!any) cv_disp.wait(lk, [&] { return !pending.empty() || stop; });
       stopping = stop;
-      if (!stopping) {
+      if (!stopping && free_slot >= 0) {
         next.flows.swap(pending);
         n_pending.store(0, std::memory_order_relaxed);
       }
     }
     if (stopping) {
-      if (busy) finish_batch(inflight);
+      for (int s = 0; s < kStages; ++s)
+        if (busy[s]) {
+          (void)batch_done(fly[s], stg[s], true);
+          finish_batch(fly[s], stg[s]);
+        }
       return;
     }
     if (!next.flows.empty()) {
-      next.slot = busy ? 1 - inflight.slot : 0;
-      launch_batch(next);
-    }
-    if (busy) {
-      finish_batch(inflight);
-      busy = false;
-    }
-    if (!next.flows.empty()) {
-      inflight = std::move(next);
-      busy = true;
+      launch_batch(next, stg[free_slot]);
+      fly[free_slot] = std::move(next);
+      busy[free_slot] = true;
     }
   }
 }
