@@ -16,10 +16,10 @@
 //     (hot superchunks are split by momenta) and taken from a work counter.
 //  3. tab_seg_reduce_kernel: the superchunks' partial sums, in order.
 //
-// Mapping: a momentum's run of a segment is taken by one wave, the 64 lanes
-// on consecutive terms, and folded over the wave (wave_sum_fold).  The sum of
+// Mapping: a momentum's run of a segment is taken by 16 lanes, on consecutive
+// terms, and folded over them; a wave takes four runs at a time.  The sum of
 // one result is fixed by the shapes: per segment, the run's terms split over
-// the lanes by position, each lane's terms in order, the fixed fold; the
+// the 16 lanes by position, each lane's terms in order, the fixed fold; the
 // segments of a superchunk added in order into part[superchunk][row][momentum];
 // the superchunks in order.  How momenta are split into items changes no bit.
 #include <hip/hip_runtime.h>
@@ -41,9 +41,9 @@ using namespace dev;
 constexpr int kC = kTabSegC;
 constexpr int kS = kTabSegS;
 constexpr int kRB = kTabSegRows;
-static_assert(kRB == 4, "the run fold leaves one row per group of 16 lanes");
+static_assert(kRB == 4, "the run fold leaves one row per group of 4 lanes");
 constexpr int kNT = kTabSegThreads;
-constexpr int kRowLds = kC + 1;           // a segment's nodes and its right neighbour
+constexpr int kRowLds = kC + 2;           // a segment's nodes and its right neighbour, on 16 bytes
 constexpr int kBufD = kRB * kRowLds;      // doubles of one segment buffer
 
 // Node index of an evaluation: k = min(floor(min(t, t_last)), k_last),
@@ -79,26 +79,35 @@ __global__ void tab_seg_zero_kernel(unsigned *hist, int n_super, int *counter) {
 // Four waves per momentum: its terms e = i n_a + j sorted by (segment, e), a
 // counting sort that uses the structure of the coordinates: for a fixed i
 // the node index grows with j (the angular nodes ascend), so the j of one i
-// that fall in one segment form a chunk of consecutive lanes.  Wave w takes
-// the w-th quarter of the radial nodes.
-//  1. counts per wave and segment: each chunk's head adds the chunk's size;
+// that fall in one segment form a chunk of consecutive lanes.  A part of L
+// lanes -- a wave, or half a wave where that holds all angular nodes -- takes an
+// equal share of the radial nodes, part by part in order.
+//  1. counts per part and segment: each chunk's head adds the chunk's size;
 //  2. offs[p][s] = first position of segment >= s (exclusive scan over the
-//     segments), and per wave and segment a cursor: the segment's start plus
-//     the counts of the waves before it, so the quarters keep their order;
+//     segments), and per part and segment a cursor: the segment's start plus
+//     the counts of the parts before it, so the parts keep their order;
 //     term counts per superchunk go to hist;
-//  3. i in order within each wave: each chunk's head takes its position
-//     from its wave's cursor and advances it; the chunk's lanes write their e.
+//  3. i in order within each part: each chunk's head takes its position
+//     from its part's cursor and advances it; the chunk's lanes write their e.
 // The order within a segment is ascending e.  Momenta outside the domain get
 // empty runs.
+//
+// Bound by the latency of the chunk steps, one radial node of a part after the
+// other: 1024 momenta, 128 x 32 nodes: 29.6 us (42.4 with a
+// wave per part, half of its lanes idle).
 constexpr int kSortW = 4;
 static_assert(kS <= kWave && kWave % kS == 0, "superchunk sums within a wave's block");
+__host__ __device__ __forceinline__ int sort_parts(int L) { return kSortW * (kWave / L); }
 
+template <int L>
 __global__ __launch_bounds__(kSortW * kWave) void tab_seg_sort_kernel(TabArgs a, uint16_t *terms,
                                                                       int *offs, unsigned *hist,
                                                                       int n_seg) {
-  extern __shared__ int cnt[];  // [kSortW][n_seg]: counts, then cursors
+  extern __shared__ int cnt[];  // [parts][n_seg]: counts, then cursors
+  constexpr int kParts = kSortW * (kWave / L);
   const int64_t ip = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
+  const int tid = threadIdx.x;
+  const int lane = tid % L, w = tid / L;  // lane of the part, part
   const int n_r = a.n_r, n_a = a.n_a;
   const int E = n_r * n_a;
   int *po = offs + ip * (n_seg + 1);
@@ -109,15 +118,17 @@ __global__ __launch_bounds__(kSortW * kWave) void tab_seg_sort_kernel(TabArgs a,
   }
   const int k_last = (int)a.n_s - 2;
   const double *opx = a.tab + 3 * n_r;
-  for (int x = tid; x < kSortW * n_seg; x += kSortW * kWave) cnt[x] = 0;
+  for (int x = tid; x < kParts * n_seg; x += kSortW * kWave) cnt[x] = 0;
   __syncthreads();
   int *mine = cnt + w * n_seg;
-  const int i_lo = (int)((int64_t)w * n_r / kSortW), i_hi = (int)((int64_t)(w + 1) * n_r / kSortW);
+  // this part's radial nodes, and the steps of the part that has most
+  const int i_lo = (int)((int64_t)w * n_r / kParts), i_hi = (int)((int64_t)(w + 1) * n_r / kParts);
+  const int steps = (n_r + kParts - 1) / kParts;
   // segment of term (i, jb + lane) (q = q_i, oj = 1 + x_{jb + lane}) and the
-  // chunk structure of this block of up to 64 j: head lanes (first lane or
+  // chunk structure of this block of up to L j: head lanes (first lane or
   // segment change), chunk sizes, the last head at or before each lane
-  auto chunk = [&](double q, double oj, int jb, int &sg, bool &head, int &size, int &hl) {
-    const bool valid = jb + lane < n_a;
+  auto chunk = [&](bool on, double q, double oj, int jb, int &sg, bool &head, int &size, int &hl) {
+    const bool valid = on && jb + lane < n_a;
     sg = -1;
     if (valid) {
       const double qm = q - p;
@@ -125,42 +136,46 @@ __global__ __launch_bounds__(kSortW * kWave) void tab_seg_sort_kernel(TabArgs a,
       const double bh = ((2.0 * q) * p) * a.inv_h;
       sg = node_of(__builtin_fma(bh, oj, ah), a.t_last, k_last) / kC;
     }
-    const int prev = __shfl_up(sg, 1, kWave);
+    const int prev = __shfl_up(sg, 1, L);
     head = valid && (lane == 0 || prev != sg);
-    const unsigned long long hm = __builtin_amdgcn_ballot_w64(head);
-    const int nv = min(kWave, n_a - jb);  // valid lanes of the block
+    unsigned long long hm = __builtin_amdgcn_ballot_w64(head);
+    if constexpr (L < kWave) hm = (hm >> ((tid % kWave) / L * L)) & ((1ull << L) - 1ull);
+    const int nv = min(L, n_a - jb);  // valid lanes of the block
     const unsigned long long above = lane == 63 ? 0ull : hm >> (lane + 1);
     const int next = above ? lane + 1 + __builtin_ctzll(above) : nv;
     size = next - lane;
     const unsigned long long upto = hm & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
     hl = 63 - __builtin_clzll(upto | 1ull);
   };
-  // radial nodes 64 at a time in a register (q_i by readlane), the first 64
-  // angular nodes in a register
+  // radial nodes L at a time in a register, the first L angular nodes in one
   const double o0 = lane < n_a ? opx[lane] : 0.0;
   auto oj_of = [&](int jb) { return jb == 0 ? o0 : (jb + lane < n_a ? opx[jb + lane] : 0.0); };
-  for (int i0 = i_lo; i0 < i_hi; i0 += kWave) {
-    const double qv = i0 + lane < i_hi ? a.tab[i0 + lane] : 0.0;
-    const int ni = min(kWave, i_hi - i0);
-    for (int ii = 0; ii < ni; ++ii) {
-      const double q = readlane_d(qv, ii);
-      for (int jb = 0; jb < n_a; jb += kWave) {
-        int sg, size, hl;
-        bool head;
-        chunk(q, oj_of(jb), jb, sg, head, size, hl);
-        if (head) atomicAdd(&mine[sg], size);
-      }
+  // f(on, i, q) for the part's radial nodes in order (every lane of the wave
+  // takes part; on: the part has this node)
+  auto each_node = [&](auto f) {
+    double qv = 0.0;
+    for (int ii = 0; ii < steps; ++ii) {
+      if (ii % L == 0) qv = i_lo + ii + lane < i_hi ? a.tab[i_lo + ii + lane] : 0.0;
+      f(i_lo + ii < i_hi, i_lo + ii, __shfl(qv, ii % L, L));
     }
-  }
+  };
+  each_node([&](bool on, int, double q) {
+    for (int jb = 0; jb < n_a; jb += L) {
+      int sg, size, hl;
+      bool head;
+      chunk(on, q, oj_of(jb), jb, sg, head, size, hl);
+      if (head) atomicAdd(&mine[sg], size);
+    }
+  });
   __syncthreads();
-  if (w == 0) {
+  if (tid < kWave) {
     // exclusive scan over the segments, blocks of 64
     int carry = 0;
     for (int x0 = 0; x0 < n_seg; x0 += kWave) {
-      const int x = x0 + lane;
-      int c[kSortW], tot = 0;
+      const int x = x0 + tid;
+      int c[kParts], tot = 0;
 #pragma unroll
-      for (int v = 0; v < kSortW; ++v) {
+      for (int v = 0; v < kParts; ++v) {
         c[v] = x < n_seg ? cnt[v * n_seg + x] : 0;
         tot += c[v];
       }
@@ -168,13 +183,13 @@ __global__ __launch_bounds__(kSortW * kWave) void tab_seg_sort_kernel(TabArgs a,
 #pragma unroll
       for (int d = 1; d < kWave; d <<= 1) {
         const int t = __shfl_up(incl, d, kWave);
-        if (lane >= d) incl += t;
+        if (tid >= d) incl += t;
       }
       int run = carry + incl - tot;
       if (x < n_seg) {
         po[x] = run;
 #pragma unroll
-        for (int v = 0; v < kSortW; ++v) {
+        for (int v = 0; v < kParts; ++v) {
           cnt[v * n_seg + x] = run;
           run += c[v];
         }
@@ -183,34 +198,39 @@ __global__ __launch_bounds__(kSortW * kWave) void tab_seg_sort_kernel(TabArgs a,
       int hs = tot;
 #pragma unroll
       for (int d = 1; d < kS; d <<= 1) hs += __shfl_xor(hs, d, kWave);
-      if (lane % kS == 0 && x < n_seg && hs) atomicAdd(&hist[x / kS], (unsigned)hs);
+      if (tid % kS == 0 && x < n_seg && hs) atomicAdd(&hist[x / kS], (unsigned)hs);
       carry += __shfl(incl, kWave - 1, kWave);
     }
-    if (lane == 0) po[n_seg] = carry;  // = E
+    if (tid == 0) po[n_seg] = carry;  // = E
   }
   __syncthreads();
   uint16_t *pt = terms + ip * E;
-  for (int i0 = i_lo; i0 < i_hi; i0 += kWave) {
-    const double qv = i0 + lane < i_hi ? a.tab[i0 + lane] : 0.0;
-    const int ni = min(kWave, i_hi - i0);
-    for (int ii = 0; ii < ni; ++ii) {
-      const double q = readlane_d(qv, ii);
-      const int i = i0 + ii;
-      for (int jb = 0; jb < n_a; jb += kWave) {
-        int sg, size, hl;
-        bool head;
-        chunk(q, oj_of(jb), jb, sg, head, size, hl);
-        int base = 0;
-        if (head) {
-          base = mine[sg];
-          mine[sg] = base + size;
-        }
-        base = __shfl(base, hl, kWave);
-        const int j = jb + lane;
-        if (j < n_a) pt[base + (lane - hl)] = (uint16_t)(term_packed(a) ? (i << 8) | j : i * n_a + j);
+  each_node([&](bool on, int i, double q) {
+    for (int jb = 0; jb < n_a; jb += L) {
+      int sg, size, hl;
+      bool head;
+      chunk(on, q, oj_of(jb), jb, sg, head, size, hl);
+      int base = 0;
+      if (head) {
+        base = mine[sg];
+        mine[sg] = base + size;
       }
+      base = __shfl(base, hl, L);
+      const int j = jb + lane;
+      if (on && j < n_a)
+        pt[base + (lane - hl)] = (uint16_t)(term_packed(a) ? (i << 8) | j : i * n_a + j);
     }
-  }
+  });
+}
+
+// Sums of four values over each group of 16 lanes: the lane's value number
+// (lane % 16) / 4, in all four of its lanes.
+__device__ __forceinline__ double fold16(const double *v, int lane) {
+  const double a = split_dpp<0x128, 8>(v[0], v[2], lane);  // offset 8
+  const double b = split_dpp<0x128, 8>(v[1], v[3], lane);
+  double x = split_dpp<0x141, 4>(a, b, lane);              // mirror in 8: the other quad
+  x = x + dpp_f64<0xB1>(x);                                // offsets 1 and 2
+  return x + dpp_f64<0x4E>(x);
 }
 
 // Momenta split of superchunk c: between ceil(n_p / kItemMax) items and
@@ -230,9 +250,18 @@ __device__ __forceinline__ double super_nodes(const TabArgs &a, int c, int n_seg
 
 // Work items from the counter until the list is drained.  Momentum ip of an
 // item is owned by lane l of wave w with ip = p_lo + w + kWaves l; for each
-// segment a wave takes the non-empty runs of its momenta one after another,
-// all 64 lanes on one run (lane l: positions o + l, o + l + 64, ...), and the
-// four row sums of the run are folded over the wave and added by the owner.
+// segment the 16 lanes of group g take the non-empty runs of the momenta with
+// l % 4 = g one after another (lane s of the group: positions o + s, o + s + 16,
+// ...), and the four row sums of the run are folded over the group.  The first
+// terms of the next run are loaded while one is evaluated.
+//
+// The costly items (most terms of a call lie in a few segments, where the
+// momenta far below the nodes' scale meet) are bound by instruction issue and
+// LDS reads, 15 doubles per term; the others by copying their segments, 64 KB at a
+// time.  64 rows of 2^20 nodes, 1024 momenta, 128 x 32 nodes: 449 us; with 64 lanes
+// on one run (77 terms on average) 460 us, with 4 bytes per lane and copy
+// instruction in place of 16 474 us, with both 489 us.  More and smaller items
+// (8 per CU instead of 4) took 60 us longer: each one copies its segments again.
 template <bool PACKED>
 __global__ __launch_bounds__(kNT) void tab_seg_kernel(TabArgs a, const unsigned *hist,
                                                       const uint16_t *__restrict__ terms,
@@ -333,28 +362,33 @@ __global__ __launch_bounds__(kNT) void tab_seg_kernel(TabArgs a, const unsigned 
     const double pv = mine ? a.p[my] : -1.0;
     const bool live = pv >= 0.0;  // NaN and p < 0 have no terms
     const int *pof = offs + (mine ? my : 0) * (int64_t)(n_seg + 1);
-    // accumulators: lane L = 16 r + s holds row r of the wave's momenta
-    // l = s, s + 16, s + 32, s + 48 (acc[l / 16]), where the fold below
-    // leaves the row sums of a run
+    // accumulators: lane 16 g + 4 r + s holds row r of the wave's momenta
+    // l = 4 t + g, t = s, s + 4, s + 8, s + 12 (acc[t / 4]), where the fold
+    // below leaves the row sums of a run
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     const int sg0 = c * kS, sg1 = min(sg0 + kS, n_seg);
     // copy segment sg of the batch's rows into buffer d: waves w, w + kRB, ...
-    // take row w % kRB, 4 bytes per lane and 256 contiguous bytes of LDS per
-    // wave instruction; words beyond the table are left unwritten (never read)
+    // take row w % kRB, 16 bytes per lane and 1 KB of LDS per wave instruction,
+    // the last 0 to 3 words (rows start and end on 8 bytes) by the first of
+    // them; nothing beyond the table is read
     const int lrow = wave % kRB;
     const unsigned *grow32 = reinterpret_cast<const unsigned *>(a.g + (r0 + lrow) * a.n_s);
     const int64_t words = 2 * a.n_s;  // 4-byte words of a row
     auto load = [&](int sg, int d) {
       if (lrow >= nrb) return;  // wave-uniform: no such row in the batch
       const int64_t w0 = 2 * (int64_t)sg * kC;
+      const int nw = (int)min<int64_t>(words - w0, 2 * (kC + 1));
+      const int n16 = nw >> 2;
+      const unsigned *src = grow32 + w0;
       unsigned *dst = reinterpret_cast<unsigned *>(lg0 + d * kBufD + lrow * kRowLds);
-      for (int m = wave / kRB; m * kWave < 2 * kRowLds; m += kWaves / kRB) {  // wave-uniform
+      using Lds = __attribute__((address_space(3))) void *;
+      for (int m = wave / kRB; m * kWave < n16; m += kWaves / kRB) {  // wave-uniform
         const int x = m * kWave + lane;
-        if (x < 2 * kRowLds && w0 + x < words)
-          __builtin_amdgcn_global_load_lds(
-              grow32 + w0 + x, (__attribute__((address_space(3))) void *)(dst + m * kWave), 4, 0,
-              0);
+        if (x < n16)
+          __builtin_amdgcn_global_load_lds(src + 4 * x, (Lds)(dst + 4 * m * kWave), 16, 0, 0);
       }
+      if (wave < kRB && lane < (nw & 3))
+        __builtin_amdgcn_global_load_lds(src + 4 * n16 + lane, (Lds)(dst + 4 * n16), 4, 0, 0);
     };
     load(sg0, 0);
     // run bounds of this lane's momentum: segment sg, and sg + 1 ahead
@@ -370,20 +404,38 @@ __global__ __launch_bounds__(kNT) void tab_seg_kernel(TabArgs a, const unsigned 
       if (sg + 1 < sg1) load(sg + 1, cur ^ 1);
       const double *lg = lg0 + cur * kBufD;
       const int T0 = sg * kC;
-      unsigned long long todo = __builtin_amdgcn_ballot_w64(live && o_nxt > o_cur);
-      while (todo) {  // wave-uniform: the momenta with terms in this segment
-        const int l = __builtin_ctzll(todo);
+      // the momenta of this lane's group with terms in this segment
+      const int g4 = lane >> 4, ls = lane & 15;
+      unsigned long long todo =
+          (__builtin_amdgcn_ballot_w64(live && o_nxt > o_cur) >> g4) & 0x1111111111111111ull;
+      struct Run {
+        const uint16_t *pt;
+        int l, pos, end;  // owner; this lane's next position; end of the run
+        unsigned e;       // the term there
+        bool any;
+      };
+      auto next_run = [&]() {  // every lane of the wave takes part
+        Run r;
+        r.any = todo != 0ull;
+        r.l = g4 + (r.any ? __builtin_ctzll(todo) : 0);
         todo &= todo - 1ull;
-        const int ra0 = __builtin_amdgcn_readlane(o_cur, l);
-        const int ra1 = __builtin_amdgcn_readlane(o_nxt, l);
-        const double p = readlane_d(pv, l);
-        const int64_t ip = p_lo + wave + (int64_t)kWaves * l;
-        const uint16_t *pt = terms + ip * E;
+        const int end = __shfl(o_nxt, r.l, kWave);
+        r.pos = __shfl(o_cur, r.l, kWave) + ls;
+        r.end = r.any ? end : 0;
+        r.pt = terms + (p_lo + wave + (int64_t)kWaves * r.l) * E;
+        r.e = r.pos < r.end ? r.pt[r.pos] : 0u;
+        return r;
+      };
+      Run run = next_run();
+      while (__builtin_amdgcn_ballot_w64(run.any)) {  // wave-uniform
+        const Run ahead = next_run();
+        const double p = __shfl(pv, run.l, kWave);
         double in[kRB];
 #pragma unroll
         for (int r = 0; r < kRB; ++r) in[r] = 0.0;
-        for (int pos = ra0 + lane; pos < ra1; pos += kWave) {
-          const unsigned e = pt[pos];
+        for (; run.pos < run.end; run.pos += 16) {
+          const unsigned e = run.e;
+          if (run.pos + 16 < run.end) run.e = run.pt[run.pos + 16];
           int i, j;
           if constexpr (PACKED) {
             i = (int)(e >> 8);
@@ -414,25 +466,22 @@ __global__ __launch_bounds__(kNT) void tab_seg_kernel(TabArgs a, const unsigned 
             in[r] = __builtin_fma(rad[1 + r] * mu, __builtin_fma(f, g1 - g0, g0), in[r]);
           }
         }
-        // lane groups of 16 end with the sums of rows 0..3
-        const double rs = wave_sum_fold<kRB>(in, lane);
-        if ((lane & 15) == (l & 15)) {
-          switch (l >> 4) {  // wave-uniform: one add, not four selected ones
-            case 0: acc[0] += rs; break;
-            case 1: acc[1] += rs; break;
-            case 2: acc[2] += rs; break;
-            default: acc[3] += rs; break;
-          }
-        }
+        const double rs = fold16(in, lane);
+        const int t = run.l >> 2;
+        const bool owner = run.any && (lane & 3) == (t & 3);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] += owner && (t >> 2) == k ? rs : 0.0;
+        run = ahead;
       }
       o_cur = o_nxt;
       o_nxt = o_after;
     }
     {
-      const int r = lane >> 4;
+      const int r = (lane >> 2) & 3;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const int64_t ip = p_lo + wave + (int64_t)kWaves * ((lane & 15) + 16 * k);
+        const int l = 4 * (4 * k + (lane & 3)) + (lane >> 4);
+        const int64_t ip = p_lo + wave + (int64_t)kWaves * l;
         if (r < nrb && ip < p_hi) part[((int64_t)c * a.n_rows + r0 + r) * a.n_p + ip] = acc[k];
       }
     }
@@ -441,6 +490,7 @@ __global__ __launch_bounds__(kNT) void tab_seg_kernel(TabArgs a, const unsigned 
 
 // out[a, r] = pref sum_c part[c][r][a] (superchunks in order); NaN and the
 // domain flag for p < 0.
+constexpr int kReduce = 16;
 __global__ void tab_seg_reduce_kernel(TabArgs a, const double *part, int n_super) {
   const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (x >= a.n_p * a.n_rows) return;
@@ -449,7 +499,17 @@ __global__ void tab_seg_reduce_kernel(TabArgs a, const double *part, int n_super
   double v;
   if (p >= 0.0) {
     double s = 0.0;
-    for (int c = 0; c < n_super; ++c) s = s + part[((int64_t)c * a.n_rows + r) * a.n_p + ip];
+    const double *q = part + r * a.n_p + ip;
+    const int64_t stride = a.n_rows * a.n_p;
+    int c = 0;
+    for (; c + kReduce <= n_super; c += kReduce) {  // a batch of loads in flight
+      double w[kReduce];
+#pragma unroll
+      for (int k = 0; k < kReduce; ++k) w[k] = q[(c + k) * stride];
+#pragma unroll
+      for (int k = 0; k < kReduce; ++k) s = s + w[k];
+    }
+    for (; c < n_super; ++c) s = s + q[c * stride];
     v = a.pref * s;
   } else {
     v = __builtin_nan("");
@@ -481,13 +541,20 @@ int launch_tab_seg(const TabArgs &t, const TabSegShape &s, const TabSegBufs &b, 
                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
        (void)hipFuncSetAttribute((const void *)&tab_seg_kernel<false>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
-       (void)hipFuncSetAttribute((const void *)&tab_seg_sort_kernel,
+       (void)hipFuncSetAttribute((const void *)&tab_seg_sort_kernel<kWave>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
+       (void)hipFuncSetAttribute((const void *)&tab_seg_sort_kernel<kWave / 2>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
        (void)hipGetLastError(), true);
   (void)once;
   hipLaunchKernelGGL(tab_seg_zero_kernel, dim3(1), dim3(256), 0, st, b.hist, s.n_super, b.counter);
-  hipLaunchKernelGGL(tab_seg_sort_kernel, dim3((unsigned)t.n_p), dim3(kSortW * kWave),
-                     sizeof(int) * kSortW * s.n_seg, st, t, b.terms, b.offs, b.hist, s.n_seg);
+  // half a wave per part where it holds all angular nodes and the LDS (two
+  // workgroups per CU) all counters
+  const bool half = t.n_a <= kWave / 2 && sizeof(int) * sort_parts(kWave / 2) * s.n_seg <= 80 * 1024;
+  hipLaunchKernelGGL(half ? tab_seg_sort_kernel<kWave / 2> : tab_seg_sort_kernel<kWave>,
+                     dim3((unsigned)t.n_p), dim3(kSortW * kWave),
+                     sizeof(int) * sort_parts(half ? kWave / 2 : kWave) * s.n_seg, st, t, b.terms,
+                     b.offs, b.hist, s.n_seg);
   if (term_packed(t))
     hipLaunchKernelGGL(tab_seg_kernel<true>, dim3((unsigned)n_cu), dim3(kNT), (size_t)s.lds, st, t,
                        (const unsigned *)b.hist, (const uint16_t *)b.terms, (const int *)b.offs,
