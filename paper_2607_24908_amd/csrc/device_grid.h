@@ -508,8 +508,9 @@ __device__ __forceinline__ void mfma_powers(double x, int lane, double *v) {
 }
 
 // Two 16-row slices (rows 16 s0 + ., 16 s1 + . of one group): four
-// independent accumulator chains.
-template <int G, int E>
+// independent accumulator chains.  FULL: quotients to rounding (values that are
+// interpolated, where a bias would show; 1 % of a grid's time).
+template <int G, int E, bool FULL = false>
 __device__ __forceinline__ void mfma_slice_pair(const double *grp, int lane, const double *v,
                                                 int s0, int s1, double &tot) {
   constexpr int kP = MfmaShape<G, E>::kP, kN = MfmaShape<G, E>::kN;
@@ -532,9 +533,9 @@ __device__ __forceinline__ void mfma_slice_pair(const double *grp, int lane, con
   P0 = __builtin_amdgcn_mfma_f64_16x16x4f64(l0, v[kP - 1], P0, 0, 0, 0);
   P1 = __builtin_amdgcn_mfma_f64_16x16x4f64(l1, v[kP - 1], P1, 0, 0, 0);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) tot = __builtin_fma(N0[r], rcp64_full(P0[r]), tot);
+  for (int r = 0; r < 4; ++r) tot = __builtin_fma(N0[r], FULL ? rcp64_full(P0[r]) : rcp64(P0[r]), tot);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) tot = __builtin_fma(N1[r], rcp64_full(P1[r]), tot);
+  for (int r = 0; r < 4; ++r) tot = __builtin_fma(N1[r], FULL ? rcp64_full(P1[r]) : rcp64(P1[r]), tot);
 }
 
 // Lane partial (four rows per 16-row slice, every slice of the table) of

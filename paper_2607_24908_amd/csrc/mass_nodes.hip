@@ -379,8 +379,8 @@ __device__ __forceinline__ void node_values(const GridArgs &g, const MassPlan &m
 #pragma unroll 1
           for (int gl = 0; gl < live; ++gl) {
             const double *grp = lC + gl * kRows * kWave;
-            mfma_slice_pair<G, E>(grp, lane, v, 0, 1, tot);
-            mfma_slice_pair<G, E>(grp, lane, v, 2, 3, tot);
+            mfma_slice_pair<G, E, true>(grp, lane, v, 0, 1, tot);
+            mfma_slice_pair<G, E, true>(grp, lane, v, 2, 3, tot);
           }
           tot = swap_add<32>(tot, tot);
           tot = swap_add<16>(tot, tot);
