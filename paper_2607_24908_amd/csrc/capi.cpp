@@ -740,7 +740,7 @@ int Ctx::tab_device(const frg_quad &q, const frg_gtab &tb, int64_t n_p, const do
 // pref, k2, inv_h, t_last, n_p, n_rows, n_s, os_p, os_r, n_r, n_a set by the
 // caller).
 int Ctx::tab_config(TabArgs &a, bool &lds_rows_out, int &W_out, int64_t &sblocks_out,
-                    bool multi_rows) {
+                    bool flows) {
   const int64_t n_p = a.n_p;
   tab_lane_split(a.n_r, a.n_a, &a.R, &a.J, &a.T, &a.U);
   a.pairs = tune.tab_pairs ? 1 : 0;
@@ -749,20 +749,27 @@ int Ctx::tab_config(TabArgs &a, bool &lds_rows_out, int &W_out, int64_t &sblocks
                         tab_lds_bytes(a, true) <= 150 * 1024;
   // rows in LDS: several rows per workgroup share every coordinate (knob
   // tab_rb; auto: two rows when there are two and the LDS holds them, which
-  // measured fastest; four rows of plain values were no faster than two)
-  if (lds_rows && multi_rows) {
+  // measured fastest: 1024 momenta, 64 rows of 4096 nodes 86 us with two, 116 with
+  // one, 124 with four; for flows four where workgroups of 16 waves, one
+  // momentum each, then fill the chip: 64 flows of 256 nodes 18.4 us per stage
+  // with four, 19.4 with two, while 32 flows would leave half of it idle)
+  if (lds_rows) {
     for (int rb : {4, 2}) {
-      if (tune.tab_rb ? tune.tab_rb != rb : (rb != 2 || a.n_rows < rb)) continue;
       TabArgs b = a;
       b.rb = rb;
+      const bool fill = (a.n_rows + 3) / 4 * ((n_p + 15) / 16) >= n_cu;
+      if (tune.tab_rb ? tune.tab_rb != rb
+                      : (a.n_rows < rb || (rb == 4 && !(flows && fill &&
+                                                        pflow_pull_lds_bytes(b) <= 150 * 1024))))
+        continue;
       if (tab_lds_bytes(b, true) <= 150 * 1024) {
         a.rb = rb;
         break;
       }
     }
   }
-  const int W = a.rb > 1 ? std::max(1, std::min(16, tune.tab_rW))
-                         : std::max(1, std::min(4, lds_rows ? tune.tab_W : tune.tab_sW));
+  int W = a.rb > 1 ? std::max(1, std::min(16, tune.tab_rW))
+                   : std::max(1, std::min(4, lds_rows ? tune.tab_W : tune.tab_sW));
   a.pw = std::max(1, std::min(64, lds_rows ? tune.tab_pw : tune.tab_spw));
   // streamed rows: tab_wpc workgroups per CU work through the rows of their
   // XCD one at a time; momentum blocks are made small enough that every
@@ -782,6 +789,11 @@ int Ctx::tab_config(TabArgs &a, bool &lds_rows_out, int &W_out, int64_t &sblocks
     a.pw /= 2;
     a.n_pb = (int)((n_p + (int64_t)W * a.pw - 1) / ((int64_t)W * a.pw));
   }
+  // one momentum per wave and CUs left over: fewer waves per workgroup
+  while (a.rb > 1 && W > 4 && a.pw == 1 && n_groups * a.n_pb < want_wg) {
+    W /= 2;
+    a.n_pb = (int)((n_p + W - 1) / W);
+  }
   if (a.n_rows * a.n_pb > ((int64_t)1 << 31) - 1) return fail(FRG_E_INVAL, "tabulated problem too large");
   lds_rows_out = lds_rows;
   W_out = W;
@@ -793,7 +805,7 @@ int Ctx::tab_launch(TabArgs a, int reg, hipStream_t st) {
   bool lds_rows = false;
   int W = 1;
   int64_t sblocks = 0;
-  int rc = tab_config(a, lds_rows, W, sblocks, true);
+  int rc = tab_config(a, lds_rows, W, sblocks, false);
   if (rc) return rc;
   // knob tab_seg: 1 always, 2 (auto) when the table is larger than the
   // chip's memory-side cache: smaller tables are served from that cache and

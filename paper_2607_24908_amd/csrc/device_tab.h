@@ -65,6 +65,25 @@ struct PairRow {
   __device__ __forceinline__ double2 fetch(int k) const { return p[k]; }
 };
 
+// Pair rows of RB rows side by side: the pairs of node k of all rows from p[k S],
+// one more of padding where RB > 1 (S odd, so that neighbouring nodes start on
+// different LDS banks).  One address per node and constant offsets per row.
+template <int RB>
+struct PairRowSide {
+  static constexpr int S = RB > 1 ? RB + 1 : 1;
+  const double2 *p;
+  __device__ __forceinline__ double operator()(double t, double t_last, int) const {
+    t = fmin(t, t_last);
+    const double2 gd = p[(int)t * S];
+    return __builtin_fma(__builtin_amdgcn_fract(t), gd.y, gd.x);
+  }
+  __device__ __forceinline__ void locate(double t, int, int &k, double &f) const {
+    k = (int)t;
+    f = __builtin_amdgcn_fract(t);
+  }
+  __device__ __forceinline__ double2 fetch(int k) const { return p[k * S]; }
+};
+
 // Pair k of a staged row: g_k and g_{k+1} - g_k, the last node
 // (g_{n_s-2} + (g_{n_s-1} - g_{n_s-2}), 0); g is the row's plain values.
 __device__ __forceinline__ double2 row_pair(const double *g, int k, int n_s) {
@@ -98,7 +117,7 @@ __device__ __forceinline__ void tab_block_rows(const TabArgs &a, const Row *rows
   const int n_a = a.n_a;
   const int k_last = (int)a.n_s - 2;
   const int rho = lane & (a.R - 1);
-  const int iota = lane / a.R;
+  const int iota = lane >> __builtin_ctz(a.R);
   // this lane's angular nodes j = iota + J u (padded ones get mu = 0)
   double ro[UR > 0 ? UR : 1], rm[UR > 0 ? UR : 1];
   if (UR > 0) {
@@ -111,9 +130,12 @@ __device__ __forceinline__ void tab_block_rows(const TabArgs &a, const Row *rows
     }
   }
   const int64_t p0 = (pb * W + wave) * a.pw;
-  double res[RB];
-#pragma unroll
-  for (int r = 0; r < RB; ++r) res[r] = 0.0;
+  // the lanes of group r hold row r's results, lane e of it that of momentum e
+  // (all rows folded at once: 64 rows of 4096 nodes, 1024 momenta: 89 us with a
+  // sum over the wave per row, 82 so)
+  constexpr int G = kWave / RB;
+  const int row = lane / G, el = lane & (G - 1);
+  double res = 0.0;
   for (int e = 0; e < a.pw; ++e) {
     const int64_t ia = p0 + e;
     if (ia >= a.n_p) break;  // wave-uniform
@@ -167,18 +189,13 @@ __device__ __forceinline__ void tab_block_rows(const TabArgs &a, const Row *rows
         for (int r = 0; r < RB; ++r) total_l[r] = __builtin_fma(A[r], inner[r], total_l[r]);
       }
     }
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      const double v = a.pref * wave_sum(total_l[r]);
-      if (lane == e) res[r] = p >= 0.0 ? v : __builtin_nan("");
-    }
+    const double v = a.pref * wave_sum_fold<RB>(total_l, lane);
+    if (el == (e & (G - 1))) res = p >= 0.0 ? v : __builtin_nan("");
     if (!(p >= 0.0) && lane == 0) *a.flag = 1;
-  }
-  const int64_t ia = p0 + lane;
-  if (lane < a.pw && ia < a.n_p) {
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-      if (r < nrb) a.out[ia * a.os_p + (r0 + r) * a.os_r] = res[r];
+    if ((e & (G - 1)) == G - 1 || e == a.pw - 1 || ia == a.n_p - 1) {  // wave-uniform
+      const int64_t io = ia - (e & (G - 1)) + el;
+      if (el <= (e & (G - 1)) && row < nrb) a.out[io * a.os_p + (r0 + row) * a.os_r] = res;
+    }
   }
 }
 

@@ -227,7 +227,7 @@ struct Context {
   // n_pb of a): rows in LDS or streamed, waves per workgroup, streaming grid.
   // launch shape of the tabulated diagram; several rows per workgroup only
   // where the caller's kernel takes them
-  int tab_config(frg::TabArgs &a, bool &lds_rows, int &W, int64_t &sblocks, bool multi_rows);
+  int tab_config(frg::TabArgs &a, bool &lds_rows, int &W, int64_t &sblocks, bool flows);
   int tab_launch(frg::TabArgs a, int reg, hipStream_t st);
   // pflow_api.cpp: momentum-dependent flow; dsdt != nullptr: one right-hand side
   // at t_rhs, else RK4 from 0 to t_end (all arrays on the device)

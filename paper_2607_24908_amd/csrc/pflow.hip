@@ -157,42 +157,63 @@ __global__ __launch_bounds__(256) void pflow_stage_kernel(PflowArgs a) {
 // communication between workgroups.  Same arithmetic, in the same order, as
 // pflow_stage_kernel + prep_row + tab_kernel: the same bits.
 
-// State of stage m at node i of row r (the previous stage's update): the
-// state itself for the first launch; for a flow that has stopped, its
-// step-start state (carried into the new step-start buffer after stage 3).
-__device__ __forceinline__ double pull_state(const PflowPull &a, int64_t r, int64_t i, bool alive,
-                                             double l3, double c4, bool writer) {
-  const int64_t e = r * a.n_s + i;
-  if (a.prev < 0) return a.y0p[e];
+// Node e of a flow before the previous stage's update, loaded before it is known
+// whether the flow is alive (so that all loads are in flight together).
+struct PullNode {
+  double y0, J, acc;
+};
+__device__ __forceinline__ PullNode pull_load(const PflowPull &a, int64_t e) {
+  PullNode n;
+  n.y0 = a.y0p[e];
+  n.J = a.prev >= 0 ? a.Jp[e] : 0.0;
+  n.acc = a.prev >= 1 && a.prev <= 3 ? a.accp[e] : 0.0;
+  return n;
+}
+
+// State of stage m at node e (the previous stage's update): the state itself for
+// the first launch; for a flow that has stopped, its step-start state (carried
+// into the new step-start buffer after stage 3).
+__device__ __forceinline__ double pull_state(const PflowPull &a, const PullNode &n, int64_t e,
+                                             bool alive, double l3, double c4, bool writer) {
+  if (a.prev < 0) return n.y0;
   if (!alive) {
-    const double y = a.y0p[e];
-    if (a.prev == 3 && writer) a.y0n[e] = y;
-    return y;
+    if (a.prev == 3 && writer) a.y0n[e] = n.y0;
+    return n.y0;
   }
-  const double rhs = l3 * l3 * a.Jp[e] - c4;
+  const double rhs = l3 * l3 * n.J - c4;
   switch (a.prev) {
     case 0:
       if (writer) a.accn[e] = rhs;
-      return a.y0p[e] + (0.5 * a.h) * rhs;
+      return n.y0 + (0.5 * a.h) * rhs;
     case 1:
-      if (writer) a.accn[e] = a.accp[e] + 2.0 * rhs;
-      return a.y0p[e] + (0.5 * a.h) * rhs;
+      if (writer) a.accn[e] = n.acc + 2.0 * rhs;
+      return n.y0 + (0.5 * a.h) * rhs;
     case 2:
-      if (writer) a.accn[e] = a.accp[e] + 2.0 * rhs;
-      return a.y0p[e] + a.h * rhs;
+      if (writer) a.accn[e] = n.acc + 2.0 * rhs;
+      return n.y0 + a.h * rhs;
     default: {
-      const double y = a.y0p[e] + (a.h / 6.0) * (a.accp[e] + rhs);
+      const double y = n.y0 + (a.h / 6.0) * (n.acc + rhs);
       if (writer) a.y0n[e] = y;
       return y;
     }
   }
 }
 
+// Bound by the diagram's instructions and LDS reads (RB = 4: 28 for the
+// coordinates and 4 addresses of four terms, 36 for the rows, 16 reads of 16
+// bytes), after a start of about 6 us per launch (code, loads, exponentials,
+// quotients, three barriers).  The rows of a workgroup are updated side by side,
+// each by its share of the waves, and lie side by side in LDS, so that a node has
+// one address.  64 flows of 256 nodes, 128 x 32 nodes: 18.1 us per stage with
+// four flows per workgroup; with two, their rows one after the other and one
+// address per row and term 23.7 us.  2 flows: 8.8 us (15.9 with all their
+// momenta on 16 workgroups of 16 waves).
+//
 // t: the diagram at scale a.k (t.tab = the table at k = 1, t.out = a.Jn,
 // J[r * n_s + a]).  RB flows (rows) per workgroup, flows rg RB .. rg RB +
 // nrb - 1: each flow's update and row as for one flow; the diagram of the
 // rows shares every coordinate (tab_block_rows: each row's sums as alone).
-// LDS: tab_lds's layout for RB rows, then (pairs) the rows as plain values.
+// LDS: tab_lds's layout for RB rows (pairs: side by side, PairRowSide).
 template <int REG, int UR, bool PAIRS, int RB>
 __global__ __launch_bounds__(RB > 1 ? 1024 : 256) void pflow_pull_kernel(TabArgs t, PflowPull a) {
   extern __shared__ double lds[];
@@ -207,82 +228,109 @@ __global__ __launch_bounds__(RB > 1 ? 1024 : 256) void pflow_pull_kernel(TabArgs
   const int nrb = (int)min<int64_t>(RB, a.n_rows - r0);
   const bool writer = pb == 0;
   const TabLds l = tab_lds(t, lds, RB);
-  const int len = PAIRS ? 2 * n_s : n_s;  // doubles of one staged row
-  // the rows as plain values: after the pair rows, or the staged rows
-  double *lv0 = PAIRS ? l.lg + RB * len : l.lg;
+  using Row = typename std::conditional<PAIRS, PairRowSide<RB>, PlainRow>::type;
+  constexpr int S = PairRowSide<RB>::S;
+  double2 *lp = reinterpret_cast<double2 *>(l.lg);
+  // node i of row rr: its value, or that of its pair
+  auto node = [&](int rr, int i) -> double & {
+    if constexpr (PAIRS)
+      return lp[i * S + rr].x;
+    else
+      return l.lg[rr * n_s + i];
+  };
   const double inv_k2 = 1.0 / a.k2;
-  for (int rr = 0; rr < nrb; ++rr) {
+  // each row by its own share of the threads (whole waves; the rows one after
+  // another with fewer waves than rows): update of the previous stage and the
+  // row of this one
+  __shared__ int lbad[4];  // 16 bytes: the pairs behind it in LDS are read 16 at a time
+  if (threadIdx.x < RB) lbad[threadIdx.x] = 0;
+  __syncthreads();
+  const int share = W >= RB ? W / RB * kWave : (int)blockDim.x;  // threads per row
+  const int grp = threadIdx.x / share, in_grp = threadIdx.x - grp * share;
+  const int groups = W >= RB ? RB : 1;
+  for (int rr = grp; rr < nrb && grp < groups; rr += groups) {
     const int64_t r = r0 + rr;
-    double *lv = lv0 + rr * n_s;
-    // update of the previous stage and the row of this one
-    const bool alive = a.alivep[r] != 0;  // workgroup-uniform
-    double l3 = 0.0, c4 = 0.0;
-    if (alive && a.prev >= 0) {
-      l3 = a.lam3[r];
-      c4 = 0.5 * a.lam4[r] * a.Tp[r];
-    }
+    const bool alive = a.alivep[r] != 0;  // wave-uniform
+    const double l3 = a.lam3[r];
+    const double c4 = a.prev >= 0 ? 0.5 * a.lam4[r] * a.Tp[r] : 0.0;
     bool bad = false;
-    for (int i = threadIdx.x; i < n_s; i += blockDim.x) {
-      const double y = pull_state(a, r, i, alive, l3, c4, writer);
+    for (int i = in_grp; i < n_s; i += share) {
+      const int64_t e = r * a.n_s + i;
+      const PullNode n = pull_load(a, e);
       const double s = (double)i * a.h_s;
-      const double den = (hk<REG>(s, a.k2, inv_k2) + a.k2) + y;
+      const double base = hk<REG>(s, a.k2, inv_k2) + a.k2;
+      const double den = base + pull_state(a, n, e, alive, l3, c4, writer);
       const bool ok = den > 0.0;
       bad |= !ok;
-      lv[i] = (alive && ok) ? 1.0 / den : 0.0;
+      node(rr, i) = (alive && ok) ? 1.0 / den : 0.0;
     }
-    bad = __syncthreads_or(bad) && alive;
-    if (bad) {
-      // the flow ends at the start of this step with its state kept
-      for (int i = threadIdx.x; i < n_s; i += blockDim.x) lv[i] = 0.0;
-      if (writer && threadIdx.x == 0) {
-        a.t_reached[r] = a.t_n;
-        *a.flag = 1;
-      }
-      __syncthreads();
-    }
-    if (writer && threadIdx.x == 0) a.aliven[r] = alive && !bad;
-    // the diagram's row as tab_rows_block stages it
-    if constexpr (PAIRS) {
-      double2 *lp = reinterpret_cast<double2 *>(l.lg) + rr * n_s;
-      for (int k = threadIdx.x; k < n_s; k += blockDim.x) lp[k] = row_pair(lv, k, n_s);
-    }
+    if (bad && alive) lbad[rr] = 1;
   }
   __syncthreads();
-  using Row = typename std::conditional<PAIRS, PairRow, PlainRow>::type;
-  const double2 *lp = reinterpret_cast<const double2 *>(l.lg);
+  bool any_bad = false;
+  for (int rr = 0; rr < nrb; ++rr) any_bad |= lbad[rr] != 0;
+  if (any_bad) {  // workgroup-uniform
+    // such a flow ends at the start of this step with its state kept
+    for (int rr = 0; rr < nrb; ++rr) {
+      if (!lbad[rr]) continue;
+      for (int i = threadIdx.x; i < n_s; i += blockDim.x) node(rr, i) = 0.0;
+      if (writer && threadIdx.x == 0) {
+        a.t_reached[r0 + rr] = a.t_n;
+        *a.flag = 1;
+      }
+    }
+    __syncthreads();
+  }
+  if (writer && threadIdx.x < nrb)
+    a.aliven[r0 + threadIdx.x] = a.alivep[r0 + threadIdx.x] != 0 && !lbad[threadIdx.x];
+  // the slopes of the pairs (row_pair's values; the thread of node n_s - 2 also
+  // forms the last pair, whose value its own slope needs first)
+  if constexpr (PAIRS) {
+    for (int rr = grp; rr < nrb && grp < groups; rr += groups)
+      for (int k = in_grp; k < n_s - 1; k += share) {
+        const double g0 = lp[k * S + rr].x, slope = lp[(k + 1) * S + rr].x - g0;
+        lp[k * S + rr].y = slope;
+        if (k == n_s - 2) lp[(k + 1) * S + rr] = make_double2(__builtin_fma(1.0, slope, g0), 0.0);
+      }
+    __syncthreads();
+  }
   Row rows[RB];
 #pragma unroll
   for (int rr = 0; rr < RB; ++rr) {
-    const int rs = rr < nrb ? rr : nrb - 1;
+    // (pairs: rows past the batch read what lies there and are not stored)
     if constexpr (PAIRS)
-      rows[rr] = PairRow{lp + rs * n_s};
+      rows[rr] = Row{lp + rr};
     else
-      rows[rr] = PlainRow{l.lg + rs * n_s};
+      rows[rr] = Row{l.lg + (rr < nrb ? rr : nrb - 1) * n_s};
   }
-  // q_i and A_i of each row at scale k
-  for (int x = threadIdx.x; x < nrb * n_r; x += blockDim.x) {
-    const int rr = x / n_r, i = x - rr * n_r;
-    const double q = a.k * a.base[i];
-    double G;
+  auto row_of = [&](int rr) {
     if constexpr (PAIRS)
-      G = PairRow{lp + rr * n_s}((q * q) * t.inv_h, t.t_last, n_s - 2);
+      return Row{lp + rr};
     else
-      G = PlainRow{l.lg + rr * n_s}((q * q) * t.inv_h, t.t_last, n_s - 2);
-    if (rr == 0) l.lrad[i * (1 + RB)] = q;
-    l.lrad[i * (1 + RB) + 1 + rr] = ((a.kd2 * a.base[n_r + i]) * G) * G;
+      return Row{l.lg + rr * n_s};
+  };
+  // q_i and A_i of each row at scale k
+  for (int rr = grp; rr < nrb && grp < groups; rr += groups) {
+    const Row row = row_of(rr);
+    for (int i = in_grp; i < n_r; i += share) {
+      const double q = a.k * a.base[i], c = a.kd2 * a.base[n_r + i];
+      const double G = row((q * q) * t.inv_h, t.t_last, n_s - 2);
+      if (rr == 0) l.lrad[i * (1 + RB)] = q;
+      l.lrad[i * (1 + RB) + 1 + rr] = (c * G) * G;
+    }
   }
   __syncthreads();
   tab_block_rows<UR, RB>(t, rows, nrb, l.lrad, l.lo, l.lm, r0, pb, W, wave, lane);
-  // tadpole of this stage of each flow, as prep_row (wave 0 of the storing
-  // workgroup)
-  if (writer && threadIdx.x < kWave) {
-    for (int rr = 0; rr < nrb; ++rr) {
-      const double *lv = lv0 + rr * n_s;
+  // tadpole of this stage of each flow, as prep_row (a wave per flow of the
+  // storing workgroup)
+  if (writer) {
+    for (int rr = wave; rr < nrb; rr += W) {
+      const Row row = row_of(rr);
       double acc = 0.0;
       for (int i = lane; i < n_r; i += kWave) {
         const double q = a.k * a.base[i];
         const double c = a.kd2 * a.base[n_r + i];
-        const double G = interp(lv, (q * q) * a.inv_h, a.t_last, n_s - 2);
+        const double G = row((q * q) * a.inv_h, a.t_last, n_s - 2);
         acc = __builtin_fma((c * G), G, acc);
       }
       acc = wave_sum(acc);
@@ -306,7 +354,7 @@ __global__ __launch_bounds__(256) void pflow_final_kernel(PflowPull a) {
     if (a.prev == 4)
       a.dsdt[r * a.n_s + i] = alive ? l3 * l3 * a.Jp[r * a.n_s + i] - c4 : __builtin_nan("");
     else
-      (void)pull_state(a, r, i, alive, l3, c4, true);
+      (void)pull_state(a, pull_load(a, r * a.n_s + i), r * a.n_s + i, alive, l3, c4, true);
   }
 }
 }  // namespace
@@ -343,7 +391,8 @@ int launch_pflow_stage(const PflowArgs &a, int reg, void *stream) {
 
 int pflow_pull_lds_bytes(const TabArgs &t) {
   const int rb = t.rb > 1 ? t.rb : 1;
-  return tab_lds_bytes(t, true) + (t.pairs ? (int)(sizeof(double) * rb * t.n_s) : 0);
+  // with the padding of the pairs (PairRowSide)
+  return tab_lds_bytes(t, true) + (t.pairs && rb > 1 ? (int)(2 * sizeof(double) * t.n_s) : 0);
 }
 
 // Dynamic LDS beyond 64 KiB (gfx950: 160 KiB per workgroup); a refusal where
