@@ -29,24 +29,39 @@ sys.path.insert(0, ROOT)
 # ALU roofline of the FP64 path.  FP64 rate of MI355X: 78.6 TFLOP/s, i.e.
 # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 3.93e13 FMA/s, the same on the
 # vector units and on the FP64 matrix cores, which share it (a kernel that
-# mixes the two takes the sum of their times).  Floor of the per-evaluation
-# work of the grid kernel: for one radial node and a group of G angular terms
-# of a lane row, c/(Hq + delta)^2 sum_k mu_k/(delta + H_k) = N(delta)/P(delta)
-# with per-momentum polynomial coefficients, so each (term, mass) costs one
+# mixes the two takes the sum of their times).  Floor of the grid's work: for
+# one radial node and a group of angular terms of a lane row,
+# c/(Hq + delta)^2 sum_k mu_k/(delta + H_k) = N(delta)/P(delta) with
+# per-momentum polynomial coefficients, so a (term, mass) costs one
 # multiply-add of P and one of N (power sums over 16-mass tiles on the matrix
-# cores, or nested on the vector units); the two extra powers of the radial
-# factor, the reciprocal of P, its Newton step and the accumulation are
-# shared by the G = 32 terms of a group and the coefficient build by every
-# mass of the momentum, and are left out of the floor: 2 FMAs per eval.
+# cores, or nested on the vector units); with many masses the diagram is
+# evaluated at 32 nodes per panel (a factor of 16 in delta) that holds a mass
+# and interpolated, 32 multiply-adds per integral, so only the nodes cost 2
+# FMAs per term.  The extra powers of the radial factor, the reciprocals, the
+# regulator and the coefficient build are left out of the floor.
 VALU_LANE_CYCLES = 256 * 4 * 16 * 2.4e9
-# HBM bytes per grid-kernel launch from rocprofv3 FETCH_SIZE / WRITE_SIZE,
-# scaled by a 1 GiB device copy read the same way (fetch x2.00, write x1.00):
-# 461.0 KiB x 2.00 + 16384 KiB x 1.00.
-TRAFFIC = 461.0 * 1024 * 2.00 + 16384 * 1024 * 1.00
-CYCLES_PER_EVAL_FLOOR = 2
-PEAK_EVALS = VALU_LANE_CYCLES / CYCLES_PER_EVAL_FLOOR
-TRAFFIC_SOURCE = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of grid_coef_kernel on this workload "
+MASS_NODES = 32
+# HBM bytes per step from rocprofv3 FETCH_SIZE / WRITE_SIZE of the node and the
+# interpolation kernel, scaled by a 1 GiB device copy read the same way (fetch
+# x2.00, write x1.00): (338 + 5726) KiB x 2.00 + (2176 + 16384) KiB x 1.00.
+TRAFFIC = (338.3 + 5726.0) * 1024 * 2.00 + (2176 + 16384) * 1024 * 1.00
+TRAFFIC_SOURCE = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of grid_nodes_kernel and "
+                  "mass_interp_kernel on this workload "
                   "(profiles/grid_kernel_scaleup_d3_hbm_traffic.md), not measured in this run")
+
+
+def fmas_per_eval(m2, k, n_terms):
+    """FMAs per (term, mass): 2 at every mass, or 2 at the panels' nodes and 32 per
+    integral where that is the form the library takes (many masses)."""
+    k2 = k * k
+    sig = 2.0 ** (1 - np.frexp(k2)[1])
+    panels = np.unique(np.floor(np.log2(sig * (np.asarray(m2) + k2)) / 4.0)).size
+    nodes = MASS_NODES * panels
+    if m2.size < 128 or 2 * nodes > m2.size:
+        return 2.0
+    return 2.0 * nodes / m2.size + MASS_NODES / n_terms
+
+
 # Point-list (uneven sets) roofline: the algorithmic FP64 vector work of one
 # evaluation with the regulator evaluated per term, taken at the middle of the
 # estimated ranges -- exponential: one expm1-class transcendental, one
@@ -299,6 +314,8 @@ def main():
     evals_s = w.n_evals / (ms_step * 1e-3)
     kernel_s = gpu_ms * 1e-3
     achieved = w.n_evals / kernel_s / 1e9
+    fmas = fmas_per_eval(w.m2, q.k, q.n_r * q.n_a)
+    peak = VALU_LANE_CYCLES / fmas
     line = {
         "metric": "integrand evals/s (FP64, plain scale-up d=3 grid)",
         "value": evals_s,
@@ -317,13 +334,15 @@ def main():
                    "n_angular": q.n_a, "evals_per_step": int(w.n_evals),
                    "integrals_per_step": int(w.n_integrals), "entry": "frg_integrate_grid"},
         "integrals_per_s": w.n_integrals / (ms_step * 1e-3),
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_EVALS / 1e9,
-                     "unit": "Geval/s", "frac": achieved * 1e9 / PEAK_EVALS, "traffic": TRAFFIC,
-                     "kernel": "grid_coef_kernel<exp> (16-mass tiles, FP64 matrix cores)",
+        "roofline": {"bound": "alu", "achieved": achieved, "peak": peak / 1e9,
+                     "unit": "Geval/s", "frac": achieved * 1e9 / peak, "traffic": TRAFFIC,
+                     "kernel": "grid_nodes_kernel<exp> (mass nodes, FP64 matrix cores) and "
+                               "mass_interp_kernel",
                      "kernel_ms": gpu_ms,
                      "evals_per_launch": int(w.n_evals), "traffic_unit": "bytes per launch",
                      "traffic_source": TRAFFIC_SOURCE,
-                     "peak_basis": "FP64 3.93e13 FMA/s (vector or matrix) / 2 FMAs per eval"},
+                     "peak_basis": f"FP64 3.93e13 FMA/s (vector or matrix) / {fmas:.4f} FMAs per "
+                                   "eval (2 per term at the mass nodes, 32 per integral)"},
     }
     checks = {}
     if not args.no_secondary:
@@ -537,8 +556,8 @@ def secondary(ctx, frg, workloads, torch, checks):
 
 def vertex(ctx, frg, workloads, torch, reps=20):
     """Two-external-momentum diagram: 256 configurations x 512 masses, 48 x 8
-    x 16 rule (coefficient form over the azimuthal nodes); the same 2-FMA
-    floor per (term, mass) as the scale-up grid."""
+    x 16 rule (coefficient form over the azimuthal nodes); the same floor of
+    FMAs per (term, mass) as the scale-up grid."""
     w = workloads.vertex_d3()
     q = w.quad
     quad = frg.make_quad(q.d, q.reg, q.k, q.q_max, q.n_r, q.n_a)
@@ -548,7 +567,8 @@ def vertex(ctx, frg, workloads, torch, reps=20):
     log(f"vertex {w.name}: {t * 1e3:.3f} ms, {w.n_evals / t:.3e} evals/s")
     return {"workload": w.name, "ms_per_call": t * 1e3, "evals_per_s": w.n_evals / t,
             "integrals_per_s": w.n_integrals / t,
-            "frac_of_2op_floor": w.n_evals / t / PEAK_EVALS}
+            "frac_of_fma_floor": w.n_evals / t * fmas_per_eval(w.m2, q.k, q.n_r * q.n_a * w.n_phi)
+            / VALU_LANE_CYCLES}
 
 
 def fv_lpa(ctx, frg, workloads, torch, reps=3):

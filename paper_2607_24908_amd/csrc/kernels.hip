@@ -930,16 +930,17 @@ int launch_lpa_args(const LpaJob *jobs, int n_jobs, int64_t blocks, const LpaDon
     a.first[i] = i < n_jobs ? jobs[i].block : INT_MAX;
     a.job[i] = i < n_jobs ? jobs[i] : LpaJob{};
   }
-  hipLaunchKernelGGL(done.word ? lpa_args_kernel<true> : lpa_args_kernel<false>, dim3((unsigned)blocks), dim3(kLpaBlock), 0,
-                     (hipStream_t)stream, a, done);
+  hipLaunchKernelGGL(done.word ? lpa_args_kernel<true> : lpa_args_kernel<false>,
+                     dim3((unsigned)blocks), dim3(kLpaBlock), 0, (hipStream_t)stream, a, done);
   return (int)hipGetLastError();
 }
 
 int launch_lpa_table(const LpaJob *d_jobs, int n_jobs, int64_t blocks, const LpaDone &done,
                      void *stream) {
   if (blocks <= 0) return 0;
-  hipLaunchKernelGGL(done.word ? lpa_table_kernel<true> : lpa_table_kernel<false>, dim3((unsigned)blocks), dim3(kLpaBlock), 0,
-                     (hipStream_t)stream, d_jobs, n_jobs, done);
+  hipLaunchKernelGGL(done.word ? lpa_table_kernel<true> : lpa_table_kernel<false>,
+                     dim3((unsigned)blocks), dim3(kLpaBlock), 0, (hipStream_t)stream, d_jobs, n_jobs,
+                     done);
   return (int)hipGetLastError();
 }
 

@@ -331,10 +331,11 @@ void Server::run_flow(Flow *f) {
 }
 
 // Stage the batch's right-hand sides into its buffer and enqueue it on the
-// buffer's stream: the layout is jobs (of more flows than a launch takes
-// as arguments) | U of each flow | flags | outputs of each flow (dU/dt, then the 7 bands when asked); [0, o_out)
-// goes up and [o_flags, end) comes back (copy mode), or the kernel reads and
-// writes the pinned buffer in place (zero copy).  Records the buffer's event.
+// buffer's stream.  Layout: jobs (of more flows than a launch takes as
+// arguments) | U of each flow | flags | outputs of each flow (dU/dt, then the 7
+// bands when asked); [0, o_out) goes up and [o_flags, end) comes back (copy
+// mode, then the buffer's event), or the kernel reads and writes the pinned
+// buffer in place and sets its word (zero copy).
 void Server::launch_batch(Batch &b, Stage &g) {
   TraceRange trace_("frg_server_batch");  // staging and enqueueing one launch
   auto up8 = [](size_t x) { return (x + 7) & ~(size_t)7; };
