@@ -196,19 +196,23 @@ int Ctx::lpa_table(int d, int reg, int n_r, double qmk, const double **dev, doub
 
 int Ctx::fv_panels(int d, int reg, int n_r, double qmk, const double **dev) {
   LEntry &ent = ltabs.at(std::make_tuple(d, reg, n_r, dbits(qmk)));
-  if (!ent.panels) {
-    auto buf = std::make_unique<DevBuf>(&hbm);
-    if (buf->reserve(sizeof(double) * kFvPanels * kFvPoly) != FRG_OK) {  // no room in the budget
-      clear_error();
+  if (!ent.panels_asked) {
+    const size_t bytes = sizeof(double) * kFvPanels * kFvPoly;
+    if (!hbm.spare(bytes)) {  // decided once: the rule's results keep their bits
+      ent.panels_asked = true;
       *dev = nullptr;
       return FRG_OK;
     }
+    auto buf = std::make_unique<DevBuf>(&hbm);
+    int rc = buf->reserve(bytes);
+    if (rc) return rc;
     const std::vector<double> t = build_fv_panels(ent.host);
-    hipError_t e = hipMemcpy(buf->ptr, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice);
+    hipError_t e = hipMemcpy(buf->ptr, t.data(), bytes, hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "upload radial-sum panels");
     ent.panels = std::move(buf);
+    ent.panels_asked = true;
   }
-  *dev = (const double *)ent.panels->ptr;
+  *dev = ent.panels ? (const double *)ent.panels->ptr : nullptr;
   return FRG_OK;
 }
 
@@ -664,7 +668,7 @@ int Ctx::mass_nodes_launch(const GridArgs &g_in, int reg, bool vertex, bool big_
   const size_t node_bytes = sizeof(double) * (node_doubles + reg_doubles);
   size_t more = mass_nodes.bytes ? 0 : node_bytes;
   if (mass_scr.bytes < bytes) more += bytes - mass_scr.bytes;
-  if (hbm.used.load() + more > hbm.budget) return 0;
+  if (!hbm.spare(more)) return 0;
   if (!mass_done && hipEventCreateWithFlags(&mass_done, hipEventDisableTiming) != hipSuccess) {
     mass_done = nullptr;
     return fail(FRG_E_DEVICE, "hipEventCreate");

@@ -44,6 +44,12 @@ bool any_fp32c(const std::vector<SetDev> &sd);
 struct HbmAccount {
   std::atomic<uint64_t> used{0};
   uint64_t budget = ~0ull;
+  // Whether b more bytes, for a faster form of a call that has another one, take
+  // at most a 64th of what is free: so that no later call is refused for them.
+  bool spare(uint64_t b) const {
+    const uint64_t u = used.load();
+    return b == 0 || (u < budget && b <= (budget - u) / 64);
+  }
 };
 
 // Grow-only device allocation, charged to an account when it has one.
@@ -189,6 +195,7 @@ struct Context {
     double Cd = 0.0;
     frg::LpaTable host;
     std::unique_ptr<frg::DevBuf> panels;  // build_fv_panels, from the first call that asks
+    bool panels_asked = false;            // ... null then: the budget could not spare them
   };
   std::map<std::tuple<int, int, uint64_t, uint64_t, int, int>, QEntry> qtabs;
   std::map<std::tuple<int, int, int, uint64_t>, LEntry> ltabs;
@@ -202,7 +209,7 @@ struct Context {
                  frg::QuadTable **host_ref = nullptr);
   int lpa_table(int d, int reg, int n_r, double qmk, const double **dev, double *Cd);
   // polynomial panels of the radial sums for a table lpa_table has made; null where
-  // the memory budget has no room for them
+  // the memory budget cannot spare them
   int fv_panels(int d, int reg, int n_r, double qmk, const double **dev);
   int make_setdev(const frg_set &s, frg::SetDev *out);
   void fill_setdev(const frg_set &s, const frg::QuadTable &h, const double *tab, frg::SetDev *out);

@@ -67,3 +67,56 @@ def test_panels_and_wave_edges(n, N):
     finally:
         torch.cuda.synchronize()
         frg.frg_destroy(ctx)
+
+
+def test_budget_that_cannot_spare_the_panels():
+    """A context of 1 MiB keeps to the sums of the radial nodes: within rounding of
+    one with panels, right-hand sides and solves (fused and by launches the same
+    bits), and a flow whose footprint the budget just holds is still served."""
+    print("[case] fvlpa and lpa without panels", flush=True)
+    n, N = 127, 4
+    u = states(n)[1:3]
+    fv = frg.make_fvlpa(D, N, frg.FRG_REG_EXP, N_R, 1.0, 6.0, n, SMAX)
+    lpa = frg.make_lpa(d=3, N=2, n_grid=200)
+    U0 = 1.5 * (np.arange(200) * (0.5 / 199) - 0.02) ** 2
+    res = []
+    for budget in (0, 1 << 20):
+        ctx = frg.frg_create(0, budget)
+        try:
+            U = torch.tensor(u, dtype=torch.float64, device="cuda")
+            out, dt = torch.empty_like(U), torch.empty(2, dtype=torch.float64, device="cuda")
+            frg.frg_fvlpa_rhs(ctx, fv, 0.0, U, out, dt)
+            sol = []
+            for fused in (1, 0):
+                frg.frg_tune_set(ctx, "fv_persistent", fused)
+                V, tr = U.clone(), torch.empty(2, dtype=torch.float64, device="cuda")
+                frg.frg_fvlpa_solve(ctx, fv, -1e-6, 5, V, tr)
+                sol.append(V)
+            L = torch.tensor(U0, dtype=torch.float64, device="cuda")
+            dL, J = torch.empty_like(L), torch.empty(7 * 200, dtype=torch.float64, device="cuda")
+            frg.frg_flow_rhs(ctx, lpa, -0.1, L, dL, J)
+            torch.cuda.synchronize()
+            assert torch.equal(sol[0], sol[1])
+            res.append([x.cpu().numpy() for x in (out, dt, sol[0], dL, J)])
+        finally:
+            torch.cuda.synchronize()
+            frg.frg_destroy(ctx)
+    for a, b in zip(*res):  # the second flow is outside its domain: NaN rates
+        ok = np.isfinite(a)
+        assert ok.any() and np.array_equal(ok, np.isfinite(b))
+        assert np.abs(a - b)[ok].max() <= 1e-12 * np.abs(a[ok]).max()
+    big = frg.make_lpa(d=3, N=2, n_grid=1024)
+    table = 4096  # the radial table of 64 nodes
+    ctx = frg.frg_create(0, frg.frg_flow_footprint(big) + table)
+    try:
+        small = frg.make_lpa(d=3, N=2, n_grid=64)
+        L = torch.zeros(64, dtype=torch.float64, device="cuda")
+        frg.frg_flow_rhs(ctx, small, 0.0, L, torch.empty_like(L))
+        torch.cuda.synchronize()
+        out = np.zeros(1024)
+        t = frg.frg_submit(ctx, frg.make_request(big, 6.0, 0.05, -0.05, 1e-6, 1e-9, out))
+        while frg.frg_poll(ctx, t)[0] == frg.FRG_PENDING:
+            pass
+        assert np.isfinite(out).all() and (out != 0.0).any()
+    finally:
+        frg.frg_destroy(ctx)
