@@ -1,7 +1,7 @@
 // Radial sums of the local-potential flows on gfx950 from polynomial panels:
 //   s1(x) = sum_i chat_i/(hhat_i + x),  s2(x) = sum_i chat_i/(hhat_i + x)^2
-// at x = (m^2 + k^2)/k^2 for 2^kFvLo <= x < 2^kFvHi (build_fv_panels; the table
-// in LDS or global memory): s1 and its derivative by one Horner pass over 11
+// at x = (m^2 + k^2)/k^2 for 2^kPanelLo <= x < 2^kPanelHi (build_fv_panels; the
+// table, or a part of it, in LDS or global memory): s1 and its derivative by one Horner pass over 11
 // coefficients, within 2.2e-16 and 3.3e-16.  20 FMAs; the 64 nodes of the usual
 // table take 64 reciprocals term by term, or 232 FMAs and 8 reciprocals as
 // rational groups.
@@ -14,12 +14,13 @@
 namespace frg {
 namespace dev {
 
-// Panel of x; as an unsigned number below kFvPanels exactly for x in their range
-// (not for x <= 0, infinities and NaN).
+// Panel of x, counted from that at 2^LO; as an unsigned number below the number of
+// panels exactly for x in their range (not for x <= 0, infinities and NaN).
+template <int LO>
 __device__ __forceinline__ int fv_panel(double x) {
   static_assert(kFvPerOctave == 16, "four mantissa bits select the panel");
   const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32);
-  int p = (int)(hi >> 16) - ((1023 + kFvLo) << 4);
+  int p = (int)(hi >> 16) - ((1023 + LO) << 4);
   asm("" : "+v"(p));  // the address is p times the panel's size, not a folded base below zero
   return p;
 }

@@ -58,12 +58,17 @@ inline int fv_groups(int n_r) { return (n_r + kFvGroup - 1) / kFvGroup; }
 LpaTable build_lpa_table(int d, int reg, int n_r, double q_max_over_k);
 // Polynomial panels of the two radial sums of the finite-volume flux,
 //   s1(x) = sum_i c_i/(h_i + x),  s2(x) = sum_i c_i/(h_i + x)^2 = -s1'(x):
-// kFvPerOctave panels per octave of x from 2^kFvLo to 2^kFvHi, s1 as
-// kFvPoly coefficients of ascending powers of x - (middle of the panel), and
-// s2 as minus their derivative.
-constexpr int kFvLo = -14, kFvHi = 22;
+// kFvPerOctave panels per octave of x from 2^kPanelLo to 2^kPanelHi (84 KB: a flow to
+// t = -9 takes x to 1e9, one that ends at its pole towards 0), s1 as kFvPoly
+// coefficients of ascending powers of x - (middle of the panel), and s2 as minus
+// their derivative.  The finite-volume solve copies those from 2^kFvLo to 2^kFvHi
+// into LDS (51 KB: two workgroups per CU).
 constexpr int kFvPerOctave = 16;
+constexpr int kPanelLo = -26, kPanelHi = 34;
+constexpr int kPanels = (kPanelHi - kPanelLo) * kFvPerOctave;
+constexpr int kFvLo = -14, kFvHi = 22;
 constexpr int kFvPanels = (kFvHi - kFvLo) * kFvPerOctave;
+constexpr int kFvFirst = (kFvLo - kPanelLo) * kFvPerOctave;  // panel 2^kFvLo of the table
 constexpr int kFvPoly = 11;
 std::vector<double> build_fv_panels(const LpaTable &t);
 

@@ -170,7 +170,7 @@ __device__ __forceinline__ FvOut fv_iface(const FvArgs &a, const FvScale &sc, co
 #pragma unroll
   for (int m = 0; m < M; ++m) {
     x[m] = delta[m] * sc.inv_k2;
-    p[m] = fv_panel(x[m]);
+    p[m] = fv_panel<kFvLo>(x[m]);
     near &= (unsigned)p[m] < (unsigned)a.n_panels;
   }
   FvOut o;
@@ -182,7 +182,7 @@ __device__ __forceinline__ FvOut fv_iface(const FvArgs &a, const FvScale &sc, co
     for (int m = 0; m < M; ++m) {
       const bool bad = !((m == 0 ? delta[0] : (m == 1 ? delta[M / 2] : delta[M - 1])) > 0.0);
       const double xm = bad ? 1.0 : (m == 0 ? x[0] : (m == 1 ? x[M / 2] : x[M - 1]));
-      const int pm = fv_panel(xm);
+      const int pm = fv_panel<kFvLo>(xm);
       o.bad |= bad;
       FvSums s;
       if ((unsigned)pm < (unsigned)a.n_panels)

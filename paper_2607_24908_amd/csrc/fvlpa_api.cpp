@@ -49,7 +49,7 @@ int Ctx::fvlpa_device(const frg_fvlpa &f, int64_t n, double t_end, int64_t n_ste
   double *d = (double *)buf;
   FvArgs a{};
   a.tab = tab;
-  a.poly = poly;
+  a.poly = poly ? poly + kFvFirst * kFvPoly : nullptr;
   a.n_panels = poly ? kFvPanels : 0;
   a.Q = d;
   d += nq;

@@ -613,9 +613,9 @@ __device__ __forceinline__ void lpa_point(const LpaJob &jb, int j) {
   const bool pion = jb.N > 1;
   const bool ok = ds > 0.0 && (!pion || dp > 0.0);
   const double x[2] = {(ok ? ds : jb.k2) * jb.inv_k2, ((ok && pion) ? dp : jb.k2) * jb.inv_k2};
-  const int p[2] = {fv_panel(x[0]), fv_panel(x[1])};
+  const int p[2] = {fv_panel<kPanelLo>(x[0]), fv_panel<kPanelLo>(x[1])};
   double s1[2], s2[2];
-  if (jb.poly && (unsigned)p[0] < (unsigned)kFvPanels && (unsigned)p[1] < (unsigned)kFvPanels) {
+  if (jb.poly && (unsigned)p[0] < (unsigned)kPanels && (unsigned)p[1] < (unsigned)kPanels) {
     fv_poly<2, true>(jb.poly, x, p, s1, s2);
   } else {
     lpa_sums(jb, x[0], s1[0], s2[0]);

@@ -209,7 +209,7 @@ LpaTable build_lpa_table(int d, int reg, int n_r, double q_max_over_k) {
 // 33^-k), economised: the Chebyshev terms above degree kFvPoly - 1 = 10 are
 // dropped (below 66^-11 = 1e-20 of s1; their derivative below 1e-16 of s2 / 2).
 std::vector<double> build_fv_panels(const LpaTable &t) {
-  constexpr int K = 16, n = kFvPoly;  // Taylor terms, coefficients kept
+  constexpr int K = 14, n = kFvPoly;  // Taylor terms, coefficients kept
   // z^k = sum_j b[k][j] T_j(z); T_j = sum_i a[j][i] z^i
   static const auto econ = [] {
     std::vector<std::vector<long double>> a(K, std::vector<long double>(K, 0.0L)), b = a;
@@ -230,17 +230,23 @@ std::vector<double> build_fv_panels(const LpaTable &t) {
     return m;
   }();
   const int n_r = t.n_r;
-  std::vector<double> out((size_t)kFvPanels * n);
-  for (int p = 0; p < kFvPanels; ++p) {
-    const int e = kFvLo + p / kFvPerOctave, s = p % kFvPerOctave;
+  std::vector<double> out((size_t)kPanels * n);
+  for (int p = 0; p < kPanels; ++p) {
+    const int e = kPanelLo + p / kFvPerOctave, s = p % kFvPerOctave;
     const long double lo = ldexpl((long double)(kFvPerOctave + s) / kFvPerOctave, e);
     const long double w = ldexpl(0.5L / kFvPerOctave, e), c = lo + w;
     long double tk[K] = {};
+    double td[K] = {};  // the terms from 33^-2 on: double is enough
     for (int i = 0; i < n_r; ++i) {
       const long double g = 1.0L / ((long double)t.data[n_r + i] + c), f = -w * g;
-      long double v = (long double)t.data[i] * g;
-      for (int k = 0; k < K; ++k, v *= f) tk[k] += v;
+      const long double v = (long double)t.data[i] * g, v1 = v * f;
+      tk[0] += v;
+      tk[1] += v1;
+      const double fd = (double)f;
+      double vd = (double)v1 * fd;
+      for (int k = 2; k < K; ++k, vd *= fd) td[k] += vd;
     }
+    for (int k = 2; k < K; ++k) tk[k] = td[k];
     long double wi = 1.0L;
     for (int i = 0; i < n; ++i, wi /= w) {
       long double v = 0.0L;

@@ -1,6 +1,7 @@
 """LPA right-hand sides from polynomial panels: grids at the edges of the 64-point
-workgroups, masses inside the panels (2^-14 <= (m^2 + k^2)/k^2 < 2^22) and beyond
-them on both sides, batches at the edge of what a launch takes as arguments."""
+workgroups, masses over the range of the panels (2^-26 <= (m^2 + k^2)/k^2 < 2^34)
+and beyond them on both sides, batches at the edge of what a launch takes as
+arguments."""
 import numpy as np
 import pytest
 
@@ -58,6 +59,35 @@ def test_batches_and_panel_edges(n_flows):
             worst = max(worst, err, ej)
             assert err < 1e-12 and ej < 1e-12
         print(f"  max rel err {worst:.2e}")
+    finally:
+        torch.cuda.synchronize()
+        frg.frg_destroy(ctx)
+
+
+@pytest.mark.parametrize("reg", [frg.FRG_REG_EXP, frg.FRG_REG_LITIM])
+@pytest.mark.parametrize("e", [-32, -27, -26, -25, 32, 33, 34, 40])
+def test_edges_of_the_panels(e, reg):
+    """Both masses of every point at (m^2 + k^2)/k^2 = 2^e (exact differences), N = 1
+    and 4, with the other points of the second flow inside the panels."""
+    print(f"[case] lpa panels 2^{e}", flush=True)
+    ctx = frg.frg_create(0)
+    try:
+        n = 129
+        rho = np.arange(n) * (0.5 / (n - 1))
+        slope = (2.0 ** e - 1.0) * rho
+        mixed = np.where(np.arange(n) < n // 2, slope, slope[n // 2] + 1.5 * (rho - rho[n // 2]))
+        for U, N in ((slope, 1), (slope, 4), (mixed, 4)):
+            want, wj, rc = oracle.lpa_rhs(3, N, reg, 40, 6.0, 1.0, 0.5, U, allow_domain=True)
+            dU, J = torch.empty(n, dtype=torch.float64, device="cuda"), dev(np.empty(7 * n))
+            frg.frg_flow_rhs(ctx, frg.make_lpa(d=3, N=N, reg=reg, n_radial=40, n_grid=n), 0.0,
+                             dev(U), dU, J)
+            frg.frg_stream_status(ctx, allow_domain=True)
+            got, wj = dU.cpu().numpy(), np.asarray(wj).ravel()
+            ok = np.isfinite(want)  # the kink may leave the domain
+            assert np.array_equal(ok, np.isfinite(got)) and ok.any()
+            assert np.abs(got[ok] / want[ok] - 1.0).max() < 1e-12
+            jk = np.isfinite(wj)
+            assert np.abs(J.cpu().numpy()[jk] - wj[jk]).max() <= 1e-12 * np.abs(wj[jk]).max()
     finally:
         torch.cuda.synchronize()
         frg.frg_destroy(ctx)
