@@ -663,15 +663,16 @@ __device__ __forceinline__ void lpa_block(const LpaJob &jb, const LpaDone &done)
 // Jobs in the kernel's arguments (which hold 4 KB, so at most kLpaArgs): no upload
 // before the launch and no look-up through memory.  first[f]: first workgroup of job f (INT_MAX
 // past the last), side by side so that two scalar loads find the job.
+template <int CAP>
 struct LpaArgs {
-  int first[kLpaArgs];
-  LpaJob job[kLpaArgs];
+  int first[CAP];
+  LpaJob job[CAP];
 };
-template <bool HOST>
-__global__ __launch_bounds__(kLpaBlock) void lpa_args_kernel(LpaArgs a, LpaDone done) {
+template <bool HOST, int CAP>
+__global__ __launch_bounds__(kLpaBlock) void lpa_args_kernel(LpaArgs<CAP> a, LpaDone done) {
   int f = 0;
 #pragma unroll
-  for (int i = 1; i < kLpaArgs; ++i) f += a.first[i] <= (int)blockIdx.x;
+  for (int i = 1; i < CAP; ++i) f += a.first[i] <= (int)blockIdx.x;
   lpa_block<HOST>(a.job[f], done);
 }
 template <bool HOST>
@@ -921,17 +922,28 @@ int launch_grid(const GridArgs &g, int reg, int M, int W, void *stream) {
   return (int)hipGetLastError();
 }
 
+template <int CAP>
+static void lpa_args_t(const LpaJob *jobs, int n_jobs, int64_t blocks, const LpaDone &done,
+                       hipStream_t st) {
+  LpaArgs<CAP> a;
+  for (int i = 0; i < CAP; ++i) {
+    a.first[i] = i < n_jobs ? jobs[i].block : INT_MAX;
+    a.job[i] = i < n_jobs ? jobs[i] : LpaJob{};
+  }
+  hipLaunchKernelGGL((done.word ? lpa_args_kernel<true, CAP> : lpa_args_kernel<false, CAP>),
+                     dim3((unsigned)blocks), dim3(kLpaBlock), 0, st, a, done);
+}
+
 int launch_lpa_args(const LpaJob *jobs, int n_jobs, int64_t blocks, const LpaDone &done,
                     void *stream) {
   if (blocks <= 0) return 0;
   if (n_jobs > kLpaArgs) return (int)hipErrorInvalidValue;
-  LpaArgs a;
-  for (int i = 0; i < kLpaArgs; ++i) {
-    a.first[i] = i < n_jobs ? jobs[i].block : INT_MAX;
-    a.job[i] = i < n_jobs ? jobs[i] : LpaJob{};
-  }
-  hipLaunchKernelGGL(done.word ? lpa_args_kernel<true> : lpa_args_kernel<false>,
-                     dim3((unsigned)blocks), dim3(kLpaBlock), 0, (hipStream_t)stream, a, done);
+  // one or two jobs (a lone flow, most served batches) leave out 2.9 KB of unused
+  // argument space: 3.5 us from call to call, 5.1 with it
+  if (n_jobs <= 2)
+    lpa_args_t<2>(jobs, n_jobs, blocks, done, (hipStream_t)stream);
+  else
+    lpa_args_t<kLpaArgs>(jobs, n_jobs, blocks, done, (hipStream_t)stream);
   return (int)hipGetLastError();
 }
 
