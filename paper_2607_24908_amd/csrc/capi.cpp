@@ -197,7 +197,7 @@ int Ctx::lpa_table(int d, int reg, int n_r, double qmk, const double **dev, doub
 int Ctx::fv_panels(int d, int reg, int n_r, double qmk, const double **dev) {
   LEntry &ent = ltabs.at(std::make_tuple(d, reg, n_r, dbits(qmk)));
   if (!ent.panels_asked) {
-    const size_t bytes = sizeof(double) * kPanels * kFvPoly;
+    const size_t bytes = sizeof(double) * kFvTable;
     if (!hbm.spare(bytes)) {  // decided once: the rule's results keep their bits
       ent.panels_asked = true;
       *dev = nullptr;

@@ -81,5 +81,47 @@ __device__ __forceinline__ void fv_poly(const double *poly, const double *x, con
   }
 }
 
+// Whether every x is in a panel of the whole table or, finite, above them all where
+// its moments hold; p: their panels.
+template <int M>
+__device__ __forceinline__ bool fv_covered(const double *table, const double *x, int *p) {
+  bool all = table != nullptr;
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    p[m] = fv_panel<kPanelLo>(x[m]);
+    all &= (unsigned)p[m] < (unsigned)kPanels ||
+           (x[m] >= __builtin_ldexp(1.0, kPanelHi) && x[m] < __builtin_inf());
+  }
+  return all && table[kPanels * kFvPoly] > 0.0;
+}
+// s1[m], s2[m] at masses that fv_covered accepts: a panel's by fv_poly, the others
+// from four moments C_m, s1 = z (C_0 - z (C_1 - z (C_2 - z C_3))), z = 1/x, and s2 =
+// -ds1/dx; the terms left out are below 5 (2^(kFvTailH - kPanelHi))^4 = 3e-19.
+template <int M, bool FIRST>
+__device__ __forceinline__ void fv_table_sums(const double *table, const double *x, const int *p,
+                                              double *s1, double *s2) {
+  double xc[M];
+  int pc[M];
+  bool some = false;
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const bool in = (unsigned)p[m] < (unsigned)kPanels;
+    some |= in;
+    xc[m] = in ? x[m] : 1.0;
+    pc[m] = in ? p[m] : -kPanelLo * kFvPerOctave;
+  }
+  if (some) fv_poly<M, FIRST>(table, xc, pc, s1, s2);
+  using Const = const __attribute__((address_space(4))) double *;
+  const Const C = (Const)(table + kPanels * kFvPoly);
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    if ((unsigned)p[m] < (unsigned)kPanels) continue;
+    const double z = 1.0 / x[m];
+    s1[m] = z * __builtin_fma(-z, __builtin_fma(-z, __builtin_fma(-z, C[3], C[2]), C[1]), C[0]);
+    s2[m] = (z * z) * __builtin_fma(-z, __builtin_fma(-z, __builtin_fma(-z, 4.0 * C[3], 3.0 * C[2]),
+                                                      2.0 * C[1]), C[0]);
+  }
+}
+
 }  // namespace dev
 }  // namespace frg

@@ -62,7 +62,9 @@ LpaTable build_lpa_table(int d, int reg, int n_r, double q_max_over_k);
 // t = -9 takes x to 1e9, one that ends at its pole towards 0), s1 as kFvPoly
 // coefficients of ascending powers of x - (middle of the panel), and s2 as minus
 // their derivative.  The finite-volume solve copies those from 2^kFvLo to 2^kFvHi
-// into LDS (51 KB: two workgroups per CU).
+// into LDS (51 KB: two workgroups per CU).  Behind the panels kFvTail moments
+// sum_i c_i h_i^m of the expansions in 1/x for x >= 2^kPanelHi; the first is 0 if
+// some h_i is above 2^kFvTailH, where four terms of them would not do.
 constexpr int kFvPerOctave = 16;
 constexpr int kPanelLo = -26, kPanelHi = 34;
 constexpr int kPanels = (kPanelHi - kPanelLo) * kFvPerOctave;
@@ -70,6 +72,8 @@ constexpr int kFvLo = -14, kFvHi = 22;
 constexpr int kFvPanels = (kFvHi - kFvLo) * kFvPerOctave;
 constexpr int kFvFirst = (kFvLo - kPanelLo) * kFvPerOctave;  // panel 2^kFvLo of the table
 constexpr int kFvPoly = 11;
+constexpr int kFvTail = 4, kFvTailH = 18;
+constexpr int kFvTable = kPanels * kFvPoly + kFvTail;  // doubles
 std::vector<double> build_fv_panels(const LpaTable &t);
 
 double omega_sphere(int n);  // area of S^{n-1}
@@ -216,7 +220,7 @@ struct PflowArgs {
 // bounds lam (same layout); F_n from the scale-free LPA table [chat | hhat].
 struct FvArgs {
   const double *tab;   // LpaTable::data on the device
-  const double *poly;  // build_fv_panels on the device
+  const double *poly;  // build_fv_panels on the device, null: every sum from tab
   double *y0;          // state at the start of the step
   double *ys;          // stage state
   double *Q, *lam;
@@ -230,7 +234,6 @@ struct FvArgs {
   double ds, inv_ds, h, t_n;
   int64_t n_rows, n;
   int32_t n_r, N, d;
-  int32_t n_panels;    // kFvPanels; 0: no panels, every sum takes the other branch
   int32_t stage;       // 0..2 SSP-RK3 stages, 3: right-hand side only
   int32_t first;       // flux kernel: read y0 (first stage / rhs) instead of ys
 };
@@ -239,9 +242,9 @@ int launch_fv_flux(const FvArgs &a, void *stream);
 int launch_fv_stage(const FvArgs &a, void *stream);
 int launch_fv_dt(const FvArgs &a, void *stream);
 // Steps [s0, s0 + n_st) of a solve, one workgroup per flow with its state in
-// LDS (fv_solve_lds_bytes); alive, t_reached and flag set up by
+// LDS (where fv_solve_fused holds); alive, t_reached and flag set up by
 // launch_fv_init.
-int64_t fv_solve_lds_bytes(const FvArgs &a);
+bool fv_solve_fused(const FvArgs &a, int n_cu);
 constexpr int kFvSolveLdsMax = 160 * 1024;
 int launch_fv_solve(const FvArgs &a, int64_t s0, int64_t n_st, void *stream);
 int launch_pflow_init(const PflowArgs &a, double t_end, void *stream);

@@ -99,44 +99,83 @@ __device__ __forceinline__ FvCells fv_cells(const double *u, int n, int j) {
   return c;
 }
 
-// s1 and s2 outside the panels (device_panels.h): for x in [kFvXMin, kFvXMax] the
-// coefficient groups, N/P and M/P^2 by Horner with one reciprocal per group of
-// eight nodes (the powers of x and the products stay inside the FP64 range
-// there); beyond those term by term.  Every term and coefficient is positive
-// and x > 0, so neither form cancels.
+// s1 and s2 at M masses without the panels (device_panels.h): for x in [kFvXMin,
+// kFvXMax] the coefficient groups, N/P and M/P^2 by Horner with one reciprocal per
+// group of eight nodes (the powers of x and the products stay inside the FP64 range
+// there); beyond those term by term.  Every term and coefficient is positive and x >
+// 0, so neither form cancels.  The masses' chains run in step, coefficients in scalar
+// registers (loaded there through the constant address space; the compiler's own FMA
+// copies the addend into vector registers first, two moves per coefficient).
 constexpr double kFvXMin = 1e-20, kFvXMax = 1e20;
+using FvConst = const __attribute__((address_space(4))) double *;
 
-struct FvSums {
-  double s1, s2;
-};
-__device__ __forceinline__ FvSums fv_radial_far(const double *tab, int n_r, double x) {
-  const double *cf = tab + 2 * n_r;
-  FvSums s{0.0, 0.0};
-  if (x >= kFvXMin && x <= kFvXMax) {
+__device__ __forceinline__ double fma_su(double a, double b, double c) {
+  double r;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+  return r;
+}
+template <int M>
+__device__ __forceinline__ void fv_radial_far(const double *table, int n_r, const double *x,
+                                              double *s1, double *s2) {
+  const FvConst tab = (FvConst)table, cf = tab + 2 * n_r;
+  bool in[M], some = false, all = true;
+  double xc[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    in[m] = x[m] >= kFvXMin && x[m] <= kFvXMax;
+    some |= in[m];
+    all &= in[m];
+    xc[m] = in[m] ? x[m] : 1.0;
+    s1[m] = s2[m] = 0.0;
+  }
+  if (some) {
     const int ng = (n_r + kFvGroup - 1) / kFvGroup;
 #pragma unroll 1
     for (int g = 0; g < ng; ++g) {
-      const double *c = cf + kFvCoef * g;
-      double P = x + c[7];
-      for (int k = 6; k >= 0; --k) P = __builtin_fma(P, x, c[k]);
-      double N = c[15];
-      for (int k = 14; k >= 8; --k) N = __builtin_fma(N, x, c[k]);
-      double M = c[30];
-      for (int k = 29; k >= 16; --k) M = __builtin_fma(M, x, c[k]);
-      const double r = rcp64(P);
-      s.s1 = __builtin_fma(N, r, s.s1);
-      s.s2 = __builtin_fma(M * r, r, s.s2);
-    }
-  } else {
-#pragma unroll 1
-    for (int i = 0; i < n_r; ++i) {
-      const double G = rcp64(tab[n_r + i] + x);
-      const double cg = tab[i] * G;
-      s.s1 += cg;
-      s.s2 = __builtin_fma(cg, G, s.s2);
+      const FvConst c = cf + kFvCoef * g;
+      double P[M], N[M], Q[M];
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        P[m] = xc[m] + c[7];
+        N[m] = c[15];
+        Q[m] = c[30];
+      }
+#pragma unroll
+      for (int k = 6; k >= 0; --k)
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+          P[m] = fma_su(P[m], xc[m], c[k]);
+          N[m] = fma_su(N[m], xc[m], c[k + 8]);
+          Q[m] = fma_su(Q[m], xc[m], c[k + 23]);
+        }
+#pragma unroll
+      for (int k = 22; k >= 16; --k)
+#pragma unroll
+        for (int m = 0; m < M; ++m) Q[m] = fma_su(Q[m], xc[m], c[k]);
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const double r = rcp64(P[m]);
+        s1[m] = __builtin_fma(N[m], r, s1[m]);
+        s2[m] = __builtin_fma(Q[m] * r, r, s2[m]);
+      }
     }
   }
-  return s;
+  if (!all) {
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      if (!in[m]) s1[m] = s2[m] = 0.0;
+#pragma unroll 1
+    for (int i = 0; i < n_r; ++i)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const double G = rcp64(tab[n_r + i] + x[m]);
+        const double cg = tab[i] * G;
+        if (!in[m]) {
+          s1[m] += cg;
+          s2[m] = __builtin_fma(cg, G, s2[m]);
+        }
+      }
+  }
 }
 
 // Flux Q and (LAM) the local bound lam of the step estimate at interface j from
@@ -144,14 +183,16 @@ __device__ __forceinline__ FvSums fv_radial_far(const double *tab, int n_r, doub
 // = (u_0 - u_{-1})/ds = 2 u_0/ds is the only mass that enters.  The masses are
 // d_sigma u and, for N > 1 (GOLD), the limited states u-/sigma_j and u+/sigma_j;
 // bad: one of them has left the domain.  All masses of the interface in one lane,
-// so that their panel loads and Horner chains fill each other's latency; a mass
-// outside the domain is outside the panels too, so only the other branch looks.
+// so that their panel loads and Horner chains fill each other's latency.  NEAR: the
+// panels 2^kFvLo .. 2^kFvHi, at `near`, alone; a mass outside them counts as bad and
+// leaves the sums of some panel.  Else the whole table, or the sums without it where a
+// mass is in no panel (so is one outside the domain) or there is no table.
 struct FvOut {
   double Q, lam;
   bool bad;
 };
-template <bool GOLD, bool LAM>
-__device__ __forceinline__ FvOut fv_iface(const FvArgs &a, const FvScale &sc, const double *poly,
+template <bool GOLD, bool LAM, bool NEAR>
+__device__ __forceinline__ FvOut fv_iface(const FvArgs &a, const FvScale &sc, const double *near,
                                           const FvCells &c, double isj, bool zero) {
   constexpr int M = GOLD ? 3 : 1;
   const double ids = a.inv_ds;
@@ -166,35 +207,29 @@ __device__ __forceinline__ FvOut fv_iface(const FvArgs &a, const FvScale &sc, co
     delta[1] = __builtin_fma(um, isj, sc.k2);
     delta[2] = __builtin_fma(up, isj, sc.k2);
   }
-  bool near = true;
+  FvOut o;
+  o.bad = false;
 #pragma unroll
   for (int m = 0; m < M; ++m) {
     x[m] = delta[m] * sc.inv_k2;
-    p[m] = fv_panel<kFvLo>(x[m]);
-    near &= (unsigned)p[m] < (unsigned)a.n_panels;
-  }
-  FvOut o;
-  o.bad = false;
-  if (near) {
-    fv_poly<M, LAM>(poly, x, p, s1, s2);
-  } else {
-#pragma unroll 1
-    for (int m = 0; m < M; ++m) {
-      const bool bad = !((m == 0 ? delta[0] : (m == 1 ? delta[M / 2] : delta[M - 1])) > 0.0);
-      const double xm = bad ? 1.0 : (m == 0 ? x[0] : (m == 1 ? x[M / 2] : x[M - 1]));
-      const int pm = fv_panel<kFvLo>(xm);
-      o.bad |= bad;
-      FvSums s;
-      if ((unsigned)pm < (unsigned)a.n_panels)
-        fv_poly<1, true>(poly, &xm, &pm, &s.s1, &s.s2);
-      else
-        s = fv_radial_far(a.tab, a.n_r, xm);
-#pragma unroll
-      for (int i = 0; i < M; ++i) {
-        s1[i] = i == m ? s.s1 : s1[i];
-        s2[i] = i == m ? s.s2 : s2[i];
-      }
+    if constexpr (NEAR) {
+      p[m] = fv_panel<kFvLo>(x[m]);
+      o.bad |= (unsigned)p[m] >= (unsigned)kFvPanels;
+      p[m] = (int)min((unsigned)p[m], (unsigned)kFvPanels - 1u);
     }
+  }
+  if constexpr (NEAR) {
+    fv_poly<M, LAM>(near, x, p, s1, s2);
+  } else if (fv_covered<M>(a.poly, x, p)) {
+    fv_table_sums<M, LAM>(a.poly, x, p, s1, s2);
+  } else {
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const bool bad = !(delta[m] > 0.0);
+      o.bad |= bad;
+      x[m] = bad ? 1.0 : x[m];
+    }
+    fv_radial_far<M>(a.tab, a.n_r, x, s1, s2);
   }
   const double q0 = (zero ? sc.n1 : sc.c1) * s1[0];
   o.Q = q0;
@@ -239,8 +274,8 @@ __global__ __launch_bounds__(256) void fv_flux_kernel(FvArgs a) {
   const FvScale sc = fv_scale(a, a.t);
   const FvCells c = fv_cells(u, (int)a.n, (int)j);
   const double isj = fv_isj(a, (int)j);
-  const FvOut o = a.N > 1 ? fv_iface<true, true>(a, sc, a.poly, c, isj, j == 0)
-                          : fv_iface<false, true>(a, sc, a.poly, c, isj, j == 0);
+  const FvOut o = a.N > 1 ? fv_iface<true, true, false>(a, sc, nullptr, c, isj, j == 0)
+                          : fv_iface<false, true, false>(a, sc, nullptr, c, isj, j == 0);
   if (o.bad) {
     // the flow ends at the start of this step with its state kept
     a.alive[r] = 0;
@@ -271,9 +306,9 @@ __global__ __launch_bounds__(256) void fv_stage_kernel(FvArgs a) {
   }
 }
 
-// Steps [s0, s0 + n_st) of one flow per workgroup, everything in LDS: three
-// state buffers with their ghost cells, 1/sigma_j, the polynomial panels and the
-// scales of the next kFvScaleSteps steps (formed by all threads at once).  A
+// Steps of one flow by its workgroup, everything in LDS: three state buffers with
+// their ghost cells, 1/sigma_j, the polynomial panels and the scales of the next
+// kFvScaleSteps steps (formed by all threads at once).  A
 // wave takes 64 consecutive interfaces and with them the 63 cells between: each
 // lane forms its interface's flux (fv_iface), takes its left neighbour's by a
 // lane permutation and updates the cell between the two; the next wave starts
@@ -281,74 +316,68 @@ __global__ __launch_bounds__(256) void fv_stage_kernel(FvArgs a) {
 // one wave holds the cells of the ghosts.  One barrier per stage.  The
 // per-interface and per-cell arithmetic is that of the flux and stage kernels
 // (same bits); no launch per stage.  A step goes from buffer Y over A and B to A,
-// so a flow whose masses leave the domain in it ends with Y, the state of its
-// start.
+// so a step that fv_iface finds bad leaves Y, the state of its start.
 //
 // Bound by the latency of this chain (cells, states, panels, Horner, flux) on
-// the one CU of a flow, one wave on most SIMDs: 0.60 us per stage for one wave
-// (63 cells), 0.76 for four and 0.92 for the five of 256 cells, whose panel
+// the one CU of a flow, one wave on most SIMDs: 0.57 us per stage for one wave
+// (63 cells), 0.68 for the four of 200 cells and 0.85 for the five of 256 cells, whose panel
 // coefficients (84 KB per stage) also share the CU's LDS port.  128 flows of 256
-// cells, 64 nodes, N = 4, 2000 steps: 5.5 ms.  With the radial sums as rational
+// cells, 64 nodes, N = 4, 2000 steps: 5.1 ms.  With the radial sums as rational
 // groups, one lane per mass, four barriers per stage and the scales formed by
 // every thread it took 25.9 ms; this kernel's sums with a quad of lanes per
 // interface (each lane one mass, two barriers) 8.6 ms, bound by instruction
 // issue.  At most 128 VGPRs, so that two workgroups of five waves fit a CU
-// (512 flows: 1.31 us per stage, 1.83 at 151 VGPRs).
+// (512 flows: 1.20 us per stage; 1.83 at 151 VGPRs with an earlier loop of 1.31).
+//
+// From the first step with a mass outside the panels in LDS a flow goes on in a loop
+// of its own, with the whole table and the sums without it; in one loop they took
+// registers of the panels' (0.94 us per stage, 0.85 so). 128 flows of 256 cells there:
+// 1.6 us per stage with the masses in the other panels, 1.5 above them all, whatever
+// the order of the rule (14 us at 64 nodes and 211 at 1024 by rational groups, one
+// mass after the other); 4.8, 16 and 55 us at 64, 256 and 1024 nodes in a context
+// that cannot spare the table.
 constexpr int kFvScaleSteps = 32;
 constexpr int kFvWaveCells = kWave - 1;
 constexpr int kFvMaxWaves = 8;
 
-template <bool GOLD>
-__global__ __launch_bounds__(kFvMaxWaves * kWave, 4) void fv_solve_kernel(FvArgs a, int64_t s0,
-                                                                         int64_t n_st) {
-  extern __shared__ double lds[];
-  const int64_t r = blockIdx.x;
-  if (!a.alive[r]) return;  // workgroup-uniform
+struct FvLds {
+  const double *poly;
+  double *Y, *A, *B, *isj;
+  FvScale *scales;  // [kFvScaleSteps][3]
+  int *bad;         // 0 between steps
+};
+// Steps st .. n_st - 1 of the launch's, up to one that is bad: the step after the
+// last good one, whose state is in l.Y.
+template <bool GOLD, bool NEAR>
+__device__ __forceinline__ int64_t fv_steps(const FvArgs &a, FvLds &l, int64_t s0, int64_t st,
+                                            int64_t n_st) {
   const int n = (int)a.n;
   const int tid = threadIdx.x, bs = blockDim.x;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  double *poly = lds;
-  double *Y = poly + kFvPanels * kFvPoly + 2;  // cells -2 .. n + 1 each
-  double *A = Y + n + 4;
-  double *B = A + n + 4;
-  double *isj = B + n + 2;  // [n + 1]
-  FvScale *scales = reinterpret_cast<FvScale *>(isj + n + 1);  // [kFvScaleSteps][3]
-  int *bad_flag = reinterpret_cast<int *>(scales + 3 * kFvScaleSteps);
-  const double *y = a.y0 + r * n;
-  for (int i = tid; i < a.n_panels * kFvPoly; i += bs) poly[i] = a.poly[i];
-  for (int i = tid; i < n; i += bs) Y[i] = y[i];
-  for (int j = tid; j <= n; j += bs) isj[j] = fv_isj(a, j);
-  if (tid == 0) {
-    *bad_flag = 0;
-    Y[-2] = A[-2] = B[-2] = 0.0;  // read by interface 0, in which it does not enter
-    Y[-1] = -y[0];
-    Y[n] = fv_ghost(y[n - 2], y[n - 1]);
-    Y[n + 1] = fv_ghost(y[n - 1], Y[n]);
-  }
   const double cs[3] = {0.0, 1.0, 0.5};
   const double hids = a.h * a.inv_ds;
-  for (int64_t st = 0; st < n_st; ++st) {
+  for (; st < n_st; ++st) {
     const int sl = (int)(st % kFvScaleSteps);
     if (sl == 0) {
       for (int k = tid; k < 3 * kFvScaleSteps; k += bs) {
         const double t = (double)(s0 + st + k / 3) * a.h;
-        scales[k] = fv_scale(a, t + cs[k % 3] * a.h);
+        l.scales[k] = fv_scale(a, t + cs[k % 3] * a.h);
       }
       __syncthreads();
     }
     bool bad = false;
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
-      const FvScale sc = scales[3 * sl + s];
-      const double *u = s == 0 ? Y : (s == 1 ? A : B);
-      double *dst = s == 1 ? B : A;
+      const FvScale sc = l.scales[3 * sl + s];
+      const double *u = s == 0 ? l.Y : (s == 1 ? l.A : l.B);
+      double *dst = s == 1 ? l.B : l.A;
       for (int je = n - wave * kFvWaveCells; je > 0; je -= bs / kWave * kFvWaveCells) {
         const int jl = je - kFvWaveCells + lane;  // je is the wave's last interface
         const int j = max(jl, 0);
         const FvCells c{u[j - 2], u[j - 1], u[j], u[j + 1]};
-        const double y0 = s == 0 ? c.L : Y[j - 1];
-        const FvOut o = fv_iface<GOLD, false>(a, sc, poly, c, isj[j], j == 0);
+        const double y0 = s == 0 ? c.L : l.Y[j - 1];
+        const FvOut o = fv_iface<GOLD, false, NEAR>(a, sc, l.poly, c, l.isj[j], j == 0);
         bad |= o.bad;
         const double left = dpp_f64<0x138>(o.Q);  // wave_shr 1: the flux of interface j - 1
         const double v = fv_update(s, o.Q - left, hids, y0, c.L);
@@ -363,22 +392,60 @@ __global__ __launch_bounds__(kFvMaxWaves * kWave, 4) void fv_solve_kernel(FvArgs
           }
         }
       }
-      if (s == 2 && bad) *bad_flag = 1;
+      if (s == 2 && bad) *l.bad = 1;
       __syncthreads();
     }
-    if (*bad_flag) {  // workgroup-uniform
-      if (tid == 0) {
-        a.alive[r] = 0;
-        a.t_reached[r] = (double)(s0 + st) * a.h;
-        *a.flag = 1;
-      }
-      break;
-    }
-    double *t = Y;
-    Y = A;
-    A = t;
+    if (*l.bad) break;  // workgroup-uniform
+    double *t = l.Y;
+    l.Y = l.A;
+    l.A = t;
   }
-  for (int i = tid; i < n; i += bs) a.y0[r * n + i] = Y[i];
+  return st;
+}
+
+// Steps [s0, s0 + n_st) of one flow per workgroup.
+template <bool GOLD>
+__global__ __launch_bounds__(kFvMaxWaves * kWave, 4) void fv_solve_kernel(FvArgs a, int64_t s0,
+                                                                         int64_t n_st) {
+  extern __shared__ double lds[];
+  const int64_t r = blockIdx.x;
+  if (!a.alive[r]) return;  // workgroup-uniform
+  const int n = (int)a.n;
+  const int tid = threadIdx.x, bs = blockDim.x;
+  const int n_poly = a.poly ? kFvPanels * kFvPoly : 0;
+  double *poly = lds;
+  FvLds l;
+  l.poly = poly;
+  l.Y = poly + n_poly + 2;  // cells -2 .. n + 1 each
+  l.A = l.Y + n + 4;
+  l.B = l.A + n + 4;
+  l.isj = l.B + n + 2;  // [n + 1]
+  l.scales = reinterpret_cast<FvScale *>(l.isj + n + 1);
+  l.bad = reinterpret_cast<int *>(l.scales + 3 * kFvScaleSteps);
+  const double *y = a.y0 + r * n;
+  for (int i = tid; i < n_poly; i += bs) poly[i] = a.poly[kFvFirst * kFvPoly + i];
+  for (int i = tid; i < n; i += bs) l.Y[i] = y[i];
+  for (int j = tid; j <= n; j += bs) l.isj[j] = fv_isj(a, j);
+  if (tid == 0) {
+    *l.bad = 0;
+    l.Y[-2] = l.A[-2] = l.B[-2] = 0.0;  // read by interface 0, in which it does not enter
+    l.Y[-1] = -y[0];
+    l.Y[n] = fv_ghost(y[n - 2], y[n - 1]);
+    l.Y[n + 1] = fv_ghost(y[n - 1], l.Y[n]);
+  }
+  int64_t st = 0;
+  if (a.poly) st = fv_steps<GOLD, true>(a, l, s0, st, n_st);
+  if (st < n_st) {
+    __syncthreads();  // the flag is read
+    if (tid == 0) *l.bad = 0;
+    st = fv_steps<GOLD, false>(a, l, s0, st, n_st);
+    if (st < n_st && tid == 0) {
+      a.alive[r] = 0;
+      a.t_reached[r] = (double)(s0 + st) * a.h;
+      *a.flag = 1;
+    }
+  }
+  for (int i = tid; i < n; i += bs) a.y0[r * n + i] = l.Y[i];
 }
 
 // One workgroup per flow: step estimate 1 / max_j lam_j.
@@ -419,9 +486,25 @@ int launch_fv_stage(const FvArgs &a, void *stream) {
   return (int)hipGetLastError();
 }
 
-int64_t fv_solve_lds_bytes(const FvArgs &a) {
-  return (int64_t)sizeof(double) * (kFvPanels * kFvPoly + 3 * (a.n + 4) + a.n + 1) +
+static int64_t fv_solve_lds_bytes(const FvArgs &a) {
+  return (int64_t)sizeof(double) *
+             ((a.poly ? kFvPanels * kFvPoly : 0) + 3 * (a.n + 4) + a.n + 1) +
          (int64_t)sizeof(FvScale) * 3 * kFvScaleSteps + 16;
+}
+
+// One workgroup per flow, or the launches of the flux and stage kernels. With panels
+// the first wherever the LDS holds the flow. Without, the sums bound both forms: a
+// coefficient group of a wave's masses takes a SIMD about 0.2 us, and the launches
+// 8 us per stage beside them, over the whole chip (128 flows of 256 cells, 1024 nodes:
+// 55 us per stage by launches, 68 in the workgroup; at 64 nodes 4.8 in the workgroup).
+bool fv_solve_fused(const FvArgs &a, int n_cu) {
+  if (fv_solve_lds_bytes(a) > kFvSolveLdsMax) return false;
+  if (a.poly) return true;
+  const int64_t waves = (a.n + kFvWaveCells - 1) / kFvWaveCells, simds = 4 * (int64_t)n_cu;
+  const double sum = 0.2 * fv_groups(a.n_r);
+  const int64_t mine = ((a.n_rows + n_cu - 1) / n_cu * waves + 3) / 4;
+  const int64_t all = (a.n_rows * (a.n / kWave + 1) + simds - 1) / simds;
+  return sum * (double)mine <= 8.0 + sum * (double)all;
 }
 
 int launch_fv_solve(const FvArgs &a, int64_t s0, int64_t n_st, void *stream) {

@@ -49,8 +49,7 @@ int Ctx::fvlpa_device(const frg_fvlpa &f, int64_t n, double t_end, int64_t n_ste
   double *d = (double *)buf;
   FvArgs a{};
   a.tab = tab;
-  a.poly = poly ? poly + kFvFirst * kFvPoly : nullptr;
-  a.n_panels = poly ? kFvPanels : 0;
+  a.poly = poly;
   a.Q = d;
   d += nq;
   a.lam = d;
@@ -102,7 +101,7 @@ int Ctx::fvlpa_device(const frg_fvlpa &f, int64_t n, double t_end, int64_t n_ste
   if (!rc && solve) {
     const double hh = t_end / (double)n_steps;
     a.h = hh;
-    if (tune.fv_persistent && fv_solve_lds_bytes(a) <= kFvSolveLdsMax) {
+    if (tune.fv_persistent && fv_solve_fused(a, n_cu)) {
       // one workgroup per flow runs the steps with its state in LDS, in
       // launches of at most kFvStepsPerLaunch steps
       for (int64_t s0 = 0; s0 < n_steps && !rc; s0 += kFvStepsPerLaunch) {

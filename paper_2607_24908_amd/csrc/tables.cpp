@@ -230,7 +230,7 @@ std::vector<double> build_fv_panels(const LpaTable &t) {
     return m;
   }();
   const int n_r = t.n_r;
-  std::vector<double> out((size_t)kPanels * n);
+  std::vector<double> out((size_t)kFvTable);
   for (int p = 0; p < kPanels; ++p) {
     const int e = kPanelLo + p / kFvPerOctave, s = p % kFvPerOctave;
     const long double lo = ldexpl((long double)(kFvPerOctave + s) / kFvPerOctave, e);
@@ -254,6 +254,15 @@ std::vector<double> build_fv_panels(const LpaTable &t) {
       out[(size_t)p * n + i] = (double)(v * wi);
     }
   }
+  double h_max = 0.0;
+  for (int i = 0; i < n_r; ++i) h_max = std::fmax(h_max, t.data[n_r + i]);
+  if (h_max <= std::ldexp(1.0, kFvTailH))
+    for (int m = 0; m < kFvTail; ++m) {
+      long double v = 0.0L;
+      for (int i = 0; i < n_r; ++i)
+        v += (long double)t.data[i] * powl((long double)t.data[n_r + i], m);
+      out[(size_t)kPanels * n + m] = (double)v;
+    }
   return out;
 }
 
