@@ -901,7 +901,9 @@ int Ctx::lpa_job_table(int n, const frg_lpa *lpa, const double *t, const double 
     j.N = l.N;
     j.block = (int32_t)*blocks;
     j.far_bands = 1;
-    *blocks += (l.n_grid + kLpaBlock - 1) / kLpaBlock;
+    const bool fills = l.n_grid * lpa_wave_cost(l.n_radial) > (int64_t)(4 * n_cu) * kLpaNode * l.n_radial;
+    j.per = j.poly || fills ? kLpaBlock : kLpaFew;
+    *blocks += (l.n_grid + j.per - 1) / j.per;
   }
   return FRG_OK;
 }

@@ -148,6 +148,7 @@ struct LpaJob {
   double i2, i1;      // 1/(2 dr), 1/dr^2
   int32_t n, n_r, N;
   int32_t block;      // first workgroup of the flow in its launch
+  int32_t per;        // its grid points per workgroup, at most kLpaBlock
   int32_t far_bands;  // bands -3, -2, 2, 3: 1 all rows, 0 only the first and last row
                       // (the others are zero)
 };
@@ -159,8 +160,14 @@ struct LpaDone {
   unsigned *word;
   unsigned value;
 };
-// Workgroups of kLpaBlock grid points; jobs a launch carries in its arguments.
+// Grid points of a workgroup, without a table of panels; jobs a launch carries in its
+// arguments.
 constexpr int kLpaBlock = 64;
+constexpr int kLpaFew = 4;
+// Cycles of a wave for the sums of one point from the nodes: per node in one lane, and
+// over the lanes for all of them (see lpa_sums).
+constexpr int kLpaNode = 80, kLpaFold = 250;
+constexpr int lpa_wave_cost(int n_r) { return kLpaNode * ((n_r + 63) / 64) + kLpaFold; }
 constexpr int kLpaArgs = 24;
 
 void lane_split(int n_r, int n_a, int *R, int *J, int *T, int *U);

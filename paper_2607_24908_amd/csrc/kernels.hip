@@ -557,31 +557,71 @@ __device__ __forceinline__ void fd_coef(int64_t j, int64_t n, int o, double i2, 
   *c2 = b;
 }
 
-// s1 and s2 outside the panels, term by term.
-__device__ __forceinline__ void lpa_sums(const LpaJob &jb, double x, double &s1, double &s2) {
-  s1 = 0.0;
-  s2 = 0.0;
-#pragma unroll 1
-  for (int i = 0; i < jb.n_r; ++i) {
-    const double g = rcp64(jb.tab[jb.n_r + i] + x);
-    const double c = jb.tab[i] * g;
-    s1 += c;
-    s2 = __builtin_fma(c, g, s2);
+// s1 and s2 of the lanes that `far` names, from the radial nodes: every such lane its
+// own sums (kLpaNode cycles per node), or the wave one such lane after the other, its
+// 64 lanes the nodes (kLpaFold more for the sums over the lanes), whichever is less.
+__device__ __forceinline__ void lpa_sums(const LpaJob &jb, bool far, const double *x, double *s1,
+                                         double *s2) {
+  const int lane = (int)threadIdx.x;
+  unsigned long long todo = __builtin_amdgcn_ballot_w64(far);
+  if (__builtin_popcountll(todo) * lpa_wave_cost(jb.n_r) > kLpaNode * jb.n_r) {
+    if (far) {
+      s1[0] = s2[0] = s1[1] = s2[1] = 0.0;
+      // nodes through the scalar cache (uniform addresses, never written here)
+      const auto tab = (const __attribute__((address_space(4))) double *)jb.tab;
+#pragma unroll 4
+      for (int i = 0; i < jb.n_r; ++i) {
+        const double c = tab[i], h = tab[jb.n_r + i];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const double g = rcp64(h + x[m]), cg = c * g;
+          s1[m] += cg;
+          s2[m] = __builtin_fma(cg, g, s2[m]);
+        }
+      }
+    }
+    return;
+  }
+  for (; todo; todo &= todo - 1ull) {
+    const int src = __builtin_ctzll(todo);  // wave-uniform
+    const double xs = readlane64(x[0], src), xp = readlane64(x[1], src);
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i = lane; i < jb.n_r; i += kWave) {
+      const double c = jb.tab[i], h = jb.tab[jb.n_r + i];
+      const double gs = rcp64(h + xs), gp = rcp64(h + xp);
+      const double cs = c * gs, cp = c * gp;
+      v[0] += cs;
+      v[1] = __builtin_fma(cs, gs, v[1]);
+      v[2] += cp;
+      v[3] = __builtin_fma(cp, gp, v[3]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = wave_sum(v[k]);
+    if (lane == src) {
+      s1[0] = v[0];
+      s2[0] = v[1];
+      s1[1] = v[2];
+      s2[1] = v[3];
+    }
   }
 }
 
 // LPA right-hand side and Jacobian bands for a batch of flows: one lane per grid
-// point, F_1 and F_2 at its sigma and pion mass from the panels (outside them
-// term by term).  Workgroups of one wave, so that a flow of 1024 points uses 16
-// CUs; the job of a workgroup is found by scalar loads.
+// point, F_1 and F_2 at its sigma and pion mass from the panels and the expansion
+// above them, else from the radial nodes.  Workgroups of one wave, so that a flow of
+// 1024 points uses 16 CUs; the job of a workgroup is found by scalar loads.  Without
+// a table a workgroup takes kLpaFew points, each a pass of the whole wave, unless the
+// flow fills the chip with whole waves.
 //
 // Bound by launch and memory latency: arguments, U, panels, stores, one after
 // the other.  13 flows of 128 to 1024 points, with Jacobian bands: 4.4 us (one
 // wave per grid point with its lanes over the 64 radial nodes took 10.2 us,
 // and the upload of the job table before it 3.1 us); in the server's pinned
-// buffers 5.6 us per batch (8.6 us).
+// buffers 5.6 us per batch (8.6 us).  One flow of 1024 points and nodes, called from
+// Python: 7.3 us with its masses in the panels or above them, 12.6 without a table
+// (113 us for the last two with a lane for all nodes of its point).
 template <bool HOST>
-__device__ __forceinline__ void lpa_point(const LpaJob &jb, int j) {
+__device__ __forceinline__ void lpa_point(const LpaJob &jb, int j_in) {
   auto put = [](double *at, double v) {
     if constexpr (HOST)
       __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -589,6 +629,8 @@ __device__ __forceinline__ void lpa_point(const LpaJob &jb, int j) {
       *at = v;
   };
   const int n = jb.n;
+  const bool live = j_in < n;
+  const int j = min(j_in, n - 1);  // the other lanes help in lpa_sums
   const double dr = jb.dr;
   // four values of U from c, the points of j's formulas among them (n >= 4)
   const int c = min(max(j - 1, 0), n - 4);
@@ -615,12 +657,17 @@ __device__ __forceinline__ void lpa_point(const LpaJob &jb, int j) {
   const double x[2] = {(ok ? ds : jb.k2) * jb.inv_k2, ((ok && pion) ? dp : jb.k2) * jb.inv_k2};
   const int p[2] = {fv_panel<kPanelLo>(x[0]), fv_panel<kPanelLo>(x[1])};
   double s1[2], s2[2];
+  int q[2];
+  bool far = false;
   if (jb.poly && (unsigned)p[0] < (unsigned)kPanels && (unsigned)p[1] < (unsigned)kPanels) {
     fv_poly<2, true>(jb.poly, x, p, s1, s2);
+  } else if (fv_covered<2>(jb.poly, x, q)) {
+    fv_table_sums<2, true>(jb.poly, x, q, s1, s2);
   } else {
-    lpa_sums(jb, x[0], s1[0], s2[0]);
-    lpa_sums(jb, x[1], s1[1], s2[1]);
+    far = live;
   }
+  lpa_sums(jb, far, x, s1, s2);
+  if (!live) return;
   const double F1s = jb.pre1 * s1[0];
   const double F2s = jb.pre2 * s2[0];
   const double F1p = pion ? jb.pre1 * s1[1] : 0.0;
@@ -647,8 +694,8 @@ __device__ __forceinline__ void lpa_point(const LpaJob &jb, int j) {
 // (a release at system scope would write back the L2 in every workgroup).
 template <bool HOST>
 __device__ __forceinline__ void lpa_block(const LpaJob &jb, const LpaDone &done) {
-  const int j = ((int)blockIdx.x - jb.block) * kLpaBlock + (int)threadIdx.x;
-  if (j < jb.n) lpa_point<HOST>(jb, j);
+  const int i = (int)threadIdx.x;
+  lpa_point<HOST>(jb, i < jb.per ? ((int)blockIdx.x - jb.block) * jb.per + i : INT_MAX);
   if constexpr (HOST) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);
