@@ -619,9 +619,10 @@ int Ctx::grid_launch(GridArgs g, int reg, const GridCfg &cfg_in, hipStream_t st)
 // panels, interpolated (mass_nodes.hip), in batches of momenta whose values
 // stay within kMassValBytes.  Taken with the default form knobs when
 //   - there are at least kMassMin masses (two panels of 32 nodes are then at
-//     most half of them; masses spread over one factor of 16 to 256 in delta,
-//     the common range, fill two panels) and at most kMassMax (every workgroup
-//     looks through them);
+//     most half of them; the panels are fixed, so masses spread over a factor of
+//     16 to 256 in delta fill two or three of them, those of -0.9..10 k^2 two for
+//     half of all k and three for the others) and at most kMassMax (every
+//     workgroup looks through them);
 //   - the direct form would spend kMassWork lane slots (momenta x masses x
 //     padded nodes).  The two launches cost about 20 us before they scale:
 //     measured against the direct form, 64 x 16 nodes, 1024 momenta x 128
@@ -654,16 +655,20 @@ int Ctx::mass_nodes_launch(const GridArgs &g_in, int reg, bool vertex, bool big_
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return 0;
   }
   MassPlan m{};
-  // at most half as many nodes as masses, then one place per mass
-  m.ld = kMassNodes * std::min<int64_t>(kMassPanels, g.n_m / (2 * kMassNodes)) +
+  // the nodes of the panels, in fewer rounds than the masses (two panels each), then
+  // one place per mass
+  m.ld = kMassNodes * std::min(kMassPanels, 2 * (mass_rounds((int)g.n_m) - 1)) +
          ((g.n_m + 31) & ~(int64_t)31);
+  m.pass = (int)std::min<int64_t>(kMassPassTiles, (m.ld / 16 + 3) & ~(int64_t)3);
   m.parts = mass_nodes_parts(g.n_p, n_cu);
   const int64_t batch = std::min<int64_t>(
       g.n_p, std::max<int64_t>(64, (int64_t)(kMassValBytes / (sizeof(double) * m.ld))));
   m.plane = batch * m.ld;
   const size_t o_lag = 256;
   const size_t o_val = o_lag + sizeof(double) * kMassNodes * g.n_m;
-  const size_t bytes = o_val + sizeof(double) * (size_t)m.plane * (m.parts > 1 ? 4 : 1);
+  const size_t o_spill = o_val + sizeof(double) * (size_t)m.plane * (m.parts > 1 ? 4 : 1);
+  const size_t bytes = o_spill + sizeof(double) * kWave * m.pass *
+                                     mass_nodes_blocks(batch, m.parts, n_cu);
   const size_t node_doubles = 5 * kMassNodes, reg_doubles = (size_t)kRegPanels * kRegCoef;
   const size_t node_bytes = sizeof(double) * (node_doubles + reg_doubles);
   size_t more = mass_nodes.bytes ? 0 : node_bytes;
@@ -696,6 +701,7 @@ int Ctx::mass_nodes_launch(const GridArgs &g_in, int reg, bool vertex, bool big_
   m.panels = (unsigned *)base;
   m.lag = (double *)(base + o_lag);
   m.val = (double *)(base + o_val);
+  m.spill = (double *)(base + o_spill);
   int e = 0;
   for (int64_t a = 0; a < g_in.n_p && !e; a += batch) {
     g.n_p = std::min(batch, g_in.n_p - a);

@@ -356,6 +356,8 @@ std::vector<double> build_vertex_table(int d, int n_a, int n_phi);
 constexpr int kMassNodes = 32;
 constexpr int kMassPanelLo = -24, kMassPanelHi = 24;
 constexpr int kMassPanels = (kMassPanelHi - kMassPanelLo) / 4;
+// Rounds of four tiles of 16, one per wave of a workgroup, that n masses take.
+constexpr int mass_rounds(int n) { return (n + 63) / 64; }
 // [x_n in [1, 16] | u_n = ln(x_n/4) as hi | lo | barycentric weights w_n as hi | lo]
 std::vector<double> build_mass_nodes();
 // h(y) = y/(1 - e^-y) - 1 in panels: [0, 5/16), eight per octave up to 40, and
@@ -369,15 +371,20 @@ std::vector<double> build_regulator_table();
 // Device arrays of one call: panels, which of them are interpolated; lag[32 b +
 // n] the Lagrange rows; val[a ld + e] the values (32 nodes per interpolated
 // panel, then the masses; parts > 1: four planes to be added, plane doubles
-// apart).  n_lag: set by the launch.
+// apart).  pass: tiles of 16 places that a workgroup takes over one pass of the table,
+// spill: room for their sums, 64 per tile and workgroup, if there are more tiles than
+// kMassRegTiles.
+// n_lag: set by the launch.
 struct MassPlan {
   const double *nodes, *reg;
   unsigned *panels;
-  double *val, *lag;
+  double *val, *lag, *spill;
   int64_t ld, plane;
-  int parts, n_lag;
+  int parts, n_lag, pass;
 };
 int mass_nodes_parts(int64_t n_p, int n_cu);
+int mass_nodes_blocks(int64_t n_p, int parts, int n_cu);  // workgroups of a batch
+constexpr int kMassRegTiles = 8, kMassPassTiles = 64;
 // first: the first batch of momenta of the call (also forms the Lagrange rows)
 int launch_mass_nodes(const GridArgs &g, MassPlan m, int reg, bool vertex, bool first, int n_cu,
                       void *stream);

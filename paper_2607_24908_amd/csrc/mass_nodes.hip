@@ -26,7 +26,8 @@
 // momentum at the 32 nodes of each panel that holds a mass (the coefficient form
 // on the matrix cores, device_grid.h), and at the masses that lie in no panel
 // (outside the domain, or beyond the coefficient form) themselves; where the
-// panels' nodes are more than half the masses, every mass is evaluated itself.
+// panels' nodes would take as many rounds of a workgroup's waves as the masses, every
+// mass is evaluated itself.
 // Their last workgroups form the Lagrange rows of the masses meanwhile.
 // mass_interp_kernel forms values x Lagrange rows, also on the matrix cores.
 //
@@ -43,6 +44,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "frg_internal.h"
 
@@ -144,7 +146,10 @@ __device__ __forceinline__ void lagrange_rows(const GridArgs &g, const MassPlan 
 }
 
 // Bit p: panel p holds a mass and is interpolated; bit 31: some mass is
-// evaluated itself.  The same in every workgroup (all threads take part; `sh`:
+// evaluated itself.  Interpolated while the nodes take fewer rounds (kNodeWaves tiles of
+// 16) than the masses: 4096 momenta x 131 or 190 masses in three panels, 206 us, against
+// 333 and 361 where half as many nodes as masses were asked for.  The same in every
+// workgroup (all threads take part; `sh`:
 // kNodeWaves words of LDS).
 constexpr unsigned kSingles = 1u << 31;
 __device__ __forceinline__ unsigned mass_panels(const GridArgs &g, unsigned *sh) {
@@ -160,7 +165,8 @@ __device__ __forceinline__ unsigned mass_panels(const GridArgs &g, unsigned *sh)
   mask = 0;
   for (int w = 0; w < (int)(blockDim.x / kWave); ++w) mask |= sh[w];
   mask = __builtin_amdgcn_readfirstlane(mask);
-  return 2 * N * __builtin_popcount(mask & ~kSingles) > (int)g.n_m ? kSingles : mask;
+  return mass_rounds(N * __builtin_popcount(mask & ~kSingles)) < mass_rounds((int)g.n_m) ? mask
+                                                                                     : kSingles;
 }
 
 // Slot of mass x among the interpolated panels, or -1.
@@ -286,9 +292,27 @@ __device__ __forceinline__ void expand_group(double *col, const double *f, doubl
 // fill(row, k): the regulator value of its term k; expand(gg, col, l):
 // expand_group with the group's factors and weights; single(delta): per-term
 // lane partial of a mass outside the coefficient form.
+// A chunk is built once for up to kMassRegTiles tiles, two per wave with their sums in
+// registers (the nodes of four panels, or 128 masses); for more (MANY) the sums are in
+// memory, m.spill, one row per workgroup: a pass of the table takes m.pass tiles and
+// reads and writes 128 bytes per tile and chunk beside 72 matrix instructions.  The two
+// are loops of their own: one for both took 162 us for 157 on 4096 momenta x 512 masses.
+// With two tiles per wave for every list, and each chunk built again for the next ones,
+// 1024 momenta (128 x 32 nodes) x 512 masses over ten panels took 229 us, 142 so (176
+// in the direct form); x 300, not interpolated, 152, 134 so (123).  Lists of 129 to 384
+// masses over more than four panels are the ones slower than the direct form, by up to
+// 9 % (vertex 256 x 512 over ten panels, 48 x 8 x 16 nodes: 88 us, 73): masses on the
+// device cannot be looked at before the launch.
 constexpr int kChunk = 2;      // coefficient groups of a chunk
-constexpr int kWaveTiles = 2;  // tiles of a wave held at once
-template <int G, int E, class LaneRow, class Fill, class Expand, class Single>
+constexpr int kWaveTiles = 2;  // tiles of a wave held in registers
+static_assert(kNodeWaves * kWaveTiles == kMassRegTiles && kMassPassTiles <= 32 * kNodeWaves,
+              "a wave's tiles of a pass are the bits of a word");
+// Tiles of 16: the nodes of the panels, then the masses (those in a panel are passed over).
+__device__ __forceinline__ int node_tiles(const GridArgs &g, unsigned panels) {
+  return N / 16 * __builtin_popcount(panels & ~kSingles) +
+         ((panels & kSingles) ? ((int)g.n_m + 15) / 16 : 0);
+}
+template <int G, int E, bool MANY, class LaneRow, class Fill, class Expand, class Single>
 __device__ __forceinline__ void node_values(const GridArgs &g, const MassPlan &m, double *lC,
                                             int64_t a, int part, unsigned panels,
                                             bool p_ok, bool table, int n_grp, LaneRow lane_row,
@@ -297,11 +321,9 @@ __device__ __forceinline__ void node_values(const GridArgs &g, const MassPlan &m
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int parts = m.parts;
-  // tiles of 16: the nodes of the panels, then the masses (those in a panel
-  // are passed over)
   const unsigned inside = panels & ~kSingles;
   const int n_node = N * __builtin_popcount(inside);
-  const int n_tiles = n_node / 16 + ((panels & kSingles) ? ((int)g.n_m + 15) / 16 : 0);
+  const int n_tiles = node_tiles(g, panels);
   const int n_chunks = (n_grp + kChunk - 1) / kChunk;
   const int mine = lane & 15;
   // delta of entry e of the tiles and its place in the row of values; false:
@@ -318,28 +340,50 @@ __device__ __forceinline__ void node_values(const GridArgs &g, const MassPlan &m
     d = b < (int)g.n_m ? g.m2[b] + g.k2 : 1.0;
     return b < (int)g.n_m && slot_of(g.sig * d, inside) < 0;
   };
-  for (int t0 = 0; t0 < n_tiles; t0 += kNodeWaves * kWaveTiles) {
-    // lane group r = lane / 16 holds sum r of the wave's masses
-    double x[kWaveTiles], acc[kWaveTiles];
-    bool any[kWaveTiles], some = false;
-#pragma unroll
-    for (int q = 0; q < kWaveTiles; ++q) {
+  int t0 = 0;  // first tile of the pass
+  do {
+    // x of a lane in tile q of the wave, 1 where the coefficient form has nothing to
+    // evaluate; some: it has for a lane
+    auto x_of = [&](int q, bool &some) {
       const int t = t0 + kNodeWaves * q + wave;
       double d;
       const bool want = t < n_tiles && entry(16 * t + mine, d);
       const double xs = want ? g.sig * d : 0.0;
       const bool in = table && fold_m_ok<G, E>(xs);
-      any[q] = __builtin_amdgcn_ballot_w64(in) != 0;
-      some |= any[q];
-      x[q] = in ? xs : 1.0;
-      acc[q] = 0.0;
+      some = __builtin_amdgcn_ballot_w64(in) != 0;
+      return in ? xs : 1.0;
+    };
+    const int n_q = MANY ? (min(m.pass, n_tiles - t0) - wave + kNodeWaves - 1) / kNodeWaves
+                         : kWaveTiles;
+    // lane group r = lane / 16 holds sum r of the wave's masses
+    double x[kWaveTiles], acc[kWaveTiles];
+    bool any[kWaveTiles];
+    unsigned todo = 0;  // tiles with something to evaluate
+    if constexpr (MANY) {
+#pragma unroll 1
+      for (int q = 0; q < n_q; ++q) {
+        bool some;
+        (void)x_of(q, some);
+        todo |= some ? 1u << q : 0u;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < kWaveTiles; ++q) {
+        x[q] = x_of(q, any[q]);
+        todo |= any[q];
+        acc[q] = 0.0;
+      }
     }
+    // lane's sum of tile q of the wave in memory
+    auto spilled = [&](int q) {
+      return m.spill + ((int64_t)blockIdx.x * m.pass + kNodeWaves * q + wave) * kWave + lane;
+    };
     // a pass with nodes is built for a momentum inside the coefficient form; one
     // of masses alone if any of them is
     bool build = table && 16 * t0 < n_node;  // workgroup-uniform
     if (table && !build) {
       unsigned *sh = reinterpret_cast<unsigned *>(lC);
-      if (lane == 0) sh[wave] = some;
+      if (lane == 0) sh[wave] = todo;
       __syncthreads();
 #pragma unroll
       for (int w = 0; w < kNodeWaves; ++w) build |= sh[w] != 0;
@@ -367,14 +411,10 @@ __device__ __forceinline__ void node_values(const GridArgs &g, const MassPlan &m
         if (ew < live) expand(c * kChunk + ew, lC + ew * kRows * kWave + lane, lane);
         __builtin_amdgcn_s_setprio(0);
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kWaveTiles; ++q) {
-          if (!any[q]) continue;  // wave-uniform
-          // the powers of x are formed again for each chunk: kept over the
-          // build they would cost it its registers
-          asm volatile("" : "+v"(x[q]));
+        // the chunk's part of sum c mod 4 of the masses at xq
+        auto chunk_sum = [&](double xq) {
           double v[MfmaShape<G, E>::kP];
-          mfma_powers<G, E>(x[q], lane, v);
+          mfma_powers<G, E>(xq, lane, v);
           double tot = 0.0;
 #pragma unroll 1
           for (int gl = 0; gl < live; ++gl) {
@@ -383,16 +423,34 @@ __device__ __forceinline__ void node_values(const GridArgs &g, const MassPlan &m
             mfma_slice_pair<G, E, true>(grp, lane, v, 2, 3, tot);
           }
           tot = swap_add<32>(tot, tot);
-          tot = swap_add<16>(tot, tot);
-          acc[q] += lane >> 4 == (c & 3) ? tot : 0.0;
+          return swap_add<16>(tot, tot);
+        };
+        if constexpr (MANY) {
+#pragma unroll 1
+          for (unsigned left = todo; left; left &= left - 1u) {  // wave-uniform
+            const int q = __builtin_ctz(left);
+            bool some;
+            const double tot = chunk_sum(x_of(q, some));
+            double *sum = spilled(q);
+            if (lane >> 4 == (c & 3)) *sum = c < 4 ? tot : *sum + tot;
+          }
+        } else {
+#pragma unroll
+          for (int q = 0; q < kWaveTiles; ++q) {
+            if (!any[q]) continue;  // wave-uniform
+            // the powers of x are formed again for each chunk: kept over the
+            // build they would cost it its registers
+            asm volatile("" : "+v"(x[q]));
+            const double tot = chunk_sum(x[q]);
+            acc[q] += lane >> 4 == (c & 3) ? tot : 0.0;
+          }
         }
         __syncthreads();  // the chunk is consumed
       }
     }
-#pragma unroll
-    for (int q = 0; q < kWaveTiles; ++q) {
+    auto store = [&](int q, double sums) {
       const int t = t0 + kNodeWaves * q + wave;
-      if (t >= n_tiles) continue;  // wave-uniform
+      if (t >= n_tiles) return;  // wave-uniform
       const int e = 16 * t + mine;
       double d;
       const bool want = entry(e, d);
@@ -401,7 +459,7 @@ __device__ __forceinline__ void node_values(const GridArgs &g, const MassPlan &m
       double s[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        s[r] = __shfl(acc[q], 16 * r + mine, kWave);
+        s[r] = __shfl(sums, 16 * r + mine, kWave);
         if (!in) s[r] = 0.0;
       }
       if (part == 0) {  // workgroup-uniform
@@ -426,8 +484,19 @@ __device__ __forceinline__ void node_values(const GridArgs &g, const MassPlan &m
             if ((r & (parts - 1)) == part) dst[r * m.plane] = s[r];
         }
       }
+    };
+    if constexpr (MANY) {
+      // sums of this part that have a chunk
+      const int r = lane >> 4;
+      const bool has = build && r < n_chunks && (r & (parts - 1)) == part;
+#pragma unroll 1
+      for (int q = 0; q < n_q; ++q)
+        store(q, has && ((todo >> q) & 1u) ? *spilled(q) : 0.0);
+    } else {
+#pragma unroll
+      for (int q = 0; q < kWaveTiles; ++q) store(q, acc[q]);
     }
-  }
+  } while (MANY && (t0 += m.pass) < n_tiles);
 }
 
 // LDS of the node kernels: chunk | regulator table | the rule's tables.
@@ -457,65 +526,71 @@ __global__ __launch_bounds__(64 * kNodeWaves, 4) void grid_nodes_kernel(GridArgs
   }
   __syncthreads();
   const int64_t n_work = g.n_p * m.parts;
-  for (int64_t w = blockIdx.x; w < n_work; w += n_blocks) {
-    const int64_t a = w >> __builtin_ctz(m.parts);  // parts: 1, 2 or 4
-    const int part = (int)w & (m.parts - 1);
-    const double p = g.p[a];
-    const bool p_ok = p >= 0.0;
-    const bool table = p_ok && fold_p_ok<G>(p, g);  // workgroup-uniform
-    const int rsh = __builtin_ctz(g.R);
-    struct Row {
-      double a, b;       // s = a + b (1 + x_j)
-      const double *lo;  // 1 + x_j of the row's term 0; term k at lo[J k]
-      bool live;
-    };
-    auto lane_row = [&](int gg, int l) {
-      const int t = gg / fs.NG, gi = gg - t * fs.NG;  // scalar
-      const int i = (l & (g.R - 1)) + g.R * t;
-      const double q = g.tab[min(i, n_r - 1)];
-      const double qm = q - p;
-      return Row{qm * qm, (2.0 * q) * p, lo + (l >> rsh) + g.J * gi * G, i < n_r};
-    };
-    auto fill = [&](const Row &r, int k) {
-      const double o = r.lo[g.J * k];  // padded terms: 1 + x_j = -1
-      const double H = hk_build<REG>(g, fmax(__builtin_fma(r.b, o, r.a), 0.0), ht);
-      return r.live && o >= 0.0 ? H : 0.0;
-    };
-    auto expand = [&](int gg, double *col, int l) {
-      const int t = gg / fs.NG, gi = gg - t * fs.NG;
-      const int i = (l & (g.R - 1)) + g.R * t, ic = min(i, n_r - 1);
-      const double Hq = i < n_r ? g.sig * g.tab[2 * n_r + ic] : 0.0;
-      const double c = i < n_r ? g.kap * g.tab[n_r + ic] : 0.0;  // 0: the row adds nothing
-      const double f[2] = {Hq, Hq};
-      const double *mu = lm + (l >> rsh) + g.J * gi * G;
-      expand_group<G, 2>(col, f, c, [&](int k) { return mu[g.J * k]; });
-    };
-    // every term on its own, for masses or momenta outside the coefficient form
-    auto single = [&](double delta) {
-      const int l = threadIdx.x & (kWave - 1);
-      double total = 0.0;
-#pragma unroll 1
-      for (int t = 0; t < g.T; ++t) {
+  auto run = [&](auto many) {
+    for (int64_t w = blockIdx.x; w < n_work; w += n_blocks) {
+      const int64_t a = w >> __builtin_ctz(m.parts);  // parts: 1, 2 or 4
+      const int part = (int)w & (m.parts - 1);
+      const double p = g.p[a];
+      const bool p_ok = p >= 0.0;
+      const bool table = p_ok && fold_p_ok<G>(p, g);  // workgroup-uniform
+      const int rsh = __builtin_ctz(g.R);
+      struct Row {
+        double a, b;       // s = a + b (1 + x_j)
+        const double *lo;  // 1 + x_j of the row's term 0; term k at lo[J k]
+        bool live;
+      };
+      auto lane_row = [&](int gg, int l) {
+        const int t = gg / fs.NG, gi = gg - t * fs.NG;  // scalar
+        const int i = (l & (g.R - 1)) + g.R * t;
+        const double q = g.tab[min(i, n_r - 1)];
+        const double qm = q - p;
+        return Row{qm * qm, (2.0 * q) * p, lo + (l >> rsh) + g.J * gi * G, i < n_r};
+      };
+      auto fill = [&](const Row &r, int k) {
+        const double o = r.lo[g.J * k];  // padded terms: 1 + x_j = -1
+        const double H = hk_build<REG>(g, fmax(__builtin_fma(r.b, o, r.a), 0.0), ht);
+        return r.live && o >= 0.0 ? H : 0.0;
+      };
+      auto expand = [&](int gg, double *col, int l) {
+        const int t = gg / fs.NG, gi = gg - t * fs.NG;
         const int i = (l & (g.R - 1)) + g.R * t, ic = min(i, n_r - 1);
-        const double Gq = rcp64(g.tab[2 * n_r + ic] + delta);
-        const double A = i < n_r ? (g.tab[n_r + ic] * Gq) * Gq : 0.0;
-        double inner = 0.0;
-#pragma unroll 1
-        for (int gi = 0; gi < fs.NG; ++gi) {
-          const Row r = lane_row(t * fs.NG + gi, l);
-#pragma unroll 1
-          for (int k = 0; k < G; ++k) {
-            const double mu = lm[(l >> rsh) + g.J * (gi * G + k)];
-            if (mu > 0.0) inner = __builtin_fma(mu, rcp64(fill(r, k) / g.sig + delta), inner);
+        const double Hq = i < n_r ? g.sig * g.tab[2 * n_r + ic] : 0.0;
+        const double c = i < n_r ? g.kap * g.tab[n_r + ic] : 0.0;  // 0: the row adds nothing
+        const double f[2] = {Hq, Hq};
+        const double *mu = lm + (l >> rsh) + g.J * gi * G;
+        expand_group<G, 2>(col, f, c, [&](int k) { return mu[g.J * k]; });
+      };
+      // every term on its own, for masses or momenta outside the coefficient form
+      auto single = [&](double delta) {
+        const int l = threadIdx.x & (kWave - 1);
+        double total = 0.0;
+  #pragma unroll 1
+        for (int t = 0; t < g.T; ++t) {
+          const int i = (l & (g.R - 1)) + g.R * t, ic = min(i, n_r - 1);
+          const double Gq = rcp64(g.tab[2 * n_r + ic] + delta);
+          const double A = i < n_r ? (g.tab[n_r + ic] * Gq) * Gq : 0.0;
+          double inner = 0.0;
+  #pragma unroll 1
+          for (int gi = 0; gi < fs.NG; ++gi) {
+            const Row r = lane_row(t * fs.NG + gi, l);
+  #pragma unroll 1
+            for (int k = 0; k < G; ++k) {
+              const double mu = lm[(l >> rsh) + g.J * (gi * G + k)];
+              if (mu > 0.0) inner = __builtin_fma(mu, rcp64(fill(r, k) / g.sig + delta), inner);
+            }
           }
+          total = __builtin_fma(A, inner, total);
         }
-        total = __builtin_fma(A, inner, total);
-      }
-      return total;
-    };
-    node_values<G, 2>(g, m, lC, a, part, panels, p_ok, table, g.T * fs.NG, lane_row, fill,
-                      expand, single);
-  }
+        return total;
+      };
+      node_values<G, 2, many.value>(g, m, lC, a, part, panels, p_ok, table, g.T * fs.NG,
+                                    lane_row, fill, expand, single);
+    }
+  };
+  if (__builtin_expect(node_tiles(g, panels) <= kMassRegTiles, 1))
+    run(std::false_type{});
+  else
+    run(std::true_type{});
 }
 
 // As grid_nodes_kernel for the vertex diagram: lane rows are (radial, polar)
@@ -552,74 +627,80 @@ __global__ __launch_bounds__(64 * kNodeWaves, 4) void vertex_nodes_kernel(GridAr
   }
   __syncthreads();
   const int64_t n_work = g.n_p * m.parts;
-  for (int64_t w = blockIdx.x; w < n_work; w += n_blocks) {
-    const int64_t a = w >> __builtin_ctz(m.parts);  // parts: 1, 2 or 4
-    const int part = (int)w & (m.parts - 1);
-    const double p1 = g.p[a], p2 = g.p2[a], ct = g.c12[a];
-    const bool p_ok = p1 >= 0.0 && p2 >= 0.0 && ct >= -1.0 && ct <= 1.0;
-    const double st = p_ok ? sqrt((1.0 - ct) * (1.0 + ct)) : 0.0;
-    const bool table = p_ok && fold_p_ok<G, 3>(fmax(p1, p2), g);
-    const int n_pairs = n_r * n_a;
-    struct Row {
-      double q, x, sx;  // q_i, x_j, sqrt(1 - x_j^2) of the lane row's pair
-      int az;           // azimuthal node of its term 0
-      bool live;
-    };
-    auto lane_row = [&](int gg, int l) {
-      const int t = gg / fs.NG, gi = gg - t * fs.NG;
-      const int pi = min(l + kWave * t, n_pairs - 1);
-      const int i = pi / n_a, j = pi - i * n_a;
-      return Row{g.tab[i], lx[j], lsx[j], gi * G, l + kWave * t < n_pairs};
-    };
-    auto fill = [&](const Row &r, int k) {
-      const int az = r.az + k;
-      const double s2 = vertex_s2<REG>(r.q, p2, r.x, r.sx, lcp[az], ct, st);
-      const double H = hk_build<REG>(g, s2, ht);
-      return r.live && az < n_phi ? H : 0.0;
-    };
-    auto expand = [&](int gg, double *col, int l) {
-      const int t = gg / fs.NG, gi = gg - t * fs.NG;
-      const bool vp = l + kWave * t < n_pairs;
-      const int pi = min(l + kWave * t, n_pairs - 1);
-      const int i = pi / n_a, j = pi - i * n_a;
-      const double q = g.tab[i];
-      const double s1 = fmax((q * q + p1 * p1) + (2.0 * q) * p1 * lx[j], 0.0);
-      const double Hq = vp ? g.sig * g.tab[2 * n_r + i] : 0.0;
-      const double f[3] = {Hq, Hq, vp ? hk_build<REG>(g, s1, ht) : 0.0};
-      const double c = vp ? (g.kap * g.tab[n_r + i]) * lm[j] : 0.0;  // 0: the row adds nothing
-      const double *nu = lnu + gi * G;
-      expand_group<G, 3>(col, f, c, [&](int k) { return nu[k]; });
-    };
-    auto single = [&](double delta) {
-      const int l = threadIdx.x & (kWave - 1);
-      double total = 0.0;
-#pragma unroll 1
-      for (int t = 0; t < g.T; ++t) {
+  auto run = [&](auto many) {
+    for (int64_t w = blockIdx.x; w < n_work; w += n_blocks) {
+      const int64_t a = w >> __builtin_ctz(m.parts);  // parts: 1, 2 or 4
+      const int part = (int)w & (m.parts - 1);
+      const double p1 = g.p[a], p2 = g.p2[a], ct = g.c12[a];
+      const bool p_ok = p1 >= 0.0 && p2 >= 0.0 && ct >= -1.0 && ct <= 1.0;
+      const double st = p_ok ? sqrt((1.0 - ct) * (1.0 + ct)) : 0.0;
+      const bool table = p_ok && fold_p_ok<G, 3>(fmax(p1, p2), g);
+      const int n_pairs = n_r * n_a;
+      struct Row {
+        double q, x, sx;  // q_i, x_j, sqrt(1 - x_j^2) of the lane row's pair
+        int az;           // azimuthal node of its term 0
+        bool live;
+      };
+      auto lane_row = [&](int gg, int l) {
+        const int t = gg / fs.NG, gi = gg - t * fs.NG;
+        const int pi = min(l + kWave * t, n_pairs - 1);
+        const int i = pi / n_a, j = pi - i * n_a;
+        return Row{g.tab[i], lx[j], lsx[j], gi * G, l + kWave * t < n_pairs};
+      };
+      auto fill = [&](const Row &r, int k) {
+        const int az = r.az + k;
+        const double s2 = vertex_s2<REG>(r.q, p2, r.x, r.sx, lcp[az], ct, st);
+        const double H = hk_build<REG>(g, s2, ht);
+        return r.live && az < n_phi ? H : 0.0;
+      };
+      auto expand = [&](int gg, double *col, int l) {
+        const int t = gg / fs.NG, gi = gg - t * fs.NG;
         const bool vp = l + kWave * t < n_pairs;
         const int pi = min(l + kWave * t, n_pairs - 1);
         const int i = pi / n_a, j = pi - i * n_a;
         const double q = g.tab[i];
-        const double Gq = rcp64(g.tab[2 * n_r + i] + delta);
-        const double A = vp ? (g.tab[n_r + i] * Gq) * Gq : 0.0;
         const double s1 = fmax((q * q + p1 * p1) + (2.0 * q) * p1 * lx[j], 0.0);
-        const double G1 = rcp64(hk_build<REG>(g, s1, ht) / g.sig + delta);
-        double inner = 0.0;
-#pragma unroll 1
-        for (int gi = 0; gi < fs.NG; ++gi) {
-          const Row r = lane_row(t * fs.NG + gi, l);
-#pragma unroll 1
-          for (int k = 0; k < G; ++k) {
-            const double nu = lnu[gi * G + k];
-            if (nu > 0.0) inner = __builtin_fma(nu, rcp64(fill(r, k) / g.sig + delta), inner);
+        const double Hq = vp ? g.sig * g.tab[2 * n_r + i] : 0.0;
+        const double f[3] = {Hq, Hq, vp ? hk_build<REG>(g, s1, ht) : 0.0};
+        const double c = vp ? (g.kap * g.tab[n_r + i]) * lm[j] : 0.0;  // 0: the row adds nothing
+        const double *nu = lnu + gi * G;
+        expand_group<G, 3>(col, f, c, [&](int k) { return nu[k]; });
+      };
+      auto single = [&](double delta) {
+        const int l = threadIdx.x & (kWave - 1);
+        double total = 0.0;
+  #pragma unroll 1
+        for (int t = 0; t < g.T; ++t) {
+          const bool vp = l + kWave * t < n_pairs;
+          const int pi = min(l + kWave * t, n_pairs - 1);
+          const int i = pi / n_a, j = pi - i * n_a;
+          const double q = g.tab[i];
+          const double Gq = rcp64(g.tab[2 * n_r + i] + delta);
+          const double A = vp ? (g.tab[n_r + i] * Gq) * Gq : 0.0;
+          const double s1 = fmax((q * q + p1 * p1) + (2.0 * q) * p1 * lx[j], 0.0);
+          const double G1 = rcp64(hk_build<REG>(g, s1, ht) / g.sig + delta);
+          double inner = 0.0;
+  #pragma unroll 1
+          for (int gi = 0; gi < fs.NG; ++gi) {
+            const Row r = lane_row(t * fs.NG + gi, l);
+  #pragma unroll 1
+            for (int k = 0; k < G; ++k) {
+              const double nu = lnu[gi * G + k];
+              if (nu > 0.0) inner = __builtin_fma(nu, rcp64(fill(r, k) / g.sig + delta), inner);
+            }
           }
+          total = __builtin_fma((A * lm[j]) * G1, inner, total);
         }
-        total = __builtin_fma((A * lm[j]) * G1, inner, total);
-      }
-      return total;
-    };
-    node_values<G, 3>(g, m, lC, a, part, panels, p_ok, table, g.T * fs.NG, lane_row, fill,
-                      expand, single);
-  }
+        return total;
+      };
+      node_values<G, 3, many.value>(g, m, lC, a, part, panels, p_ok, table, g.T * fs.NG,
+                                    lane_row, fill, expand, single);
+    }
+  };
+  if (__builtin_expect(node_tiles(g, panels) <= kMassRegTiles, 1))
+    run(std::false_type{});
+  else
+    run(std::true_type{});
 }
 
 // out[a, b] = pref_c sum_n L[b][n] val[a][slot_b N + n] for the masses b of a
@@ -733,6 +814,10 @@ int mass_nodes_parts(int64_t n_p, int n_cu) {
   return n_p <= n_cu ? 4 : n_p <= 2 * (int64_t)n_cu ? 2 : 1;
 }
 
+int mass_nodes_blocks(int64_t n_p, int parts, int n_cu) {
+  return (int)std::min<int64_t>(n_p * parts, 4 * (int64_t)n_cu);
+}
+
 int launch_mass_nodes(const GridArgs &g, MassPlan m, int reg, bool vertex, bool first, int n_cu,
                       void *stream) {
   if (g.n_p <= 0 || g.n_m <= 0) return 0;
@@ -740,7 +825,7 @@ int launch_mass_nodes(const GridArgs &g, MassPlan m, int reg, bool vertex, bool 
   hipStream_t st = (hipStream_t)stream;
   const int lds = mass_nodes_lds(g, reg, vertex);
   if (lds > 160 * 1024) return (int)hipErrorInvalidValue;
-  const int blocks = (int)std::min<int64_t>(g.n_p * m.parts, 4 * (int64_t)n_cu);
+  const int blocks = mass_nodes_blocks(g.n_p, m.parts, n_cu);
   if (vertex) {
     if (reg == kExp)
       nodes_reg<true, kExp>(g, m, blocks, lds, st);
