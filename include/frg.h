@@ -89,7 +89,10 @@ typedef struct frg_ctx frg_ctx;
  * buffers) and, beside them, the flow server's flow state.  A call whose
  * buffers would exceed it returns FRG_E_NOMEM without launching its kernels;
  * a flow that does not fit beside the context's buffers is refused at
- * submission.  Tables, work lists and staging buffers are owned by the
+ * submission.  Buffers that only make a call faster (interpolated grids, tables
+ * of radial sums) take at most a 64th of the budget each; those of grids are given
+ * back to a call that needs their room, and where they find none the call takes
+ * its other form.  Tables, work lists and staging buffers are owned by the
  * context and freed by frg_destroy. */
 int frg_create(frg_ctx **out, int hip_device, uint64_t hbm_budget_bytes);
 

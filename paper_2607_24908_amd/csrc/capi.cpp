@@ -48,7 +48,7 @@ DevBuf::~DevBuf() { release(); }
 void DevBuf::release() {
   if (ptr) {
     hipFree(ptr);
-    if (acct) acct->used -= bytes;
+    if (acct) (optional ? acct->extra : acct->used) -= bytes;
   }
   ptr = nullptr;
   bytes = 0;
@@ -56,19 +56,26 @@ void DevBuf::release() {
 int DevBuf::reserve(size_t b) {
   if (b <= bytes) return FRG_OK;
   const size_t nb = std::max<size_t>(b, 256);
-  if (acct && acct->used.load() - bytes + nb > acct->budget)
+  auto over = [&] { return acct && acct->used + acct->extra - bytes + nb > acct->budget; };
+  if (over() && !optional && acct->give_back) acct->give_back();
+  if (over())
     return fail(FRG_E_NOMEM,
                 "a buffer of %zu B would take the context's device buffers (%llu B) beyond its "
                 "HBM budget (%llu B)",
                 nb, (unsigned long long)acct->used.load(), (unsigned long long)acct->budget);
   release();
   hipError_t e = hipMalloc(&ptr, nb);
+  if (e != hipSuccess && acct && acct->extra && !optional) {
+    acct->give_back();
+    e = hipMalloc(&ptr, nb);
+  }
   if (e != hipSuccess) {
     ptr = nullptr;
+    (void)hipGetLastError();  // it is no launch's
     return fail(FRG_E_NOMEM, "hipMalloc(%zu): %s", nb, hipGetErrorString(e));
   }
   bytes = nb;
-  if (acct) acct->used += nb;
+  if (acct) (optional ? acct->extra : acct->used) += nb;
   return FRG_OK;
 }
 
@@ -198,18 +205,15 @@ int Ctx::fv_panels(int d, int reg, int n_r, double qmk, const double **dev) {
   LEntry &ent = ltabs.at(std::make_tuple(d, reg, n_r, dbits(qmk)));
   if (!ent.panels_asked) {
     const size_t bytes = sizeof(double) * kFvTable;
-    if (!hbm.spare(bytes)) {  // decided once: the rule's results keep their bits
-      ent.panels_asked = true;
-      *dev = nullptr;
-      return FRG_OK;
-    }
     auto buf = std::make_unique<DevBuf>(&hbm);
-    int rc = buf->reserve(bytes);
-    if (rc) return rc;
-    const std::vector<double> t = build_fv_panels(ent.host);
-    hipError_t e = hipMemcpy(buf->ptr, t.data(), bytes, hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "upload radial-sum panels");
-    ent.panels = std::move(buf);
+    if (panel_bytes + bytes <= hbm.share() && buf->reserve(bytes) == FRG_OK) {
+      const std::vector<double> t = build_fv_panels(ent.host);
+      hipError_t e = hipMemcpy(buf->ptr, t.data(), bytes, hipMemcpyHostToDevice);
+      if (e != hipSuccess) return hip_fail(e, "upload radial-sum panels");
+      ent.panels = std::move(buf);
+      panel_bytes += bytes;
+    }
+    clear_error();
     ent.panels_asked = true;
   }
   *dev = ent.panels ? (const double *)ent.panels->ptr : nullptr;
@@ -634,9 +638,10 @@ int Ctx::grid_launch(GridArgs g, int reg, const GridCfg &cfg_in, hipStream_t st)
 //     direct form, whose build nothing overlaps) and there are at most a
 //     quarter as many configurations as CUs: 64 x 128 masses 24.3 against
 //     28.8 us, 16 x 512 21.5 against 36.0 us;
-//   - the buffers fit the HBM budget, and the stream is not being captured
-//     (the buffers are the context's, ordered between streams by an event
-//     that a capture cannot wait for).
+//   - the buffers of a batch that fills the chip are at most the share of the HBM
+//     budget for such forms (5 to 80 MB, at most 155), and the
+//     stream is not being captured (the buffers are the context's, ordered between
+//     streams by an event that a capture cannot wait for).
 constexpr int64_t kMassMin = 128, kMassMax = 8192;
 constexpr double kMassWork = 2.5e8;
 constexpr size_t kMassValBytes = (size_t)64 << 20;
@@ -661,19 +666,19 @@ int Ctx::mass_nodes_launch(const GridArgs &g_in, int reg, bool vertex, bool big_
          ((g.n_m + 31) & ~(int64_t)31);
   m.pass = (int)std::min<int64_t>(kMassPassTiles, (m.ld / 16 + 3) & ~(int64_t)3);
   m.parts = mass_nodes_parts(g.n_p, n_cu);
-  const int64_t batch = std::min<int64_t>(
-      g.n_p, std::max<int64_t>(64, (int64_t)(kMassValBytes / (sizeof(double) * m.ld))));
-  m.plane = batch * m.ld;
   const size_t o_lag = 256;
-  const size_t o_val = o_lag + sizeof(double) * kMassNodes * g.n_m;
-  const size_t o_spill = o_val + sizeof(double) * (size_t)m.plane * (m.parts > 1 ? 4 : 1);
-  const size_t bytes = o_spill + sizeof(double) * kWave * m.pass *
-                                     mass_nodes_blocks(batch, m.parts, n_cu);
+  const size_t o_spill = o_lag + sizeof(double) * kMassNodes * g.n_m;
+  const size_t o_val = o_spill + sizeof(double) * kWave * m.pass *
+                                     mass_nodes_blocks(g.n_p, m.parts, n_cu);
+  const size_t per = sizeof(double) * m.ld * (m.parts > 1 ? 4 : 1);  // of one momentum
+  const size_t want = std::max(kMassValBytes * (m.parts > 1 ? 4 : 1), per * 4 * n_cu);
+  const size_t share = std::min<uint64_t>(hbm.share(), o_val + want);
+  const int64_t batch = share > o_val ? std::min<int64_t>(g.n_p, (int64_t)((share - o_val) / per)) : 0;
+  if (batch < std::min<int64_t>(g.n_p, 4 * n_cu)) return 0;  // does not fill the chip
+  m.plane = batch * m.ld;
+  const size_t bytes = o_val + per * batch;
   const size_t node_doubles = 5 * kMassNodes, reg_doubles = (size_t)kRegPanels * kRegCoef;
   const size_t node_bytes = sizeof(double) * (node_doubles + reg_doubles);
-  size_t more = mass_nodes.bytes ? 0 : node_bytes;
-  if (mass_scr.bytes < bytes) more += bytes - mass_scr.bytes;
-  if (!hbm.spare(more)) return 0;
   if (!mass_done && hipEventCreateWithFlags(&mass_done, hipEventDisableTiming) != hipSuccess) {
     mass_done = nullptr;
     return fail(FRG_E_DEVICE, "hipEventCreate");
@@ -682,8 +687,10 @@ int Ctx::mass_nodes_launch(const GridArgs &g_in, int reg, bool vertex, bool big_
     std::vector<double> t = build_mass_nodes();
     const std::vector<double> r = build_regulator_table();
     t.insert(t.end(), r.begin(), r.end());
-    int rc = mass_nodes.reserve(node_bytes);
-    if (rc) return rc;
+    if (mass_nodes.reserve(node_bytes)) {
+      clear_error();
+      return 0;
+    }
     hipError_t e = hipMemcpy(mass_nodes.ptr, t.data(), node_bytes, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
       mass_nodes.release();
@@ -691,8 +698,10 @@ int Ctx::mass_nodes_launch(const GridArgs &g_in, int reg, bool vertex, bool big_
     }
   }
   if (mass_scr.bytes < bytes) hipEventSynchronize(mass_done);
-  int rc = mass_scr.reserve(bytes);
-  if (rc) return rc;
+  if (mass_scr.reserve(bytes)) {
+    clear_error();
+    return 0;
+  }
   hipError_t he = hipStreamWaitEvent(st, mass_done, 0);
   if (he != hipSuccess) return hip_fail(he, "hipStreamWaitEvent");
   char *base = (char *)mass_scr.ptr;
@@ -1014,6 +1023,10 @@ int frg_create(frg_ctx **out, int hip_device, uint64_t hbm_budget_bytes) {
   hipMemGetInfo(&free_b, &total_b);
   c->hbm_budget = hbm_budget_bytes ? hbm_budget_bytes : free_b / 2;
   c->hbm.budget = c->hbm_budget;
+  c->hbm.give_back = [p = c.get()] {  // every user holds the context's lock
+    if (p->mass_done) hipEventSynchronize(p->mass_done);
+    p->mass_scr.release();
+  };
   c->tune.load_env();
   *out = c.release();
   clear_error();

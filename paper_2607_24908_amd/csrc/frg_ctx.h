@@ -5,6 +5,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include <atomic>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -43,22 +44,25 @@ bool any_fp32c(const std::vector<SetDev> &sd);
 // against its HBM budget.
 struct HbmAccount {
   std::atomic<uint64_t> used{0};
+  std::atomic<uint64_t> extra{0};  // of optional buffers, beside used
   uint64_t budget = ~0ull;
-  // Whether b more bytes, for a faster form of a call that has another one, take
-  // at most a 64th of what is free: so that no later call is refused for them.
-  bool spare(uint64_t b) const {
-    const uint64_t u = used.load();
-    return b == 0 || (u < budget && b <= (budget - u) / 64);
-  }
+  std::function<void()> give_back;  // frees the optional buffers
+  // What a faster form of a call that has another one may take for its buffers, and
+  // all tables of such forms together: of the budget, not of what is free, so that the
+  // form of a call (its last bits) does not hang on the calls before it.
+  uint64_t share() const { return budget / 64; }
 };
 
-// Grow-only device allocation, charged to an account when it has one.
+// Grow-only device allocation, charged to an account when it has one.  An optional
+// one is given back when another needs its room, in the budget or on the device;
+// where it has none itself it only returns FRG_E_NOMEM.
 struct DevBuf {
   void *ptr = nullptr;
   size_t bytes = 0;
   HbmAccount *acct = nullptr;
+  bool optional = false;
   DevBuf() = default;
-  explicit DevBuf(HbmAccount *a) : acct(a) {}
+  explicit DevBuf(HbmAccount *a, bool opt = false) : acct(a), optional(opt) {}
   DevBuf(const DevBuf &) = delete;
   DevBuf &operator=(const DevBuf &) = delete;
   ~DevBuf();
@@ -179,7 +183,8 @@ struct Context {
   frg::DevBuf tab_part{&hbm}, tab_terms{&hbm}, tab_offs{&hbm}, tab_scr{&hbm};
   // mass nodes (mass_nodes.hip): constants; Lagrange rows and values of the
   // last call, ordered between streams by mass_done
-  frg::DevBuf mass_nodes{&hbm}, mass_scr{&hbm};
+  frg::DevBuf mass_nodes{&hbm}, mass_scr{&hbm, true};
+  uint64_t panel_bytes = 0;  // of all LEntry::panels
   hipEvent_t mass_done = nullptr;
   hipEvent_t tab_done = nullptr;   // after the last segmented launch (which used them)
   frg::Tune tune;
@@ -195,7 +200,7 @@ struct Context {
     double Cd = 0.0;
     frg::LpaTable host;
     std::unique_ptr<frg::DevBuf> panels;  // build_fv_panels, from the first call that asks
-    bool panels_asked = false;            // ... null then: the budget could not spare them
+    bool panels_asked = false;            // ... null then: there was no room for them
   };
   std::map<std::tuple<int, int, uint64_t, uint64_t, int, int>, QEntry> qtabs;
   std::map<std::tuple<int, int, int, uint64_t>, LEntry> ltabs;
@@ -209,7 +214,7 @@ struct Context {
                  frg::QuadTable **host_ref = nullptr);
   int lpa_table(int d, int reg, int n_r, double qmk, const double **dev, double *Cd);
   // polynomial panels of the radial sums for a table lpa_table has made; null where
-  // the memory budget cannot spare them
+  // there is no room for them, decided once, so that a rule's results keep their bits
   int fv_panels(int d, int reg, int n_r, double qmk, const double **dev);
   int make_setdev(const frg_set &s, frg::SetDev *out);
   void fill_setdev(const frg_set &s, const frg::QuadTable &h, const double *tab, frg::SetDev *out);

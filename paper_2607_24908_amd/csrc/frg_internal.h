@@ -384,7 +384,7 @@ struct MassPlan {
 };
 int mass_nodes_parts(int64_t n_p, int n_cu);
 int mass_nodes_blocks(int64_t n_p, int parts, int n_cu);  // workgroups of a batch
-constexpr int kMassRegTiles = 8, kMassPassTiles = 64;
+constexpr int kMassRegTiles = 8, kMassPassTiles = 24;  // 24: every panel's
 // first: the first batch of momenta of the call (also forms the Lagrange rows)
 int launch_mass_nodes(const GridArgs &g, MassPlan m, int reg, bool vertex, bool first, int n_cu,
                       void *stream);

@@ -542,6 +542,10 @@ int frg_submit(frg_ctx *ctx, const frg_request *req, uint64_t *ticket) {
     s = ctx->server;
   }
   const int64_t bytes = frg_flow_footprint(&req->lpa);
+  {
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    if ((uint64_t)bytes + ctx->hbm.used + ctx->hbm.extra > s->budget) ctx->hbm.give_back();
+  }
   std::lock_guard<std::mutex> lk(s->m);
   if ((uint64_t)bytes + ctx->hbm.used.load() > s->budget)
     return fail(FRG_E_NOMEM, "flow footprint %lld B and the context's buffers exceed the HBM budget",
