@@ -557,38 +557,50 @@ __device__ __forceinline__ void fd_coef(int64_t j, int64_t n, int o, double i2, 
   *c2 = b;
 }
 
-// s1 and s2 of the lanes that `far` names, from the radial nodes: every such lane its
+struct LpaSums {
+  double s1[2], s2[2];
+};
+// The sums of the lanes whose masses x are not both in the panels: from the whole table
+// where that covers them (fv_covered), else from the radial nodes: every such lane its
 // own sums (kLpaNode cycles per node), or the wave one such lane after the other, its
 // 64 lanes the nodes (kLpaFold more for the sums over the lanes), whichever is less.
-__device__ __forceinline__ void lpa_sums(const LpaJob &jb, bool far, const double *x, double *s1,
-                                         double *s2) {
+// Every lane of the wave takes part.
+__device__ __forceinline__ LpaSums lpa_sums(const double *poly, const double *table, int n_r,
+                                         bool want, double xs, double xp) {
   const int lane = (int)threadIdx.x;
+  const double x[2] = {xs, xp};
+  LpaSums o{{0.0, 0.0}, {0.0, 0.0}};
+  int p[2];
+  bool far = want;
+  if (want && fv_covered<2>(poly, x, p)) {
+    fv_table_sums<2, true>(poly, x, p, o.s1, o.s2);
+    far = false;
+  }
+  // nodes through the scalar cache (uniform addresses, never written here)
+  const auto tab = (const __attribute__((address_space(4))) double *)table;
   unsigned long long todo = __builtin_amdgcn_ballot_w64(far);
-  if (__builtin_popcountll(todo) * lpa_wave_cost(jb.n_r) > kLpaNode * jb.n_r) {
+  if (__builtin_popcountll(todo) * lpa_wave_cost(n_r) > kLpaNode * n_r) {
     if (far) {
-      s1[0] = s2[0] = s1[1] = s2[1] = 0.0;
-      // nodes through the scalar cache (uniform addresses, never written here)
-      const auto tab = (const __attribute__((address_space(4))) double *)jb.tab;
 #pragma unroll 4
-      for (int i = 0; i < jb.n_r; ++i) {
-        const double c = tab[i], h = tab[jb.n_r + i];
+      for (int i = 0; i < n_r; ++i) {
+        const double c = tab[i], h = tab[n_r + i];
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
           const double g = rcp64(h + x[m]), cg = c * g;
-          s1[m] += cg;
-          s2[m] = __builtin_fma(cg, g, s2[m]);
+          o.s1[m] += cg;
+          o.s2[m] = __builtin_fma(cg, g, o.s2[m]);
         }
       }
     }
-    return;
+    return o;
   }
   for (; todo; todo &= todo - 1ull) {
     const int src = __builtin_ctzll(todo);  // wave-uniform
-    const double xs = readlane64(x[0], src), xp = readlane64(x[1], src);
+    const double us = readlane64(xs, src), up = readlane64(xp, src);
     double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int i = lane; i < jb.n_r; i += kWave) {
-      const double c = jb.tab[i], h = jb.tab[jb.n_r + i];
-      const double gs = rcp64(h + xs), gp = rcp64(h + xp);
+    for (int i = lane; i < n_r; i += kWave) {
+      const double c = table[i], h = table[n_r + i];
+      const double gs = rcp64(h + us), gp = rcp64(h + up);
       const double cs = c * gs, cp = c * gp;
       v[0] += cs;
       v[1] = __builtin_fma(cs, gs, v[1]);
@@ -598,12 +610,13 @@ __device__ __forceinline__ void lpa_sums(const LpaJob &jb, bool far, const doubl
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[k] = wave_sum(v[k]);
     if (lane == src) {
-      s1[0] = v[0];
-      s2[0] = v[1];
-      s1[1] = v[2];
-      s2[1] = v[3];
+      o.s1[0] = v[0];
+      o.s2[0] = v[1];
+      o.s1[1] = v[2];
+      o.s2[1] = v[3];
     }
   }
+  return o;
 }
 
 // LPA right-hand side and Jacobian bands for a batch of flows: one lane per grid
@@ -621,20 +634,24 @@ __device__ __forceinline__ void lpa_sums(const LpaJob &jb, bool far, const doubl
 // Python: 7.3 us with its masses in the panels or above them, 12.6 without a table
 // (113 us for the last two with a lane for all nodes of its point).
 template <bool HOST>
-__device__ __forceinline__ void lpa_point(const LpaJob &jb, int j_in) {
+__device__ __forceinline__ void lpa_point(const LpaJob &jb) {
   auto put = [](double *at, double v) {
     if constexpr (HOST)
       __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     else
       *at = v;
   };
-  const int n = jb.n;
-  const bool live = j_in < n;
+  // what the first loads need, in one trip to the scalar cache
+  const int n = jb.n, per = jb.per, block = jb.block;
+  const double *U = jb.U;
+  asm volatile("" ::"s"(n), "s"(per), "s"(block), "s"(U));
+  const int i = (int)threadIdx.x, j_in = ((int)blockIdx.x - block) * per + i;
+  const bool live = (i < per) & (j_in < n);
   const int j = min(j_in, n - 1);  // the other lanes help in lpa_sums
   const double dr = jb.dr;
   // four values of U from c, the points of j's formulas among them (n >= 4)
   const int c = min(max(j - 1, 0), n - 4);
-  const double u0 = jb.U[c], u1 = jb.U[c + 1], u2 = jb.U[c + 2], u3 = jb.U[c + 3];
+  const double u0 = U[c], u1 = U[c + 1], u2 = U[c + 2], u3 = U[c + 3];
   const bool last2 = j == n - 2;  // c = j - 2 there, else j - 1
   const double ul = last2 ? u1 : u0, um = last2 ? u2 : u1, ur = last2 ? u3 : u2;
   double d1 = ur - ul, d2 = (ur - 2.0 * um) + ul;
@@ -657,16 +674,17 @@ __device__ __forceinline__ void lpa_point(const LpaJob &jb, int j_in) {
   const double x[2] = {(ok ? ds : jb.k2) * jb.inv_k2, ((ok && pion) ? dp : jb.k2) * jb.inv_k2};
   const int p[2] = {fv_panel<kPanelLo>(x[0]), fv_panel<kPanelLo>(x[1])};
   double s1[2], s2[2];
-  int q[2];
-  bool far = false;
-  if (jb.poly && (unsigned)p[0] < (unsigned)kPanels && (unsigned)p[1] < (unsigned)kPanels) {
-    fv_poly<2, true>(jb.poly, x, p, s1, s2);
-  } else if (fv_covered<2>(jb.poly, x, q)) {
-    fv_table_sums<2, true>(jb.poly, x, q, s1, s2);
-  } else {
-    far = live;
+  const bool near = jb.poly && (unsigned)p[0] < (unsigned)kPanels &&
+                    (unsigned)p[1] < (unsigned)kPanels;
+  if (near) fv_poly<2, true>(jb.poly, x, p, s1, s2);
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(live && !near) != 0ull, 0)) {  // wave-uniform
+    const LpaSums o = lpa_sums(jb.poly, jb.tab, jb.n_r, live && !near, x[0], x[1]);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      s1[m] = near ? s1[m] : o.s1[m];
+      s2[m] = near ? s2[m] : o.s2[m];
+    }
   }
-  lpa_sums(jb, far, x, s1, s2);
   if (!live) return;
   const double F1s = jb.pre1 * s1[0];
   const double F2s = jb.pre2 * s2[0];
@@ -694,8 +712,7 @@ __device__ __forceinline__ void lpa_point(const LpaJob &jb, int j_in) {
 // (a release at system scope would write back the L2 in every workgroup).
 template <bool HOST>
 __device__ __forceinline__ void lpa_block(const LpaJob &jb, const LpaDone &done) {
-  const int i = (int)threadIdx.x;
-  lpa_point<HOST>(jb, i < jb.per ? ((int)blockIdx.x - jb.block) * jb.per + i : INT_MAX);
+  lpa_point<HOST>(jb);
   if constexpr (HOST) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);
