@@ -17,9 +17,10 @@
 //  3. tab_seg_reduce_kernel: the superchunks' partial sums, in order.
 //
 // Mapping: a momentum's run of a segment is taken by 16 lanes, on consecutive
-// terms, and folded over them; a wave takes four runs at a time.  The sum of
+// terms, and folded over them, four runs of a wave at a time; by all 64 lanes, one
+// run after the other, where the rule has many terms (tab_seg_wide).  The sum of
 // one result is fixed by the shapes: per segment, the run's terms split over
-// the 16 lanes by position, each lane's terms in order, the fixed fold; the
+// the lanes by position, each lane's terms in order, the fixed fold; the
 // segments of a superchunk added in order into part[superchunk][row][momentum];
 // the superchunks in order.  How momenta are split into items changes no bit.
 #include <hip/hip_runtime.h>
@@ -262,7 +263,19 @@ __device__ __forceinline__ double super_nodes(const TabArgs &a, int c, int n_seg
 // on one run (77 terms on average) 460 us, with 4 bytes per lane and copy
 // instruction in place of 16 474 us, with both 489 us.  More and smaller items
 // (8 per CU instead of 4) took 60 us longer: each one copies its segments again.
-template <bool PACKED>
+//
+// WIDE: all 64 lanes take one run, the wave's runs one after the other.  The costly
+// items of up to some 2000 momenta hold only a few per wave, so that of four groups of
+// 16 lanes some idle: 61 rows of 2^20 + 1 nodes, 1000 momenta, us per call with 16
+// and with 64 lanes: 64 x 32 nodes 326 and 374, 128 x 32 463 and 471, 128 x 48 611 and
+// 572, 128 x 128 1244 and 1042; 40 rows of 2^21 nodes, 200 momenta, 512 x 64 nodes: 750
+// and 526.  With more momenta 16 lanes stay ahead (64 rows, 5000 momenta, 128 x 48: 2322
+// and 2547 us, 128 x 128 4682 and 4726); the choice goes by the rule alone, so that a part
+// of the momenta gives the bits of all.
+constexpr int kWideTerms = 4608;
+bool tab_seg_wide(int n_r, int n_a) { return n_r * n_a > kWideTerms; }
+
+template <bool PACKED, bool WIDE>
 __global__ __launch_bounds__(kNT) void tab_seg_kernel(TabArgs a, const unsigned *hist,
                                                       const uint16_t *__restrict__ terms,
                                                       const int *__restrict__ offs, int *counter,
@@ -362,9 +375,9 @@ __global__ __launch_bounds__(kNT) void tab_seg_kernel(TabArgs a, const unsigned 
     const double pv = mine ? a.p[my] : -1.0;
     const bool live = pv >= 0.0;  // NaN and p < 0 have no terms
     const int *pof = offs + (mine ? my : 0) * (int64_t)(n_seg + 1);
-    // accumulators: lane 16 g + 4 r + s holds row r of the wave's momenta
-    // l = 4 t + g, t = s, s + 4, s + 8, s + 12 (acc[t / 4]), where the fold
-    // below leaves the row sums of a run
+    // accumulators, where the fold below leaves the row sums of a run: lane 16 g +
+    // 4 r + s holds row r of the wave's momenta l = 4 t + g, t = s, s + 4, s + 8, s + 12
+    // (acc[t / 4]); WIDE: lane 16 r + s that of l = s, s + 16, s + 32, s + 48 (acc[l / 16])
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     const int sg0 = c * kS, sg1 = min(sg0 + kS, n_seg);
     // copy segment sg of the batch's rows into buffer d: waves w, w + kRB, ...
@@ -404,6 +417,65 @@ __global__ __launch_bounds__(kNT) void tab_seg_kernel(TabArgs a, const unsigned 
       if (sg + 1 < sg1) load(sg + 1, cur ^ 1);
       const double *lg = lg0 + cur * kBufD;
       const int T0 = sg * kC;
+      // term e of the momentum p, onto the row sums in
+      auto term = [&](unsigned e, double p, double *in) {
+        int i, j;
+        if constexpr (PACKED) {
+          i = (int)(e >> 8);
+          j = (int)(e & 255u);
+        } else {
+          // e = i n_a + j (exact: e < 2^16, and e + 1/2 is at least
+          // 1/(2 n_a) away from a multiple of n_a)
+          i = (int)(((float)e + 0.5f) * inv_na);
+          j = (int)e - i * n_a;
+        }
+        const double *rad = lrad + i * kRS;
+        const double q = rad[0];
+        const double qm = q - p;
+        const double ah = (qm * qm) * a.inv_h;
+        const double bh = ((2.0 * q) * p) * a.inv_h;
+        const double t = fmin(__builtin_fma(bh, lang[2 * j], ah), a.t_last);
+        int k = (int)t;
+        k = k < k_last ? k : k_last;
+        const double f = t - (double)k;
+        const double mu = lang[2 * j + 1];
+        // k lies in the segment by construction; the clamp only keeps the
+        // LDS index in bounds
+        int x = k - T0;
+        x = x < 0 ? 0 : (x > kC - 1 ? kC - 1 : x);
+#pragma unroll
+        for (int r = 0; r < kRB; ++r) {
+          const double g0 = lg[r * kRowLds + x], g1 = lg[r * kRowLds + x + 1];
+          in[r] = __builtin_fma(rad[1 + r] * mu, __builtin_fma(f, g1 - g0, g0), in[r]);
+        }
+      };
+      if constexpr (WIDE) {
+        unsigned long long todo = __builtin_amdgcn_ballot_w64(live && o_nxt > o_cur);
+        while (todo) {  // wave-uniform: the momenta with terms in this segment
+          const int l = __builtin_ctzll(todo);
+          todo &= todo - 1ull;
+          const int end = __builtin_amdgcn_readlane(o_nxt, l);
+          const double p = readlane_d(pv, l);
+          const uint16_t *pt = terms + (p_lo + wave + (int64_t)kWaves * l) * E;
+          double in[kRB];
+#pragma unroll
+          for (int r = 0; r < kRB; ++r) in[r] = 0.0;
+          for (int pos = __builtin_amdgcn_readlane(o_cur, l) + lane; pos < end; pos += kWave)
+            term(pt[pos], p, in);
+          const double rs = wave_sum_fold<kRB>(in, lane);
+          if ((lane & 15) == (l & 15)) {
+            switch (l >> 4) {  // wave-uniform: one add, not four selected ones
+              case 0: acc[0] += rs; break;
+              case 1: acc[1] += rs; break;
+              case 2: acc[2] += rs; break;
+              default: acc[3] += rs; break;
+            }
+          }
+        }
+        o_cur = o_nxt;
+        o_nxt = o_after;
+        continue;
+      }
       // the momenta of this lane's group with terms in this segment
       const int g4 = lane >> 4, ls = lane & 15;
       unsigned long long todo =
@@ -436,35 +508,7 @@ __global__ __launch_bounds__(kNT) void tab_seg_kernel(TabArgs a, const unsigned 
         for (; run.pos < run.end; run.pos += 16) {
           const unsigned e = run.e;
           if (run.pos + 16 < run.end) run.e = run.pt[run.pos + 16];
-          int i, j;
-          if constexpr (PACKED) {
-            i = (int)(e >> 8);
-            j = (int)(e & 255u);
-          } else {
-            // e = i n_a + j (exact: e < 2^16, and e + 1/2 is at least
-            // 1/(2 n_a) away from a multiple of n_a)
-            i = (int)(((float)e + 0.5f) * inv_na);
-            j = (int)e - i * n_a;
-          }
-          const double *rad = lrad + i * kRS;
-          const double q = rad[0];
-          const double qm = q - p;
-          const double ah = (qm * qm) * a.inv_h;
-          const double bh = ((2.0 * q) * p) * a.inv_h;
-          const double t = fmin(__builtin_fma(bh, lang[2 * j], ah), a.t_last);
-          int k = (int)t;
-          k = k < k_last ? k : k_last;
-          const double f = t - (double)k;
-          const double mu = lang[2 * j + 1];
-          // k lies in the segment by construction; the clamp only keeps the
-          // LDS index in bounds
-          int x = k - T0;
-          x = x < 0 ? 0 : (x > kC - 1 ? kC - 1 : x);
-#pragma unroll
-          for (int r = 0; r < kRB; ++r) {
-            const double g0 = lg[r * kRowLds + x], g1 = lg[r * kRowLds + x + 1];
-            in[r] = __builtin_fma(rad[1 + r] * mu, __builtin_fma(f, g1 - g0, g0), in[r]);
-          }
+          term(e, p, in);
         }
         const double rs = fold16(in, lane);
         const int t = run.l >> 2;
@@ -477,10 +521,10 @@ __global__ __launch_bounds__(kNT) void tab_seg_kernel(TabArgs a, const unsigned 
       o_nxt = o_after;
     }
     {
-      const int r = (lane >> 2) & 3;
+      const int r = WIDE ? lane >> 4 : (lane >> 2) & 3;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const int l = 4 * (4 * k + (lane & 3)) + (lane >> 4);
+        const int l = WIDE ? 16 * k + (lane & 15) : 4 * (4 * k + (lane & 3)) + (lane >> 4);
         const int64_t ip = p_lo + wave + (int64_t)kWaves * l;
         if (r < nrb && ip < p_hi) part[((int64_t)c * a.n_rows + r0 + r) * a.n_p + ip] = acc[k];
       }
@@ -537,9 +581,13 @@ int launch_tab_seg(const TabArgs &t, const TabSegShape &s, const TabSegBufs &b, 
   if (t.n_p <= 0 || t.n_rows <= 0) return 0;
   hipStream_t st = (hipStream_t)stream;
   static const bool once =
-      ((void)hipFuncSetAttribute((const void *)&tab_seg_kernel<true>,
+      ((void)hipFuncSetAttribute((const void *)&tab_seg_kernel<true, false>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
-       (void)hipFuncSetAttribute((const void *)&tab_seg_kernel<false>,
+       (void)hipFuncSetAttribute((const void *)&tab_seg_kernel<true, true>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
+       (void)hipFuncSetAttribute((const void *)&tab_seg_kernel<false, false>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
+       (void)hipFuncSetAttribute((const void *)&tab_seg_kernel<false, true>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
        (void)hipFuncSetAttribute((const void *)&tab_seg_sort_kernel<kWave>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
@@ -555,15 +603,13 @@ int launch_tab_seg(const TabArgs &t, const TabSegShape &s, const TabSegBufs &b, 
                      dim3((unsigned)t.n_p), dim3(kSortW * kWave),
                      sizeof(int) * sort_parts(half ? kWave / 2 : kWave) * s.n_seg, st, t, b.terms,
                      b.offs, b.hist, s.n_seg);
-  if (term_packed(t))
-    hipLaunchKernelGGL(tab_seg_kernel<true>, dim3((unsigned)n_cu), dim3(kNT), (size_t)s.lds, st, t,
-                       (const unsigned *)b.hist, (const uint16_t *)b.terms, (const int *)b.offs,
-                       b.counter, b.part, s.n_seg, s.n_super, s.n_batch, s.target);
-  else
-    hipLaunchKernelGGL(tab_seg_kernel<false>, dim3((unsigned)n_cu), dim3(kNT), (size_t)s.lds, st,
-                       t, (const unsigned *)b.hist, (const uint16_t *)b.terms,
-                       (const int *)b.offs, b.counter, b.part, s.n_seg, s.n_super, s.n_batch,
-                       s.target);
+  const bool wide = tab_seg_wide(t.n_r, t.n_a);
+  const auto kernel = term_packed(t)
+                          ? (wide ? tab_seg_kernel<true, true> : tab_seg_kernel<true, false>)
+                          : (wide ? tab_seg_kernel<false, true> : tab_seg_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)n_cu), dim3(kNT), (size_t)s.lds, st, t,
+                     (const unsigned *)b.hist, (const uint16_t *)b.terms, (const int *)b.offs,
+                     b.counter, b.part, s.n_seg, s.n_super, s.n_batch, s.target);
   const int64_t n = t.n_p * t.n_rows;
   hipLaunchKernelGGL(tab_seg_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, t,
                      (const double *)b.part, s.n_super);
