@@ -11,6 +11,8 @@
 
 namespace frg {
 
+constexpr int64_t kPflowRhsFused = 4096;  // see pflow_device
+
 static int check_pflow(const frg_pflow &pf, int64_t n_flows) {
   if (pf.d < 3 || pf.d > 8) return fail(FRG_E_INVAL, "pflow.d=%d outside [3, 8]", pf.d);
   if (pf.reg != FRG_REG_EXP && pf.reg != FRG_REG_LITIM)
@@ -118,7 +120,11 @@ int Ctx::pflow_device(const frg_pflow &pf, int64_t n, const double *lam3, const 
   int W = 1;
   int64_t sblocks = 0;
   rc = tab_config(tb, lds_rows, W, sblocks, true);
-  const bool pull = tune.pflow_fused && lds_rows && pflow_pull_lds_bytes(tb) <= 150 * 1024;
+  // (a lone right-hand side of long rows prepares each row once: in the fused form
+  // every workgroup of a flow forms it, 2 flows of 6000 nodes, 64 x 6 nodes: 110 us
+  // against 84, 5000 nodes 62 against 61; one of short rows has a launch less)
+  const bool pull = tune.pflow_fused && lds_rows && pflow_pull_lds_bytes(tb) <= 150 * 1024 &&
+                    (solve || ns <= kPflowRhsFused);
   auto set_scale = [&](double t, double tn) {
     a.k = pf.lambda * std::exp(t);
     a.k2 = a.k * a.k;
