@@ -151,8 +151,14 @@ int frg_integrate(frg_ctx *ctx, const frg_set *sets, int32_t n_sets, int32_t mem
  * per (p, node) and reused for every mass.  Large calls with many masses form
  * the sum at 32 masses per factor of 16 in m^2 + k^2 and interpolate the others
  * (the interpolant differs from the sum by less than 1e-17 relative, far below
- * rounding; masses in no such range are summed themselves).  err_est /
- * used_fp64 as in frg_set (n_p * n_m entries, optional). */
+ * rounding; masses in no such range are summed themselves).  Such a call agrees
+ * with the direct form to rounding, so the last bits of a result depend on
+ * whether its call is interpolated: on n_p, n_m, the rule's size and the spread of
+ * the call's masses, on the device and the context's HBM budget, and on stream
+ * capture (a captured call takes the direct form).  Among interpolated calls a
+ * momentum's results do not depend on the other momenta; knob "grid_form" 3 gives
+ * every result the same bits in every call.  err_est / used_fp64 as in frg_set
+ * (n_p * n_m entries, optional). */
 int frg_integrate_grid(frg_ctx *ctx, const frg_quad *quad, int64_t n_p, const double *p,
                        int64_t n_m, const double *m2, double *out, double *err_est,
                        uint8_t *used_fp64, int32_t mem, void *hip_stream);
@@ -436,9 +442,11 @@ int frg_server_stats(frg_ctx *ctx, int64_t *flows_done, int64_t *launches, doubl
  * synchronises the stream) and keeps the fastest.  cache_path (optional,
  * NULL = keep the current one) names a text file read now and rewritten
  * after each tuning.  The environment variables FRG_AUTOTUNE and
- * FRG_AUTOTUNE_CACHE set the same at frg_create.  The summation order of
- * every result is fixed by (n_radial, n_angular): no launch shape changes a
- * result. */
+ * FRG_AUTOTUNE_CACHE set the same at frg_create.  Within a form the summation
+ * order of every result is fixed by (n_radial, n_angular), and the form does not
+ * depend on the tuned choices: no launch shape changes a result.  A grid that is
+ * interpolated in the mass is tuned too, for captured calls of its key, which
+ * take the direct form. */
 int frg_autotune(frg_ctx *ctx, int32_t mode, const char *cache_path);
 
 /* Set / read one default launch-shape knob: "grid_M" (4, 8, 16), "grid_W"
@@ -453,11 +461,13 @@ int frg_autotune(frg_ctx *ctx, int32_t mode, const char *cache_path);
  * nested evaluation on the vector units, at most 8 masses per wave; the two
  * agree to a few ulp), "fv_persistent" (finite-volume solves, 1: one
  * workgroup per flow runs the steps with its cells in LDS, the default up to
- * 3339 cells, more take two launches per stage; 0: two launches per stage;
- * the same bits), "pflow_fused" (momentum-dependent flows with rows in LDS,
- * 1: one launch per RK4 stage, each workgroup redoing the previous stage's
- * update for its row, the default; 0: a diagram launch and a stage launch
- * per stage; the same bits), "vertex_W" (vertex diagrams whose coefficient
+ * 3339 cells, more take two launches per stage, as do flows of many cells or
+ * nodes where the budget has no room for the table of radial sums; 0: two
+ * launches per stage; the same bits), "pflow_fused" (momentum-dependent flows
+ * with rows in LDS, 1: one launch per RK4 stage, each workgroup redoing the
+ * previous stage's update for its row, the default; 0: a diagram launch and a
+ * stage launch per stage, which a lone right-hand side of more than 4096 nodes
+ * takes in any case; the same bits), "vertex_W" (vertex diagrams whose coefficient
  * table takes over half the LDS: waves of the one workgroup per CU, 1..12,
  * default 12; above 8 only for the matrix-core form with groups of up to 16
  * azimuthal terms, else 8), "server_zero_copy" (flow server, 1: the LPA kernel reads
@@ -470,8 +480,11 @@ int frg_autotune(frg_ctx *ctx, int32_t mode, const char *cache_path);
  * "tab_pw" (momenta per wave, 1..64), "tab_lds_nodes" (2..6144),
  * "tab_pairs" (1: rows in LDS as (value, slope) pairs, the default; 0: as
  * values; the same bits), "tab_rb" (rows in LDS per workgroup, sharing every
- * coordinate: 0 auto (two where there are two and they fit), 1, 2 or 4; the
- * same bits), "tab_rW" (waves of such a workgroup, 1..16, default 16),
+ * coordinate: 0 auto (two where there are two and they fit, and four for
+ * momentum-dependent flows where workgroups of 16 waves with one momentum each then
+ * fill the chip), 1, 2 or 4; the same bits), "tab_rW" (waves of such a workgroup,
+ * 1..16, default 16; halved, down to 4, while each has one momentum and CUs are left
+ * over; the same bits),
  * "tab_seg" (rows that do not fit in LDS: 0 read
  * through the caches; 1 the segmented form; 2 the segmented form for tables
  * above 256 MiB, the default; the forms agree to rounding), and for cache-streamed rows "tab_wpc" (workgroups per

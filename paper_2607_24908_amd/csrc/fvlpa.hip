@@ -322,7 +322,7 @@ __global__ __launch_bounds__(256) void fv_stage_kernel(FvArgs a) {
 // the one CU of a flow, one wave on most SIMDs: 0.57 us per stage for one wave
 // (63 cells), 0.68 for the four of 200 cells and 0.85 for the five of 256 cells, whose panel
 // coefficients (84 KB per stage) also share the CU's LDS port.  128 flows of 256
-// cells, 64 nodes, N = 4, 2000 steps: 5.1 ms.  With the radial sums as rational
+// cells, 64 nodes, N = 4, 2000 steps: 5.2 ms.  With the radial sums as rational
 // groups, one lane per mass, four barriers per stage and the scales formed by
 // every thread it took 25.9 ms; this kernel's sums with a quad of lanes per
 // interface (each lane one mass, two barriers) 8.6 ms, bound by instruction

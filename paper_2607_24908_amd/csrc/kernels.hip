@@ -627,7 +627,7 @@ __device__ __forceinline__ LpaSums lpa_sums(const double *poly, const double *ta
 // flow fills the chip with whole waves.
 //
 // Bound by launch and memory latency: arguments, U, panels, stores, one after
-// the other.  13 flows of 128 to 1024 points, with Jacobian bands: 4.4 us (one
+// the other.  13 flows of 128 to 1024 points, with Jacobian bands: 4.1 us (one
 // wave per grid point with its lanes over the 64 radial nodes took 10.2 us,
 // and the upload of the job table before it 3.1 us); in the server's pinned
 // buffers 5.6 us per batch (8.6 us).  One flow of 1024 points and nodes, called from
